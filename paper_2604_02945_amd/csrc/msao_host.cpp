@@ -6,12 +6,14 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
 #include <numeric>
 #include <string>
+#include <thread>
 #include <vector>
 
 #include "../../include/msao.h"
@@ -19,14 +21,22 @@
 
 using namespace msao;
 
+// Slots of pinned staging: so many uploads may be waiting on the GPU before
+// the host waits for the oldest.
+constexpr int kStageSlots = 4;
+
 struct msao_ctx {
     int device = 0;
     std::string err;
-    // two pinned staging slots, each guarded by the event of its last upload
-    void* stage[2] = {nullptr, nullptr};
-    size_t stage_cap[2] = {0, 0};
-    hipEvent_t stage_ev[2] = {nullptr, nullptr};
-    bool stage_used[2] = {false, false};
+    // pinned staging slots, used in turn. The upload kernel's block b sets
+    // stage_done[slot * kUploadMaxBlocks + b] to stage_ticket[slot] once it
+    // has read the slot; until its stage_blocks[slot] blocks have, the slot
+    // is not written again.
+    void* stage[kStageSlots] = {};
+    size_t stage_cap[kStageSlots] = {};
+    uint32_t* stage_done = nullptr;   // pinned
+    uint32_t stage_ticket[kStageSlots] = {};
+    int stage_blocks[kStageSlots] = {};
     int next_slot = 0;
     // profiling: an event pair around every launch, averaged per kernel on query
     bool profiling = false;
@@ -127,8 +137,7 @@ msao_status validate_impl(const msao_segment* segs, int n, int R, const msao_par
 struct Plan {
     std::vector<DevSeg> seg;
     std::vector<int32_t> wi_b, wi_e;             // per segment: its scoring work items [wi_b, wi_e) (host only)
-    std::vector<int32_t> seg_gi, tseg;           // seg_gi: per-segment prefix of gather items (host only)
-    std::vector<int32_t> wi_seg, gi_seg;         // segment of every work item
+    std::vector<int32_t> tseg;
     std::vector<RmEntry> rm;
     std::vector<WiRange> rm_rng;
     std::vector<float> alpha;
@@ -137,26 +146,26 @@ struct Plan {
     int max_n = 0;                 // largest selection (LDS key staging)
     int big_seg = kPostBigSegment; // selections this large take 1024-thread blocks
     std::vector<SelUnit> sel_unit; // one selection block each: a segment, or a frame (per-frame scope)
-    std::vector<int32_t> hi_seg;   // SimHash calls: segment of each hash tile
+    int n_hi = 0;                  // SimHash calls: hash tiles
     bool any_temporal = false, any_guided = false;
     bool any_copy = false;         // some segment is compacted by the scoring pass
     // learned calls (Eq. 3 heads, Eq. 6 descriptors)
     bool learned = false;
-    std::vector<int32_t> hb_seg;   // segment of each head block (one per frame of a segment with a head)
+    int n_hb = 0;                  // head blocks (one per frame of a segment with a head)
     int max_head_p = 0;            // largest frame among segments with a head
     int mlp_hidden = 0;            // > 0: the relevance MLP's u = W1[:, :P] p + b1 per request
     size_t off_hbseg = 0, off_partial_x = 0, off_proj = 0, off_head_count = 0, off_mlp_u = 0, off_mas = 0;
     size_t off_seg = 0, off_wi = 0, off_gi = 0, off_rmoff = 0, off_rmseg = 0, off_tseg = 0, off_alpha = 0;
     size_t off_selu = 0, off_hiseg = 0, off_clseg = 0, off_frseg = 0;
-    std::vector<int32_t> frame_seg;  // segment of every temporal frame
+    int longest_run = 0;             // longest run of one segment in an array of item segments (not counting shorter kinds)
     bool simhash_d = false;        // a run with SimHash: d of temporal segments in K-bit units
     size_t off_hdsum = 0;          // [R*4] SimHash Dsum (simhash_d without clip_fused)
     bool clip_fused = false;       // a run with SimHash whose clips k_clip scores and hashes in one pass
     int clip_dtype = -1, clip_bits = 0;
-    std::vector<int32_t> cl_seg;   // segment of each k_clip block
+    int n_cl = 0;                  // k_clip blocks
     int n_wi_score = 0;            // k_score's work items [0, n_wi_score); the fused clips' follow
     int n_wi_pair = 0;             // k_pair's work items [0, n_wi_pair), whole blocks
-    size_t table_bytes = 0, off_partial = 0, total_bytes = 0;
+    size_t copy_bytes = 0, table_bytes = 0, off_partial = 0, total_bytes = 0;
 };
 
 size_t table_layout(Plan& pl, int n, int R, int64_t n_wi, int64_t n_gwi, int64_t n_hb, int64_t n_sel, int64_t n_hi,
@@ -168,15 +177,18 @@ size_t table_layout(Plan& pl, int n, int R, int64_t n_wi, int64_t n_gwi, int64_t
         o = align_up(o + bytes, 16);
         return at;
     };
+    // staged tables, the segment records first
     pl.off_seg = take(sizeof(DevSeg) * (size_t)std::max(n, 1));
-    pl.off_wi = take(sizeof(int32_t) * (size_t)std::max<int64_t>(n_wi, 1));
-    pl.off_gi = take(sizeof(int32_t) * (size_t)std::max<int64_t>(n_gwi, 1));
     pl.off_rmoff = take(sizeof(RmEntry) * (size_t)std::max(R * kNumMod, 1));
     pl.off_rmseg = take(sizeof(WiRange) * (size_t)std::max(n, 1));
     pl.off_tseg = take(sizeof(int32_t) * (size_t)std::max(n, 1));
     pl.off_alpha = take(sizeof(float) * (size_t)std::max(R * kNumMod, 1));
-    pl.off_hbseg = take(sizeof(int32_t) * (size_t)std::max<int64_t>(n_hb, 1));
     pl.off_selu = take(sizeof(SelUnit) * (size_t)std::max<int64_t>(n_sel, 1));
+    pl.copy_bytes = o;
+    // arrays that the upload kernel writes from the segment records
+    pl.off_wi = take(sizeof(int32_t) * (size_t)std::max<int64_t>(n_wi, 1));
+    pl.off_gi = take(sizeof(int32_t) * (size_t)std::max<int64_t>(n_gwi, 1));
+    pl.off_hbseg = take(sizeof(int32_t) * (size_t)std::max<int64_t>(n_hb, 1));
     pl.off_hiseg = take(sizeof(int32_t) * (size_t)std::max<int64_t>(n_hi, 1));
     pl.off_clseg = take(sizeof(int32_t) * (size_t)std::max<int64_t>(n_cl, 1));
     pl.off_frseg = take(sizeof(int32_t) * (size_t)std::max<int64_t>(n_fr, 1));
@@ -220,17 +232,16 @@ void build_plan(const msao_ctx* ctx, const msao_segment* segs, int n, int R, con
     const bool per_frame = (p->flags & MSAO_FLAG_SELECT_PER_FRAME) != 0;
     pl.big_seg = ctx ? ctx->post_big_segment : kPostBigSegment;
     pl.sel_unit.clear();
-    pl.hi_seg.clear();
+    pl.n_hi = 0;
     pl.max_n = 0;
     pl.learned = learned;
     pl.mlp_hidden = learned ? mlp_hidden : 0;
-    pl.hb_seg.clear();
+    pl.n_hb = 0;
     pl.max_head_p = 0;
     pl.seg.resize((size_t)n);
     pl.wi_b.assign((size_t)std::max(n, 1), 0);
     pl.wi_e.assign((size_t)std::max(n, 1), 0);
-    pl.seg_gi.assign((size_t)n + 1, 0);
-    pl.cl_seg.clear();
+    pl.n_cl = 0;
     pl.clip_fused = false;
     // a run with SimHash scores and hashes its clips in one pass when every
     // clip's tiles of 16 frames fit a 32-bit buffer resource
@@ -286,19 +297,18 @@ void build_plan(const msao_ctx* ctx, const msao_segment* segs, int n, int R, con
         d.frame_off = d.temporal ? (int32_t)frame : -1;
         d.nchunk = s.hidden * es / 16;
         d.A_s = (int32_t)std::ceil((double)p->tau_s * (double)s.hidden);
-        d.L_s = q24(p->lambda_s[s.modality]);
-        d.L_t = q24(p->lambda_t[s.modality]);
+        const uint32_t L_s = q24(p->lambda_s[s.modality]), L_t = q24(p->lambda_t[s.modality]);
         d.lam_s = p->lambda_s[s.modality];
         d.lam_t = p->lambda_t[s.modality];
         d.E = s.hidden;
-        d.key_ms = d.L_s;
-        d.key_mt = d.L_t;
+        d.key_ms = L_s;
+        d.key_mt = L_t;
         if (simhash_d && hashes && d.temporal) {
             // d counts K SimHash bits: keys in units of C K / g
             const int64_t K = hashes[i].bits, g = std::gcd((int64_t)s.hidden, K);
             d.E = (int32_t)K;
-            d.key_ms = (uint64_t)d.L_s * (uint64_t)(K / g);
-            d.key_mt = (uint64_t)d.L_t * (uint64_t)(s.hidden / g);
+            d.key_ms = (uint64_t)L_s * (uint64_t)(K / g);
+            d.key_mt = (uint64_t)L_t * (uint64_t)(s.hidden / g);
         }
         // selections: the segment, or each of its frames (per-frame scope);
         // a large one is written by several blocks, each of a slice
@@ -306,7 +316,7 @@ void build_plan(const msao_ctx* ctx, const msao_segment* segs, int n, int R, con
         // a learned run ranks a segment with a head by its Eq. 3 importance
         const bool by_imp = select_imp && learned && heads && heads[i].weight && N > 0;
         const int kind = by_imp ? kKeyImp
-                         : d.temporal && d.L_t > 0 ? (d.L_s > 0 ? kKeyFull : kKeyE) : (d.L_s > 0 ? kKeyZ : kKeyZero);
+                         : d.temporal && L_t > 0 ? (L_s > 0 ? kKeyFull : kKeyE) : (L_s > 0 ? kKeyZ : kKeyZero);
         auto push_selection = [&](int frame, int n_u, int kfix) {
             const int parts = n_u >= pl.big_seg                 ? (n_u + kSelBigPartTokens - 1) / kSelBigPartTokens
                               : n_u >= kSelSplitMin && split_mid ? (n_u + kSelPartTokens - 1) / kSelPartTokens
@@ -354,12 +364,12 @@ void build_plan(const msao_ctx* ctx, const msao_segment* segs, int n, int R, con
             d.cap = std::max<int32_t>(d.cap, s.n_frames * (int32_t)keep_count(s.keep_ratio, s.tokens_per_frame));
         if (hashes) {
             // SimHash blocks of kHashBlockTokens tokens (segments without a hash get zeros)
-            d.hi_begin = (int32_t)pl.hi_seg.size();
+            d.hi_begin = pl.n_hi;
             if (d.temporal) {
                 d.planes = (const uint8_t*)hashes[i].planes;
                 d.hash_bits = hashes[i].bits;
             }
-            for (int64_t r = 0; r < N; r += kHashBlockTokens) pl.hi_seg.push_back(i);
+            pl.n_hi += (int)((N + kHashBlockTokens - 1) / kHashBlockTokens);
         }
         d.fused = (fuse && d.temporal) ? 1 : 0;
         // (a fused clip's kept rows are always left to the gather)
@@ -369,8 +379,8 @@ void build_plan(const msao_ctx* ctx, const msao_segment* segs, int n, int R, con
             d.head_b = heads[i].bias;
             d.grid_w = heads[i].grid_w > 0 ? heads[i].grid_w : s.tokens_per_frame;
             d.pool = heads[i].pool;
-            d.hb_begin = (int32_t)pl.hb_seg.size();
-            for (int f = 0; f < s.n_frames; ++f) pl.hb_seg.push_back(i);
+            d.hb_begin = pl.n_hb;
+            pl.n_hb += s.n_frames;
             pl.max_head_p = std::max(pl.max_head_p, s.tokens_per_frame);
         }
         // scoring work items, one wavefront each
@@ -448,8 +458,8 @@ void build_plan(const msao_ctx* ctx, const msao_segment* segs, int n, int R, con
         }
         pl.wi_e[(size_t)i] = items;  // the item count until the ranges are laid out below
         d.g_begin = gi;
-        if (!d.copy_in_score) gi += (d.cap + kGatherRows - 1) / kGatherRows;
-        pl.seg_gi[(size_t)i + 1] = gi;
+        d.n_gather = d.copy_in_score ? 0 : (d.cap + kGatherRows - 1) / kGatherRows;
+        gi += d.n_gather;
         if (d.k < 0) pl.any_guided = true;
         if (d.copy_in_score) pl.any_copy = true;
         tok += N;
@@ -478,8 +488,8 @@ void build_plan(const msao_ctx* ctx, const msao_segment* segs, int n, int R, con
         pl.wi_b[(size_t)i] = wi;
         wi += items;
         pl.wi_e[(size_t)i] = wi;
-        d.cl_begin = (int32_t)pl.cl_seg.size();
-        for (int b = 0; b < (items + kClipWaves - 1) / kClipWaves; ++b) pl.cl_seg.push_back(i);
+        d.cl_begin = pl.n_cl;
+        pl.n_cl += (items + kClipWaves - 1) / kClipWaves;
     }
     pl.ntok = tok;
     pl.nframes = frame;
@@ -504,20 +514,16 @@ void build_plan(const msao_ctx* ctx, const msao_segment* segs, int n, int R, con
         pl.rm_rng[(size_t)count[(size_t)(s.request * kNumMod + s.modality)]++] =
             WiRange{pl.wi_b[(size_t)i], pl.wi_e[(size_t)i], i, 0};
     }
-    pl.wi_seg.resize((size_t)pl.n_wi);
-    pl.gi_seg.resize((size_t)pl.n_gwi);
     for (int i = 0; i < n; ++i) {
-        std::fill(pl.wi_seg.begin() + pl.wi_b[(size_t)i], pl.wi_seg.begin() + pl.wi_e[(size_t)i], i);
-        std::fill(pl.gi_seg.begin() + pl.seg_gi[(size_t)i], pl.gi_seg.begin() + pl.seg_gi[(size_t)i + 1], i);
+        DevSeg& d = pl.seg[(size_t)i];
+        d.n_items = pl.wi_e[(size_t)i] - pl.wi_b[(size_t)i];
+        const int longest = std::max(std::max(d.n_items, d.n_gather), d.T);
+        pl.longest_run = std::max(pl.longest_run, longest);
     }
     pl.alpha.assign((size_t)std::max(R * kNumMod, 1), 0.0f);
     if (alpha)
         for (int x = 0; x < R * kNumMod; ++x) pl.alpha[(size_t)x] = alpha[x];
-    pl.frame_seg.clear();
-    for (int i = 0; i < n; ++i)
-        if (pl.seg[(size_t)i].temporal) pl.frame_seg.insert(pl.frame_seg.end(), (size_t)pl.seg[(size_t)i].T, i);
-    table_layout(pl, n, R, pl.n_wi, pl.n_gwi, (int64_t)pl.hb_seg.size(), (int64_t)pl.sel_unit.size(),
-                 (int64_t)pl.hi_seg.size(), (int64_t)pl.cl_seg.size(), (int64_t)pl.frame_seg.size());
+    table_layout(pl, n, R, pl.n_wi, pl.n_gwi, pl.n_hb, (int64_t)pl.sel_unit.size(), pl.n_hi, pl.n_cl, pl.nframes);
     pl.off_partial = align_up(pl.table_bytes, kWsAlign);
     pl.total_bytes = pl.off_partial + sizeof(Partial) * (size_t)std::max(pl.n_wi, 1);
     pl.simhash_d = simhash_d && pl.any_temporal;
@@ -529,7 +535,7 @@ void build_plan(const msao_ctx* ctx, const msao_segment* segs, int n, int R, con
         pl.off_partial_x = align_up(pl.total_bytes, kWsAlign);
         pl.off_proj = align_up(pl.off_partial_x + sizeof(PartialX) * (size_t)std::max(pl.n_wi, 1), kWsAlign);
         pl.off_head_count = align_up(pl.off_proj + sizeof(float) * (size_t)std::max<int64_t>(pl.ntok, 1), kWsAlign);
-        pl.total_bytes = pl.off_head_count + sizeof(uint32_t) * std::max<size_t>(pl.hb_seg.size(), 1);
+        pl.total_bytes = pl.off_head_count + sizeof(uint32_t) * (size_t)std::max(pl.n_hb, 1);
         if (pl.mlp_hidden > 0) {
             pl.off_mlp_u = align_up(pl.total_bytes, kWsAlign);
             pl.total_bytes = pl.off_mlp_u + sizeof(float) * (size_t)pl.mlp_hidden * (size_t)std::max(R, 1);
@@ -580,41 +586,69 @@ msao_status reserve_stage(msao_ctx* ctx, int slot, size_t bytes)
     return MSAO_OK;
 }
 
-// Copy the tables into a pinned slot and enqueue its upload into the
-// workspace. With grow false a slot smaller than the tables is an error
-// instead of a new pinned allocation (msao_run_noalloc allocates nothing).
-msao_status upload(msao_ctx* ctx, const Plan& pl, void* ws, hipStream_t stream, bool grow = true)
+// Until the last upload from a slot has read it. That upload was launched
+// without an error on a stream that was not being captured, so it runs.
+void wait_stage(msao_ctx* ctx, int slot)
+{
+    uint32_t* done = ctx->stage_done + slot * kUploadMaxBlocks;
+    for (int b = 0; b < ctx->stage_blocks[slot]; ++b)
+        for (int spin = 0; __atomic_load_n(&done[b], __ATOMIC_ACQUIRE) != ctx->stage_ticket[slot]; ++spin)
+            if (spin >= 4096) std::this_thread::yield();
+    ctx->stage_blocks[slot] = 0;
+}
+
+// Put the tables into a pinned slot and enqueue the kernel that brings them
+// into the workspace. With grow false a slot smaller than the tables is an
+// error instead of a new pinned allocation (msao_run_noalloc allocates nothing).
+msao_status upload(msao_ctx* ctx, const Plan& pl, int n, void* ws, hipStream_t stream, bool grow = true)
 {
     const int slot = ctx->next_slot;
-    hipError_t e;
-    if (!grow && ctx->stage_cap[slot] < pl.table_bytes)
+    if (!grow && ctx->stage_cap[slot] < pl.copy_bytes)
         return fail(&ctx->err, MSAO_ERR_UNSUPPORTED, "per-call tables larger than the context's reserved staging");
-    ctx->next_slot ^= 1;
-    if (ctx->stage_used[slot]) {
-        if ((e = hipEventSynchronize(ctx->stage_ev[slot])) != hipSuccess) return hip_fail(ctx, e, "hipEventSynchronize");
-    }
-    if (ctx->stage_cap[slot] < pl.table_bytes) MSAO_TRY(reserve_stage(ctx, slot, pl.table_bytes));
+    ctx->next_slot = (slot + 1) % kStageSlots;
+    wait_stage(ctx, slot);
+    if (ctx->stage_cap[slot] < pl.copy_bytes) MSAO_TRY(reserve_stage(ctx, slot, pl.copy_bytes));
     uint8_t* h = (uint8_t*)ctx->stage[slot];
-    std::memset(h, 0, pl.table_bytes);
     auto put = [&](size_t off, const void* src, size_t bytes) {
         if (bytes) std::memcpy(h + off, src, bytes);
     };
     put(pl.off_seg, pl.seg.data(), sizeof(DevSeg) * pl.seg.size());
-    put(pl.off_wi, pl.wi_seg.data(), sizeof(int32_t) * pl.wi_seg.size());
-    put(pl.off_gi, pl.gi_seg.data(), sizeof(int32_t) * pl.gi_seg.size());
     put(pl.off_rmoff, pl.rm.data(), sizeof(RmEntry) * pl.rm.size());
     put(pl.off_rmseg, pl.rm_rng.data(), sizeof(WiRange) * pl.rm_rng.size());
     put(pl.off_tseg, pl.tseg.data(), sizeof(int32_t) * pl.tseg.size());
     put(pl.off_alpha, pl.alpha.data(), sizeof(float) * pl.alpha.size());
-    put(pl.off_hbseg, pl.hb_seg.data(), sizeof(int32_t) * pl.hb_seg.size());
     put(pl.off_selu, pl.sel_unit.data(), sizeof(SelUnit) * pl.sel_unit.size());
-    put(pl.off_hiseg, pl.hi_seg.data(), sizeof(int32_t) * pl.hi_seg.size());
-    put(pl.off_clseg, pl.cl_seg.data(), sizeof(int32_t) * pl.cl_seg.size());
-    put(pl.off_frseg, pl.frame_seg.data(), sizeof(int32_t) * pl.frame_seg.size());
-    if ((e = hipMemcpyAsync(ws, h, pl.table_bytes, hipMemcpyHostToDevice, stream)) != hipSuccess)
-        return hip_fail(ctx, e, "hipMemcpyAsync");
-    if ((e = hipEventRecord(ctx->stage_ev[slot], stream)) != hipSuccess) return hip_fail(ctx, e, "hipEventRecord");
-    ctx->stage_used[slot] = true;
+    uint8_t* b = (uint8_t*)ws;
+    UploadArgs a;
+    std::memset(&a, 0, sizeof a);
+    a.src = h;
+    a.dst = b;
+    a.copy_bytes = (uint32_t)pl.copy_bytes;
+    a.n = n;
+    a.copy_units = (int32_t)((pl.copy_bytes + kUploadCopyBytes - 1) / kUploadCopyBytes);
+    // units per segment: one for each stripe of the longest run, while they are not many
+    a.fill_parts = std::min((pl.longest_run + kUploadFill - 1) / kUploadFill, 32);
+    a.fill_parts = std::max(a.fill_parts, 1);
+    a.any_hash = pl.n_hi > 0 ? 1 : 0;
+    a.wi_seg = (int32_t*)(b + pl.off_wi);
+    a.gi_seg = (int32_t*)(b + pl.off_gi);
+    a.hb_seg = (int32_t*)(b + pl.off_hbseg);
+    a.frame_seg = (int32_t*)(b + pl.off_frseg);
+    a.cl_seg = (int32_t*)(b + pl.off_clseg);
+    a.hi_seg = (int32_t*)(b + pl.off_hiseg);
+    // a graph's replays read the slot again, whenever they come: no word from them
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &cap) != hipSuccess) (void)hipGetLastError();
+    const bool tracked = cap == hipStreamCaptureStatusNone;
+    if (tracked) {
+        a.done = ctx->stage_done + slot * kUploadMaxBlocks;
+        a.ticket = ++ctx->stage_ticket[slot];
+    }
+    const int64_t units = a.copy_units + (int64_t)n * a.fill_parts;
+    const int blocks = (int)std::min<int64_t>(units, kUploadMaxBlocks);
+    const int rc = launch_upload(a, blocks, stream);
+    if (rc != 0) return hip_fail(ctx, (hipError_t)rc, "table upload");
+    if (tracked) ctx->stage_blocks[slot] = blocks;
     return MSAO_OK;
 }
 
@@ -635,16 +669,16 @@ Tables device_tables(const Plan& pl, void* ws, int n, int R, const msao_params* 
     t.proj = pl.learned ? (float*)(b + pl.off_proj) : nullptr;
     t.head_count = pl.learned ? (uint32_t*)(b + pl.off_head_count) : nullptr;
     t.hb_seg = (const int32_t*)(b + pl.off_hbseg);
-    t.n_hb = (int32_t)pl.hb_seg.size();
+    t.n_hb = pl.n_hb;
     t.sel_unit = (const SelUnit*)(b + pl.off_selu);
     t.hi_seg = (const int32_t*)(b + pl.off_hiseg);
     t.hdsum = pl.simhash_d && !pl.clip_fused ? (const uint64_t*)(b + pl.off_hdsum) : nullptr;
     t.cl_seg = (const int32_t*)(b + pl.off_clseg);
     t.frame_seg = (const int32_t*)(b + pl.off_frseg);
-    t.n_cl = (int32_t)pl.cl_seg.size();
+    t.n_cl = pl.n_cl;
     t.n_wi_score = pl.n_wi_score;
     t.n_wi_pair = pl.n_wi_pair;
-    t.n_hi = (int32_t)pl.hi_seg.size();
+    t.n_hi = pl.n_hi;
     t.n = n;
     t.R = R;
     t.n_wi = pl.n_wi;
@@ -892,17 +926,17 @@ msao_status msao_create(msao_ctx** out, int device)
     msao_ctx* c = new msao_ctx();
     c->device = device;
     DeviceGuard guard(device);
-    for (int i = 0; i < 2; ++i) {
-        if ((e = hipEventCreateWithFlags(&c->stage_ev[i], hipEventDisableTiming)) != hipSuccess) {
-            g_err = std::string("hipEventCreate: ") + hipGetErrorString(e);
-            msao_destroy(c);
-            return MSAO_ERR_HIP;
-        }
+    if ((e = hipHostMalloc((void**)&c->stage_done, sizeof(uint32_t) * kStageSlots * kUploadMaxBlocks,
+                           hipHostMallocDefault)) != hipSuccess) {
+        g_err = std::string("hipHostMalloc: ") + hipGetErrorString(e);
+        msao_destroy(c);
+        return MSAO_ERR_HIP;
     }
-    // set-up of msao_run_noalloc, which allocates nothing: both staging slots
+    std::memset(c->stage_done, 0, sizeof(uint32_t) * kStageSlots * kUploadMaxBlocks);
+    // set-up of msao_run_noalloc, which allocates nothing: the staging slots
     // hold its largest tables, and this device's copy of the library's
     // scratch array has its device address looked up
-    for (int i = 0; i < 2; ++i) {
+    for (int i = 0; i < kStageSlots; ++i) {
         if (reserve_stage(c, i, kNoAllocTableBytes) != MSAO_OK) {
             g_err = c->err;
             msao_destroy(c);
@@ -928,13 +962,11 @@ void msao_destroy(msao_ctx* ctx)
 {
     if (!ctx) return;
     DeviceGuard guard(ctx->device);
-    for (int i = 0; i < 2; ++i) {
-        if (ctx->stage_ev[i]) {
-            if (ctx->stage_used[i]) (void)hipEventSynchronize(ctx->stage_ev[i]);
-            (void)hipEventDestroy(ctx->stage_ev[i]);
-        }
+    for (int i = 0; i < kStageSlots; ++i) {
+        wait_stage(ctx, i);
         if (ctx->stage[i]) (void)hipHostFree(ctx->stage[i]);
     }
+    if (ctx->stage_done) (void)hipHostFree(ctx->stage_done);
     for (int k = 0; k < MSAO_NUM_KERNELS; ++k)
         for (auto& pr : ctx->rec[k]) {
             (void)hipEventSynchronize(pr.second);
@@ -993,7 +1025,7 @@ msao_status msao_mas_score(msao_ctx* ctx, const msao_segment* segs, int n, int R
     if (req) MSAO_TRY(check_out_alignment(ctx, {{req->agg, 8}, {req->rho, 4}, {req->temporal, 4}, {req->beta, 4}, {req->mas, 4}}));
     DeviceGuard guard(ctx->device);
     hipStream_t st = (hipStream_t)stream;
-    MSAO_TRY(upload(ctx, pl, ws, st));
+    MSAO_TRY(upload(ctx, pl, n, ws, st));
     ScoreArgs sa;
     std::memset(&sa, 0, sizeof sa);
     sa.t = device_tables(pl, ws, n, R, params);
@@ -1031,7 +1063,7 @@ msao_status msao_temporal_redundancy(msao_ctx* ctx, const msao_segment* segs, in
     if (frm) MSAO_TRY(check_out_alignment(ctx, {{frm->dframe, 8}, {frm->sim, 4}, {frm->gamma, 4}}));
     DeviceGuard guard(ctx->device);
     hipStream_t st = (hipStream_t)stream;
-    MSAO_TRY(upload(ctx, pl, ws, st));
+    MSAO_TRY(upload(ctx, pl, n, ws, st));
     ScoreArgs sa;
     std::memset(&sa, 0, sizeof sa);
     sa.t = device_tables(pl, ws, n, R, params);
@@ -1067,7 +1099,7 @@ msao_status msao_temporal_simhash(msao_ctx* ctx, const msao_segment* segs, int n
     if (frm) MSAO_TRY(check_out_alignment(ctx, {{frm->dframe, 8}, {frm->sim, 4}, {frm->gamma, 4}}));
     DeviceGuard guard(ctx->device);
     hipStream_t st = (hipStream_t)stream;
-    MSAO_TRY(upload(ctx, pl, ws, st));
+    MSAO_TRY(upload(ctx, pl, n, ws, st));
     HashArgs ha;
     std::memset(&ha, 0, sizeof ha);
     ha.t = device_tables(pl, ws, n, R, params);
@@ -1099,7 +1131,7 @@ msao_status msao_select_tokens(msao_ctx* ctx, const msao_segment* segs, int n, i
     MSAO_TRY(check_out_alignment(ctx, {{z, 4}, {d, 4}, {mas, 4}, {sel->kept_idx, 4}, {sel->kept_count, 4}}));
     DeviceGuard guard(ctx->device);
     hipStream_t st = (hipStream_t)stream;
-    MSAO_TRY(upload(ctx, pl, ws, st));
+    MSAO_TRY(upload(ctx, pl, n, ws, st));
     PostArgs pa;
     std::memset(&pa, 0, sizeof pa);
     pa.t = device_tables(pl, ws, n, R, params);
@@ -1131,7 +1163,7 @@ msao_status msao_compact(msao_ctx* ctx, const msao_segment* segs, int n, const i
     MSAO_TRY(check_compact_out(ctx, pl, segs, n, out, out_byte_off, out_bytes));
     DeviceGuard guard(ctx->device);
     hipStream_t st = (hipStream_t)stream;
-    MSAO_TRY(upload(ctx, pl, ws, st));
+    MSAO_TRY(upload(ctx, pl, n, ws, st));
     GatherArgs ga;
     std::memset(&ga, 0, sizeof ga);
     ga.t = device_tables(pl, ws, n, R, &p);
@@ -1204,7 +1236,7 @@ msao_status msao_mas_score_learned(msao_ctx* ctx, const msao_segment* segs, int 
     MSAO_TRY(check_out_alignment(ctx, {{importance, 4}, {alpha_out, 4}, {desc, 4}}));
     DeviceGuard guard(ctx->device);
     hipStream_t st = (hipStream_t)stream;
-    MSAO_TRY(upload(ctx, pl, ws, st));
+    MSAO_TRY(upload(ctx, pl, n, ws, st));
     ScoreArgs sa;
     std::memset(&sa, 0, sizeof sa);
     sa.t = device_tables(pl, ws, n, R, params);
@@ -1215,7 +1247,7 @@ msao_status msao_mas_score_learned(msao_ctx* ctx, const msao_segment* segs, int 
     sa.importance = importance;
     MSAO_TRY(launched(ctx, MSAO_KERNEL_SCORE, st, run_score, &sa));
     float* mlp_u = mlp ? (float*)((uint8_t*)ws + pl.off_mlp_u) : nullptr;
-    if (!pl.hb_seg.empty() || mlp) {
+    if (pl.n_hb > 0 || mlp) {
         HeadArgs ha;
         std::memset(&ha, 0, sizeof ha);
         ha.t = sa.t;
@@ -1425,7 +1457,7 @@ msao_status msao_run(msao_ctx* ctx, const msao_segment* segs, int n, int R, cons
     MSAO_TRY(check_run_outputs(ctx, pl, sv, tok, frm, req, sel, out, out_byte_off, out_bytes));
     DeviceGuard guard(ctx->device);
     hipStream_t st = (hipStream_t)stream;
-    MSAO_TRY(upload(ctx, pl, ws, st));
+    MSAO_TRY(upload(ctx, pl, n, ws, st));
     return enqueue_run(ctx, pl, device_tables(pl, ws, n, R, params), tok, frm, req, sel, out, out_bytes, st);
 }
 
@@ -1456,7 +1488,7 @@ msao_status msao_run_noalloc(msao_ctx* ctx, const msao_segment* segs, int n, int
     if (!ws) return fail(&ctx->err, MSAO_ERR_HIP, "the scratch array of this device was not set up");
     DeviceGuard guard(ctx->device);
     hipStream_t st = (hipStream_t)stream;
-    MSAO_TRY(upload(ctx, pl, ws, st, false));
+    MSAO_TRY(upload(ctx, pl, n, ws, st, false));
     return enqueue_run(ctx, pl, device_tables(pl, ws, n, R, params), tok, frm, req, sel, out, out_bytes, st);
 }
 
@@ -1479,7 +1511,7 @@ msao_status msao_run_simhash(msao_ctx* ctx, const msao_segment* segs, int n, int
     MSAO_TRY(check_out_alignment(ctx, {{sig, 8}}));
     DeviceGuard guard(ctx->device);
     hipStream_t st = (hipStream_t)stream;
-    MSAO_TRY(upload(ctx, pl, ws, st));
+    MSAO_TRY(upload(ctx, pl, n, ws, st));
     return enqueue_run(ctx, pl, device_tables(pl, ws, n, R, params), tok, frm, req, sel, out, out_bytes, st, sig);
 }
 
@@ -1502,7 +1534,7 @@ msao_status msao_run_learned(msao_ctx* ctx, const msao_segment* segs, int n, int
     MSAO_TRY(check_out_alignment(ctx, {{importance, 4}, {alpha_out, 4}, {desc, 4}}));
     DeviceGuard guard(ctx->device);
     hipStream_t st = (hipStream_t)stream;
-    MSAO_TRY(upload(ctx, pl, ws, st));
+    MSAO_TRY(upload(ctx, pl, n, ws, st));
     const Tables t = device_tables(pl, ws, n, R, params);
     // statistics, head projections (and the rows of segments kept whole)
     ScoreArgs sa;
@@ -1517,7 +1549,7 @@ msao_status msao_run_learned(msao_ctx* ctx, const msao_segment* segs, int n, int
     MSAO_TRY(launched(ctx, MSAO_KERNEL_SCORE, st, run_score, &sa));
     // Eq. 3 importance of the head segments, kept in the workspace for the selection
     float* mlp_u = mlp ? (float*)((uint8_t*)ws + pl.off_mlp_u) : nullptr;
-    if (!pl.hb_seg.empty() || mlp) {
+    if (pl.n_hb > 0 || mlp) {
         HeadArgs ha;
         std::memset(&ha, 0, sizeof ha);
         ha.t = t;
@@ -1593,7 +1625,7 @@ msao_status msao_plan_create(msao_ctx* ctx, const msao_segment* segs, int n, int
     msao_status st = check_ws(ctx, p->pl, ws, ws_bytes);
     if (st == MSAO_OK) {
         DeviceGuard guard(ctx->device);
-        st = upload(ctx, p->pl, ws, (hipStream_t)stream);
+        st = upload(ctx, p->pl, n, ws, (hipStream_t)stream);
     }
     if (st != MSAO_OK) {
         delete p;

@@ -30,7 +30,7 @@ struct DevSeg {
     int32_t per_item;      // rows per item, or frames per item for temporal segments
     int32_t nchunk;        // 16-byte chunks per row
     int32_t A_s;           // Eq. 4 as an integer test: sparse iff active < A_s = ceil(tau_s*C)
-    uint32_t L_s, L_t;     // Q24 selection weights of the segment's modality
+    int32_t n_items, n_gather; // its scoring and gather work items
     float lam_s, lam_t;    // the same weights as floats (informativeness)
     int32_t k;             // fixed keep count, or -1 when MAS-guided
     int32_t cap;           // compaction capacity in rows
@@ -302,6 +302,26 @@ struct GatherArgs {
     uint8_t* out;
     int64_t out_bytes;
 };
+
+// The tables of one call, from pinned staging into the workspace
+// (msao_upload.hip). copy_bytes lead the tables and are staged; the arrays
+// that name the segment of each item are written from the segment records.
+struct UploadArgs {
+    const uint8_t* src;      // pinned staging slot (the segment records first)
+    uint8_t* dst;            // workspace
+    uint32_t copy_bytes;     // a multiple of 16
+    int32_t n;               // segments
+    int32_t copy_units, fill_parts;
+    int32_t any_hash;        // the call has hash tiles
+    int32_t *wi_seg, *gi_seg, *hb_seg, *frame_seg, *cl_seg, *hi_seg;
+    uint32_t* done;          // pinned, one word per block, set to ticket (NULL: not written)
+    uint32_t ticket;
+};
+constexpr int kUploadBlock = 256;
+constexpr int kUploadCopyBytes = 8192;   // staged bytes per unit
+constexpr int kUploadFill = 8192;        // entries per stripe of a run
+constexpr int kUploadMaxBlocks = 256;
+int launch_upload(const UploadArgs& a, int blocks, void* stream);
 
 // Draft-model confidence (msao_entropy.hip): one row of logits per workgroup.
 struct EntArgs {
