@@ -67,9 +67,11 @@ __global__ __launch_bounds__(kUploadBlock) void k_upload(UploadArgs a)
             fill_run(a.hi_seg, sg.hi_begin, (sg.n_tok + kHashBlockTokens - 1) / kHashBlockTokens, s, part, a.fill_parts);
     }
     if (a.done) {
-        __syncthreads();  // every thread's reads of the slot have returned: its stores took their values
+        // every thread's reads of the slot have returned (its stores took their
+        // values), and nothing that it wrote need be visible to the host
+        __syncthreads();
         if (threadIdx.x == 0)
-            __hip_atomic_store(a.done + blockIdx.x, a.ticket, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+            __hip_atomic_store(a.done + blockIdx.x, a.ticket, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
 }
 
