@@ -145,7 +145,10 @@ struct Plan {
     int n_wi = 0, n_gwi = 0;
     int max_n = 0;                 // largest selection (LDS key staging)
     int big_seg = kPostBigSegment; // selections this large take 1024-thread blocks
-    std::vector<SelUnit> sel_unit; // one selection block each: a segment, or a frame (per-frame scope)
+    std::vector<SelUnit> sel_unit; // selection blocks: a segment, or a frame (per-frame scope), or a part of one
+    int n_big_blk = 0;             // the first of them: chunks of large selections
+    size_t off_big = 0;            // what their passes hand on
+    bool lean = false;             // no room for that
     int n_hi = 0;                  // SimHash calls: hash tiles
     bool any_temporal = false, any_guided = false;
     bool any_copy = false;         // some segment is compacted by the scoring pass
@@ -198,8 +201,8 @@ size_t table_layout(Plan& pl, int n, int R, int64_t n_wi, int64_t n_gwi, int64_t
 
 // Workspace bound that does not depend on tuning: work items, gather items,
 // head blocks and hash tiles never outnumber tokens plus segments, and
-// selection blocks are bounded by segments, frames and one per
-// kSelPartTokens tokens, so one Partial and table entries per token, plus
+// selection blocks are bounded by segments, frames and one per 768 tokens
+// (far more than there are), so one Partial and table entries per token, plus
 // what a learned call adds (a PartialX per work item, one
 // projection and one head count per token, kMaxMlpHidden floats of the MLP's
 // prompt product per request, and the MAS of every (request, modality) that
@@ -210,10 +213,13 @@ size_t workspace_bytes_for(int n, int R, int64_t ntok, int64_t nframes)
     Plan pl;
     const int64_t items = ntok + n;
     // selection blocks: one per segment, or per frame of a clip, plus the
-    // extra blocks of selections of kSelSplitMin tokens or more
-    const int64_t sels = n + nframes + ntok / kSelPartTokens + 1;
+    // extra blocks of large selections
+    const int64_t sels = n + nframes + ntok / 768 + 1;
+    // the areas of large selections: a head and a partly filled chunk each beyond the bytes per token
+    const int64_t bigs = ntok / kSelRegTokens;
+    const size_t big = bigs > 0 ? big_area_bytes(ntok) + (size_t)bigs * big_area_bytes(1) : 0;
     const size_t tb = table_layout(pl, n, R, items, items, items, sels, items, items, items);
-    return align_up(tb, kWsAlign) + align_up(sizeof(Partial) * (size_t)std::max<int64_t>(items, 1), kWsAlign) +
+    return align_up(tb, kWsAlign) + align_up(big, kWsAlign) + align_up(sizeof(Partial) * (size_t)std::max<int64_t>(items, 1), kWsAlign) +
            align_up(sizeof(PartialX) * (size_t)std::max<int64_t>(items, 1), kWsAlign) +
            align_up(sizeof(float) * (size_t)std::max<int64_t>(ntok, 1), kWsAlign) +
            align_up(sizeof(uint32_t) * (size_t)std::max<int64_t>(items, 1), kWsAlign) +
@@ -270,12 +276,8 @@ void build_plan(const msao_ctx* ctx, const msao_segment* segs, int n, int R, con
             chains_total += segs[i].tokens_per_frame;
             pairs_total += (segs[i].tokens_per_frame + 1) / 2;
         }
-    // selections before any split: mid-size ones are split only while the
-    // launch would otherwise leave CUs without a selection block
-    int64_t whole_sels = 0;
-    for (int i = 0; i < n; ++i)
-        whole_sels += per_frame && segs[i].n_frames >= 2 && segs[i].tokens_per_frame > 0 ? segs[i].n_frames : 1;
-    const bool split_mid = whole_sels < kSelSplitMaxSelections;
+    std::vector<SelUnit> big_units;  // chunks of large selections, ahead of the others
+    size_t big_bytes = 0;
     for (int i = 0; i < n; ++i) {
         const msao_segment& s = segs[i];
         DevSeg& d = pl.seg[(size_t)i];
@@ -318,32 +320,36 @@ void build_plan(const msao_ctx* ctx, const msao_segment* segs, int n, int R, con
         const int kind = by_imp ? kKeyImp
                          : d.temporal && L_t > 0 ? (L_s > 0 ? kKeyFull : kKeyE) : (L_s > 0 ? kKeyZ : kKeyZero);
         auto push_selection = [&](int frame, int n_u, int kfix) {
-            const int parts = n_u >= pl.big_seg                 ? (n_u + kSelBigPartTokens - 1) / kSelBigPartTokens
-                              : n_u >= kSelSplitMin && split_mid ? (n_u + kSelPartTokens - 1) / kSelPartTokens
-                                                                 : 1;
-            for (int q = 0; q < parts; ++q) {
-                SelUnit u;
-                std::memset(&u, 0, sizeof u);
-                u.Ms = d.key_ms;
-                u.Mt = d.key_mt;
-                u.kmax = kind == kKeyZ ? (uint64_t)d.C
-                         : kind == kKeyE ? (uint64_t)d.E
-                         : kind == kKeyFull ? d.key_ms * (uint64_t)d.C + d.key_mt * (uint64_t)d.E
-                         : kind == kKeyImp ? 0xFFFFFFFFull : 0ull;
-                u.seg = i;
-                u.frame = frame;
+            SelUnit u;
+            std::memset(&u, 0, sizeof u);
+            u.Ms = d.key_ms;
+            u.Mt = d.key_mt;
+            u.kmax = kind == kKeyZ ? (uint64_t)d.C
+                     : kind == kKeyE ? (uint64_t)d.E
+                     : kind == kKeyFull ? d.key_ms * (uint64_t)d.C + d.key_mt * (uint64_t)d.E
+                     : kind == kKeyImp ? (uint64_t)kImpKeyMax : 0ull;
+            u.seg = i;
+            u.frame = frame;
+            u.nparts = 1;
+            u.off = d.tok_off + (frame >= 0 ? frame * s.tokens_per_frame : 0);
+            u.N = n_u;
+            u.kfix = kfix;
+            u.kind = kind;
+            u.E = (uint32_t)d.E;
+            u.units = frame >= 0 ? s.n_frames : 1;
+            u.seg_off = d.tok_off;
+            u.request = s.request;
+            u.modality = s.modality;
+            const bool big = n_u > kSelRegTokens && !pl.lean;
+            if (n_u > kSelRegTokens) u.nparts = (n_u + (big ? kBigChunk : kSelPartTokens) - 1) / (big ? kBigChunk : kSelPartTokens);
+            if (big) {
+                u.big = (uint32_t)(1 + big_bytes / 16);
+                big_bytes += big_area_bytes(n_u);
+            }
+            std::vector<SelUnit>& to = big ? big_units : pl.sel_unit;
+            for (int q = 0; q < u.nparts; ++q) {
                 u.part = q;
-                u.nparts = parts;
-                u.off = d.tok_off + (frame >= 0 ? frame * s.tokens_per_frame : 0);
-                u.N = n_u;
-                u.kfix = kfix;
-                u.kind = kind;
-                u.E = (uint32_t)d.E;
-                u.units = frame >= 0 ? s.n_frames : 1;
-                u.seg_off = d.tok_off;
-                u.request = s.request;
-                u.modality = s.modality;
-                pl.sel_unit.push_back(u);
+                to.push_back(u);
             }
         };
         if (framed) {
@@ -491,6 +497,8 @@ void build_plan(const msao_ctx* ctx, const msao_segment* segs, int n, int R, con
         d.cl_begin = pl.n_cl;
         pl.n_cl += (items + kClipWaves - 1) / kClipWaves;
     }
+    pl.n_big_blk = (int)big_units.size();
+    pl.sel_unit.insert(pl.sel_unit.begin(), big_units.begin(), big_units.end());
     pl.ntok = tok;
     pl.nframes = frame;
     pl.n_wi = wi;
@@ -530,6 +538,10 @@ void build_plan(const msao_ctx* ctx, const msao_segment* segs, int n, int R, con
     if (pl.simhash_d && !pl.clip_fused) {
         pl.off_hdsum = align_up(pl.total_bytes, kWsAlign);
         pl.total_bytes = pl.off_hdsum + sizeof(uint64_t) * (size_t)std::max(R * kNumMod, 1);
+    }
+    if (big_bytes > 0) {
+        pl.off_big = align_up(pl.total_bytes, kWsAlign);
+        pl.total_bytes = pl.off_big + big_bytes;
     }
     if (learned) {
         pl.off_partial_x = align_up(pl.total_bytes, kWsAlign);
@@ -696,6 +708,20 @@ Tables device_tables(const Plan& pl, void* ws, int n, int R, const msao_params* 
     }
     t.flags = p->flags;
     return t;
+}
+
+// Builds a plan within `limit` bytes of workspace and `table_limit` of
+// tables where one exists: without the areas of large selections if it does
+// not fit with them (the tables are then larger, one record per
+// kSelPartTokens tokens instead of kBigChunk).
+template <typename Build>
+void build_within(Plan& pl, size_t table_limit, size_t limit, Build&& build)
+{
+    build(pl);
+    if (pl.n_big_blk == 0 || (pl.table_bytes <= table_limit && pl.total_bytes <= limit)) return;
+    pl = Plan{};
+    pl.lean = true;
+    build(pl);
 }
 
 msao_status check_ws(msao_ctx* ctx, const Plan& pl, void* ws, size_t ws_bytes)
@@ -1015,6 +1041,7 @@ msao_status msao_mas_score(msao_ctx* ctx, const msao_segment* segs, int n, int R
     if (!ctx) return fail(&g_err, MSAO_ERR_INVALID_ARG, "ctx is NULL");
     MSAO_TRY(validate_impl(segs, n, R, params, &ctx->err));
     Plan pl;
+    pl.lean = true;  // no selection
     build_plan(ctx, segs, n, R, params, alpha, nullptr, pl);
     MSAO_TRY(check_ws(ctx, pl, ws, ws_bytes));
     const bool want_frames = frm && (frm->dframe || frm->sim || frm->gamma) && pl.nframes > 0;
@@ -1055,6 +1082,7 @@ msao_status msao_temporal_redundancy(msao_ctx* ctx, const msao_segment* segs, in
     if (!ctx) return fail(&g_err, MSAO_ERR_INVALID_ARG, "ctx is NULL");
     MSAO_TRY(validate_impl(segs, n, R, params, &ctx->err));
     Plan pl;
+    pl.lean = true;  // no selection
     build_plan(ctx, segs, n, R, params, nullptr, nullptr, pl);
     MSAO_TRY(check_ws(ctx, pl, ws, ws_bytes));
     const bool want_frames = frm && (frm->dframe || frm->sim || frm->gamma) && pl.nframes > 0;
@@ -1092,6 +1120,7 @@ msao_status msao_temporal_simhash(msao_ctx* ctx, const msao_segment* segs, int n
     MSAO_TRY(validate_impl(segs, n, R, params, &ctx->err));
     MSAO_TRY(check_hashes(ctx, segs, n, hashes));
     Plan pl;
+    pl.lean = true;  // no selection
     build_plan(ctx, segs, n, R, params, nullptr, nullptr, pl, false, nullptr, false, 0, hashes);
     MSAO_TRY(check_ws(ctx, pl, ws, ws_bytes));
     if (pl.ntok > 0 && (!sig || !d)) return fail(&ctx->err, MSAO_ERR_INVALID_ARG, "sig and d are required");
@@ -1121,7 +1150,7 @@ msao_status msao_select_tokens(msao_ctx* ctx, const msao_segment* segs, int n, i
     if (!ctx) return fail(&g_err, MSAO_ERR_INVALID_ARG, "ctx is NULL");
     MSAO_TRY(validate_impl(segs, n, R, params, &ctx->err));
     Plan pl;
-    build_plan(ctx, segs, n, R, params, nullptr, nullptr, pl);
+    build_within(pl, SIZE_MAX, ws_bytes, [&](Plan& q) { build_plan(ctx, segs, n, R, params, nullptr, nullptr, q); });
     MSAO_TRY(check_ws(ctx, pl, ws, ws_bytes));
     if (!sel || !sel->kept_idx || !sel->kept_count)
         return fail(&ctx->err, MSAO_ERR_INVALID_ARG, "selection needs kept_idx and kept_count");
@@ -1140,8 +1169,9 @@ msao_status msao_select_tokens(msao_ctx* ctx, const msao_segment* segs, int n, i
     pa.d = d;
     pa.mas_in = mas;
     pa.n_sel_blocks = (int)pl.sel_unit.size();
-    pa.keys_cap = std::min(pl.max_n, kMaxLdsKeys);
-    pa.big_block = pl.max_n >= pl.big_seg ? 1 : 0;
+    pa.n_big_blocks = pl.n_big_blk;
+    pa.big = pl.n_big_blk > 0 ? (uint8_t*)ws + pl.off_big : nullptr;
+    pa.big_block = pl.max_n >= pl.big_seg || pl.max_n > kSelSmallTokens ? 1 : 0;
     return launched(ctx, MSAO_KERNEL_POST, st, run_post, &pa);
 }
 
@@ -1155,6 +1185,7 @@ msao_status msao_compact(msao_ctx* ctx, const msao_segment* segs, int n, const i
     msao_params p = msao_default_params();
     MSAO_TRY(validate_impl(segs, n, R, &p, &ctx->err));
     Plan pl;
+    pl.lean = true;  // no selection
     build_plan(ctx, segs, n, R, &p, nullptr, out_byte_off, pl, false, nullptr, false, 0, nullptr, true);
     MSAO_TRY(check_ws(ctx, pl, ws, ws_bytes));
     if (pl.ntok > 0 && (!kept_idx || !kept_count))
@@ -1225,6 +1256,7 @@ msao_status msao_mas_score_learned(msao_ctx* ctx, const msao_segment* segs, int 
     MSAO_TRY(validate_impl(segs, n, R, params, &ctx->err));
     MSAO_TRY(check_learned(ctx, segs, n, heads, mlp));
     Plan pl;
+    pl.lean = true;  // no selection
     build_plan(ctx, segs, n, R, params, alpha, nullptr, pl, false, heads, true, mlp ? mlp->hidden : 0);
     MSAO_TRY(check_ws(ctx, pl, ws, ws_bytes));
     const bool want_frames = frm && (frm->dframe || frm->sim || frm->gamma) && pl.nframes > 0;
@@ -1416,8 +1448,10 @@ msao_status enqueue_run(msao_ctx* ctx, const Plan& pl, const Tables& t, const ms
     pa.n_req_blocks = want_req ? t.R : 0;
     pa.n_frame_blocks = want_frames ? (int)pl.nframes : 0;
     pa.n_sel_blocks = (int)pl.sel_unit.size();
-    pa.keys_cap = std::min(pl.max_n, kMaxLdsKeys);
-    pa.big_block = pl.max_n >= pl.big_seg ? 1 : 0;
+    pa.n_big_blocks = pl.n_big_blk;
+    // (the workspace begins off_seg before the segment records)
+    pa.big = pl.n_big_blk > 0 ? (uint8_t*)t.seg - pl.off_seg + pl.off_big : nullptr;
+    pa.big_block = pl.max_n >= pl.big_seg || pl.max_n > kSelSmallTokens ? 1 : 0;
     MSAO_TRY(launched(ctx, MSAO_KERNEL_POST, st, run_post, &pa));
     if (!out || t.n_gwi == 0) return MSAO_OK;
     GatherArgs ga;
@@ -1451,7 +1485,8 @@ msao_status msao_run(msao_ctx* ctx, const msao_segment* segs, int n, int R, cons
     if (!ctx) return fail(&g_err, MSAO_ERR_INVALID_ARG, "ctx is NULL");
     MSAO_TRY(validate_impl(segs, n, R, params, &ctx->err));
     Plan pl;
-    build_plan(ctx, segs, n, R, params, alpha, out_byte_off, pl, out != nullptr);
+    build_within(pl, SIZE_MAX, ws_bytes,
+                 [&](Plan& q) { build_plan(ctx, segs, n, R, params, alpha, out_byte_off, q, out != nullptr); });
     MSAO_TRY(check_ws(ctx, pl, ws, ws_bytes));
     const std::vector<msao_segment> sv(segs, segs + n);
     MSAO_TRY(check_run_outputs(ctx, pl, sv, tok, frm, req, sel, out, out_byte_off, out_bytes));
@@ -1472,7 +1507,8 @@ msao_status msao_run_noalloc(msao_ctx* ctx, const msao_segment* segs, int n, int
     if (!ctx) return fail(&g_err, MSAO_ERR_INVALID_ARG, "ctx is NULL");
     MSAO_TRY(validate_impl(segs, n, R, params, &ctx->err));
     Plan pl;
-    build_plan(ctx, segs, n, R, params, alpha, out_byte_off, pl, out != nullptr);
+    build_within(pl, kNoAllocTableBytes, kNoAllocScratchBytes,
+                 [&](Plan& q) { build_plan(ctx, segs, n, R, params, alpha, out_byte_off, q, out != nullptr); });
     char buf[200];
     if (pl.table_bytes > kNoAllocTableBytes || pl.total_bytes > kNoAllocScratchBytes) {
         std::snprintf(buf, sizeof buf,
@@ -1502,8 +1538,10 @@ msao_status msao_run_simhash(msao_ctx* ctx, const msao_segment* segs, int n, int
     MSAO_TRY(validate_impl(segs, n, R, params, &ctx->err));
     MSAO_TRY(check_hashes(ctx, segs, n, hashes));
     Plan pl;
-    build_plan(ctx, segs, n, R, params, alpha, out_byte_off, pl, out != nullptr, nullptr, false, 0, hashes, false,
-               true);
+    build_within(pl, SIZE_MAX, ws_bytes, [&](Plan& q) {
+        build_plan(ctx, segs, n, R, params, alpha, out_byte_off, q, out != nullptr, nullptr, false, 0, hashes, false,
+                   true);
+    });
     MSAO_TRY(check_ws(ctx, pl, ws, ws_bytes));
     const std::vector<msao_segment> sv(segs, segs + n);
     MSAO_TRY(check_run_outputs(ctx, pl, sv, tok, frm, req, sel, out, out_byte_off, out_bytes));
@@ -1526,8 +1564,10 @@ msao_status msao_run_learned(msao_ctx* ctx, const msao_segment* segs, int n, int
     MSAO_TRY(validate_impl(segs, n, R, params, &ctx->err));
     MSAO_TRY(check_learned(ctx, segs, n, heads, mlp));
     Plan pl;
-    build_plan(ctx, segs, n, R, params, alpha, out_byte_off, pl, out != nullptr, heads, true, mlp ? mlp->hidden : 0,
-               nullptr, false, false, true);
+    build_within(pl, SIZE_MAX, ws_bytes, [&](Plan& q) {
+        build_plan(ctx, segs, n, R, params, alpha, out_byte_off, q, out != nullptr, heads, true, mlp ? mlp->hidden : 0,
+                   nullptr, false, false, true);
+    });
     MSAO_TRY(check_ws(ctx, pl, ws, ws_bytes));
     const std::vector<msao_segment> sv(segs, segs + n);
     MSAO_TRY(check_run_outputs(ctx, pl, sv, tok, frm, req, sel, out, out_byte_off, out_bytes));
@@ -1594,8 +1634,9 @@ msao_status msao_run_learned(msao_ctx* ctx, const msao_segment* segs, int n, int
     ps.d = tok ? tok->d : nullptr;
     ps.mas_in = mas_ws;
     ps.n_sel_blocks = (int)pl.sel_unit.size();
-    ps.keys_cap = std::min(pl.max_n, kMaxLdsKeys);
-    ps.big_block = pl.max_n >= pl.big_seg ? 1 : 0;
+    ps.n_big_blocks = pl.n_big_blk;
+    ps.big = pl.n_big_blk > 0 ? (uint8_t*)ws + pl.off_big : nullptr;
+    ps.big_block = pl.max_n >= pl.big_seg || pl.max_n > kSelSmallTokens ? 1 : 0;
     MSAO_TRY(launched(ctx, MSAO_KERNEL_POST, st, run_post, &ps));
     if (!out || t.n_gwi == 0) return MSAO_OK;
     GatherArgs ga;
@@ -1621,7 +1662,8 @@ msao_status msao_plan_create(msao_ctx* ctx, const msao_segment* segs, int n, int
     p->segs.assign(segs, segs + n);
     if (out_byte_off) p->out_off.assign(out_byte_off, out_byte_off + n);
     p->params = *params;
-    build_plan(ctx, segs, n, R, params, alpha, out_byte_off, p->pl, out_byte_off != nullptr);
+    build_within(p->pl, SIZE_MAX, ws_bytes,
+                 [&](Plan& q) { build_plan(ctx, segs, n, R, params, alpha, out_byte_off, q, out_byte_off != nullptr); });
     msao_status st = check_ws(ctx, p->pl, ws, ws_bytes);
     if (st == MSAO_OK) {
         DeviceGuard guard(ctx->device);

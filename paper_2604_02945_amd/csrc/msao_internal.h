@@ -68,12 +68,12 @@ struct DevSeg {
 // when the other weight is 0 (the same order, a narrower range); or, in a
 // learned run, a segment with a head ranked by its Eq. 3 importance.
 enum : int { kKeyZero = 0, kKeyZ = 1, kKeyE = 2, kKeyFull = 3, kKeyImp = 4 };
+constexpr uint32_t kImpKeyMax = 0x3F800000u;  // the bits of 1.0f
 
 // One selection block: a whole segment (frame -1) or one frame of a clip
-// (per-frame scope), or one of the nparts blocks of a large selection. Every
-// block of a selection finds the same threshold from all of its keys; block
-// `part` then writes the keep flags and kept indices of its own slice. It
-// holds everything the block needs before its first load of z and d.
+// (per-frame scope), or one of the nparts blocks of a large selection, which
+// writes its slice of the tokens. It holds everything the block needs before
+// its first load of z and d.
 struct SelUnit {
     uint64_t Ms, Mt;        // key multipliers
     uint64_t kmax;          // largest key the selection can hold (z <= C, d <= E)
@@ -84,31 +84,32 @@ struct SelUnit {
     uint32_t E;             // bits d counts per token
     int32_t units;          // selections of the segment (T under the per-frame scope, else 1)
     int32_t seg_off;        // global token id of the segment's first token
-    int32_t request, modality, pad_;
+    int32_t request, modality;
+    uint32_t big;           // a selection of k_big_hist and k_big_cand: 1 + the offset of its area, in 16 bytes (else 0)
 };
-// Selections of the large-block launch (kPostBigSegment tokens or more,
-// 1,024 threads) are split into parts of kSelBigPartTokens tokens for their
-// counting and writing, one block each. Selections of kSelSplitMin tokens or
-// more are split into parts of about kSelPartTokens tokens when the launch
-// has fewer than kSelSplitMaxSelections selections: more parts would only
-// queue behind each other on the CUs, since each part stages all of the keys
-// again.
-#ifndef MSAO_SEL_PART_TOKENS
-#define MSAO_SEL_PART_TOKENS 768
-#endif
-constexpr int kSelPartTokens = MSAO_SEL_PART_TOKENS;
-#ifndef MSAO_SEL_BIG_PART_TOKENS
-#define MSAO_SEL_BIG_PART_TOKENS 2048
-#endif
-constexpr int kSelBigPartTokens = MSAO_SEL_BIG_PART_TOKENS;
-#ifndef MSAO_SEL_SPLIT_MIN
-#define MSAO_SEL_SPLIT_MIN 1024
-#endif
-constexpr int kSelSplitMin = MSAO_SEL_SPLIT_MIN;
-#ifndef MSAO_SEL_SPLIT_MAX_SELECTIONS
-#define MSAO_SEL_SPLIT_MAX_SELECTIONS 256
-#endif
-constexpr int kSelSplitMaxSelections = MSAO_SEL_SPLIT_MAX_SELECTIONS;
+// A selection of at most kSelRegTokens tokens is one block, whose threads hold
+// its keys in registers. A larger one is one block per chunk of kBigChunk
+// tokens after two passes of their own (k_big_hist, k_big_cand), with an area
+// of the workspace for what these hand on; where a caller's workspace has no
+// room for that, blocks of kSelPartTokens tokens each search all of the keys.
+constexpr int kSelRegTokens = 16384;
+constexpr int kSelSmallTokens = 8192; // most tokens of a selection in a block of kPostBlock threads
+constexpr int kSelPartTokens = 2048;
+constexpr int kBigChunk = 4096;
+constexpr int kBigBins = 2048;        // first radix digit
+struct BigHead {
+    int32_t k;                        // keep count
+    uint32_t digit, below, in_bin;    // first digit of the key of rank k - 1; keys of smaller digits; of that digit
+};
+struct BigPre {
+    uint32_t below, in_bin;           // the same of the chunks before this one
+};
+inline size_t big_area_bytes(int64_t n)
+{
+    const size_t chunks = (size_t)((n + kBigChunk - 1) / kBigChunk);
+    const size_t pre = (chunks * sizeof(BigPre) + 15) & ~(size_t)15;
+    return sizeof(BigHead) + pre + chunks * kBigBins * 2 + (((size_t)n * 4 + 15) & ~(size_t)15);
+}
 
 // Integer partial sums of one scoring work item (no atomics, no zeroing).
 struct Partial {
@@ -208,7 +209,8 @@ struct PostArgs {
     int32_t n_req_blocks; // then one per request
     int32_t n_frame_blocks;// then one per temporal frame
     int32_t temporal_only;// request role writes only the temporal term
-    int32_t keys_cap;     // selection keys staged in LDS per block (larger segments re-read z, d)
+    int32_t n_big_blocks; // of the selection blocks, the first: chunks of large selections
+    uint8_t* big;         // workspace area of the large selections
     int32_t big_block;    // 1: the launch's selections take 1024-thread blocks
     // learned calls: head counts and descriptors feed Eq. 4, Eq. 6 gives alpha
     int32_t learned;
@@ -380,6 +382,7 @@ constexpr int kPairTargetWaves = 1024;
 #define MSAO_POST_BLOCK 256
 #endif
 constexpr int kPostBlock = MSAO_POST_BLOCK;  // threads per post-scoring block
+constexpr int kPostBigBlock = 1024;          // the same for launches with a large selection
 #ifndef MSAO_POST_BIG_SEGMENT
 #define MSAO_POST_BIG_SEGMENT 4096
 #endif
@@ -405,7 +408,6 @@ constexpr int kGatherFewItems = MSAO_GATHER_FEW_ITEMS;
 #define MSAO_GATHER_ROWS 1
 #endif
 constexpr int kGatherRows = MSAO_GATHER_ROWS;  // kept rows per gather work item
-constexpr int kMaxLdsKeys = 16384; // 128 KiB of LDS per selection block
 
 // A plain streaming read (msao_calib.hip): wavefront w reads bytes
 // [w * chunk_bytes, (w + 1) * chunk_bytes) of data and writes the XOR of

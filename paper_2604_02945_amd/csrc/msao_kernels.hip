@@ -1052,6 +1052,9 @@ void k_pair(ScoreArgs a)
 constexpr int kRadixBits = 11;
 constexpr int kRadixBins = 1 << kRadixBits;
 
+constexpr int kMaxCand = 2048;   // radix candidates copied out of the keys
+constexpr int kSmallCand = 256;  // candidates ranked directly instead of by further digit passes
+
 // Shared state of a post-scoring block of NT threads.
 typedef unsigned int post_u32x4 __attribute__((ext_vector_type(4)));
 
@@ -1065,6 +1068,7 @@ struct PostShared {
     uint32_t wcnt[kWaves][4];
     unsigned long long lo, hi, red;
     uint64_t vsel;            // selection: key of the wanted rank among few candidates
+    uint64_t cand[kMaxCand];  // radix candidates copied out once few remain
     uint64_t nsp[kWaves], dsum[kWaves], ntok[kNumMod], qbits[kNumMod];
     uint32_t digit, below, in_bin, ncand;
     uint32_t ncopy;           // selection: candidates copied for a direct rank
@@ -1075,12 +1079,6 @@ struct PostShared {
     float fred4[kWaves][kNumMod];
     float alpha[kNumMod];
 };
-
-// Radix candidates copied out of the staged keys once few remain (LDS entries
-// after the keys).
-constexpr int kMaxCand = 2048;
-constexpr int kSmallCand = 256;  // candidates ranked directly instead of by further digit passes
-__device__ __host__ __forceinline__ int cand_cap_for(int keys_cap) { return keys_cap < kMaxCand ? keys_cap : kMaxCand; }
 
 // Block-wide sum of a 64-bit integer (exact, so the order does not matter).
 template <int NT>
@@ -1093,32 +1091,6 @@ __device__ __forceinline__ uint64_t block_sum_u64(uint64_t v, PostShared<NT>& sh
     if ((threadIdx.x & (kWave - 1)) == 0 && v) atomicAdd(&sh.red, (unsigned long long)v);
     __syncthreads();
     return (uint64_t)sh.red;
-}
-
-// Block-wide exclusive scan of 32-bit counts in thread order; *total gets the sum.
-template <int NT>
-__device__ __forceinline__ uint32_t block_exscan(uint32_t v, PostShared<NT>& sh, uint32_t* total)
-{
-    const int lane = threadIdx.x & (kWave - 1);
-    const int wid = threadIdx.x >> 6;
-    uint32_t x = v;
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-        const uint32_t y = __shfl_up(x, o);
-        if (lane >= o) x += y;
-    }
-    __syncthreads();
-    if (lane == kWave - 1) sh.scan[wid] = x;
-    __syncthreads();
-    uint32_t before = 0, tot = 0;
-#pragma unroll
-    for (int i = 0; i < (NT / kWave); ++i) {
-        const uint32_t t = sh.scan[i];
-        if (i < wid) before += t;
-        tot += t;
-    }
-    *total = tot;
-    return before + x - v;
 }
 
 struct RMAgg {
@@ -1247,7 +1219,7 @@ __device__ void request_terms(const Tables& t, int r, const RMAgg g[kNumMod], Ma
 }
 
 template <int NT>
-__device__ void role_request(const PostArgs& a, int r, PostShared<NT>& sh)
+__device__ __forceinline__ void role_request(const PostArgs& a, int r, PostShared<NT>& sh)
 {
     const Tables& t = a.t;
     RMAgg g[kNumMod];
@@ -1308,7 +1280,7 @@ __device__ __forceinline__ double wave_sum_f64(double v)
 // The descriptor: 1, rho, sum a / sum C, sum L1 / sum C, sqrt(sum L2 / sum C),
 // the temporal term (0 if none), 1 if it exists, ln(1 + Ntok) / 16.
 template <int NT>
-__device__ void role_request_learned(const PostArgs& a, int r, PostShared<NT>& sh)
+__device__ __forceinline__ void role_request_learned(const PostArgs& a, int r, PostShared<NT>& sh)
 {
     const Tables& t = a.t;
     constexpr int kParts = (NT / kWave) / kNumMod;
@@ -1478,7 +1450,7 @@ __device__ void role_request_learned(const PostArgs& a, int r, PostShared<NT>& s
 
 // Eq. 5 for one frame of a temporal segment: D_t = sum of d over its tokens.
 template <int NT>
-__device__ void role_frame(const PostArgs& a, int f, PostShared<NT>& sh)
+__device__ __forceinline__ void role_frame(const PostArgs& a, int f, PostShared<NT>& sh)
 {
     const Tables& t = a.t;
     const DevSeg& sg = t.seg[t.frame_seg[f]];
@@ -1496,28 +1468,142 @@ __device__ void role_frame(const PostArgs& a, int f, PostShared<NT>& sh)
     }
 }
 
-// Selection key Ms*z + Mt*(E - d), order-equivalent to L_s z / C + L_t (E -
-// d) / E (E = C for bit sampling, where Ms = L_s and Mt = L_t): when one
-// weight is 0 the other term alone orders the tokens, so it is used unscaled.
-// A learned importance as a key: larger importance first. The bits of a
-// positive float grow with its value, so their complement orders it
-// downwards; NaN and values not above 0 take the largest key (importance 0).
-__device__ __forceinline__ uint64_t imp_key(float m)
+// A learned importance as a key: larger importance first. It is a sigmoid, at
+// most 1, and the bits of a positive float grow with its value, so their
+// distance below those of 1 orders it downwards; NaN and values not above 0
+// take the largest key (importance 0). (30 bits instead of the complement's
+// 32: the first digit then tells 16 values per octave apart instead of 4, and
+// few enough keys share one to be ranked directly.)
+__device__ __forceinline__ uint32_t imp_key(float m) { return m > 0.0f ? kImpKeyMax - __float_as_uint(m) : kImpKeyMax; }
+
+// The keys of a selection's tokens, key(i) = Ms z + Mt (E - d) of token i,
+// order-equivalent to L_s z / C + L_t (E - d) / E (E = C for bit sampling,
+// where Ms = L_s and Mt = L_t); when one weight is 0 the other term alone
+// orders the tokens, so it is used unscaled; or the learned importance.
+// `first`: the z values or importances; d: NULL where not used.
+struct TokenKeys {
+    const uint32_t* first;
+    const uint32_t* d;
+    int kind;
+    uint64_t Ms, Mt;
+    uint32_t E;
+    __device__ __forceinline__ uint64_t of(uint32_t z, uint32_t dd) const
+    {
+        if (kind == kKeyImp) return (uint64_t)imp_key(__uint_as_float(z));
+        return Ms * (uint64_t)z + (d ? Mt * (uint64_t)(E - dd) : 0ull);
+    }
+    __device__ __forceinline__ uint64_t at(int i) const { return of(first ? first[i] : 0u, d ? d[i] : 0u); }
+};
+
+__device__ __forceinline__ TokenKeys token_keys(const PostArgs& a, const SelUnit& su)
 {
-    return m > 0.0f ? (uint64_t)(~__float_as_uint(m)) : 0xFFFFFFFFull;
+    const bool full = su.kind == kKeyFull;
+    TokenKeys t;
+    t.first = su.kind == kKeyZ || full ? a.z + su.off
+              : su.kind == kKeyImp ? (const uint32_t*)(a.t.proj + su.off) : nullptr;
+    t.d = su.kind == kKeyE || full ? a.d + su.off : nullptr;
+    t.kind = su.kind;
+    t.Ms = full ? su.Ms : 1ull;
+    t.Mt = full ? su.Mt : 1ull;
+    t.E = su.E;
+    return t;
 }
 
-__device__ __forceinline__ uint64_t sel_key(const uint32_t* __restrict__ z, const uint32_t* __restrict__ d,
-                                            const float* __restrict__ imp, int g, int kind, uint64_t Ms, uint64_t Mt,
-                                            uint32_t E)
-{
-    switch (kind) {
-    case kKeyZ: return (uint64_t)z[g];
-    case kKeyE: return (uint64_t)(E - d[g]);
-    case kKeyFull: return Ms * (uint64_t)z[g] + Mt * (uint64_t)(E - d[g]);
-    case kKeyImp: return imp_key(imp[g]);
-    default: return 0ull;
+// A selection's keys as the radix search reads them: each() calls f(key, in)
+// the same number of times in every lane, in = the lane has a key there.
+// All of them, from memory at every pass:
+template <int NT>
+struct MemKeys {
+    TokenKeys t;
+    const int32_t* idx;  // the tokens (NULL: tokens 0 .. N - 1)
+    int N;
+    template <typename F>
+    __device__ __forceinline__ void each(F&& f) const
+    {
+        const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x >> 6;
+        constexpr int U = 4;
+        for (int base = wid * kWave; base < N; base += U * NT) {
+            uint64_t x[U];
+            // clamped indices: every load is issued before any is used
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int i = min(base + u * NT + lane, N - 1);
+                x[u] = t.at(idx ? idx[i] : i);
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) f(x[u], base + u * NT + lane < N);
+        }
     }
+};
+
+// Read once and kept in registers: lane t of the block has those of tokens
+// base + lo .. base + hi - 1, K of them at most, and every thread's tokens
+// follow the thread's before it. A selection is a chain of passes over its
+// keys in one block, bound by the latency of its steps and the instructions
+// of its passes: four consecutive tokens per load, no copy of the keys in LDS
+// and one scan of the counts instead of a counting and a placing pass. The
+// launch of 8 clips of 8,192 tokens (1,024 threads, one block each) takes
+// 10.6 us where four blocks a clip with the keys staged in LDS took 11.6;
+// 96 selections of at most 1,500 (256 threads) 6.3 against 6.4.
+template <int NT, int K>
+struct RegKeys {
+    uint64_t key[K];
+    int base, lo, hi;
+    template <typename F>
+    __device__ __forceinline__ void each(F&& f) const
+    {
+#pragma unroll
+        for (int j = 0; j < K; ++j) f(key[j], j >= lo && j < hi);
+    }
+};
+
+typedef unsigned int sel_u32x4 __attribute__((ext_vector_type(4), aligned(4)));
+
+// This thread's K of the tokens [t0, t0 + n) (keys of t), thread 0 first. A
+// last thread with fewer than K left reads the K before the end and uses
+// only its own; a range of fewer than K tokens is read one by one.
+template <int NT, int K>
+__device__ __forceinline__ void load_keys(RegKeys<NT, K>& r, const TokenKeys& t, int t0, int n)
+{
+    uint32_t zz[K], dd[K];
+#pragma unroll
+    for (int j = 0; j < K; ++j) zz[j] = dd[j] = 0u;
+    const int i0 = (int)threadIdx.x * K;
+    if (n >= K) {
+        const int b = min(i0, n - K);
+        r.base = t0 + b;
+        r.lo = min(K, i0 - b);
+        r.hi = K;
+        if (i0 < n) {
+            if (t.first) {
+#pragma unroll
+                for (int q = 0; q < K / 4; ++q) {
+                    const sel_u32x4 v = *reinterpret_cast<const sel_u32x4*>(t.first + r.base + 4 * q);
+                    zz[4 * q] = v.x; zz[4 * q + 1] = v.y; zz[4 * q + 2] = v.z; zz[4 * q + 3] = v.w;
+                }
+            }
+            if (t.d) {
+#pragma unroll
+                for (int q = 0; q < K / 4; ++q) {
+                    const sel_u32x4 v = *reinterpret_cast<const sel_u32x4*>(t.d + r.base + 4 * q);
+                    dd[4 * q] = v.x; dd[4 * q + 1] = v.y; dd[4 * q + 2] = v.z; dd[4 * q + 3] = v.w;
+                }
+            }
+        }
+    } else {
+        r.base = t0;
+        r.lo = 0;
+        r.hi = threadIdx.x == 0 ? n : 0;
+#pragma unroll
+        for (int j = 0; j < K; ++j) {
+            if (j < r.hi) {
+                if (t.first) zz[j] = t.first[t0 + j];
+                if (t.d) dd[j] = t.d[t0 + j];
+            }
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < K; ++j) r.key[j] = t.of(zz[j], dd[j]);
 }
 
 template <int CTRL, int ROW_MASK>
@@ -1540,13 +1626,11 @@ __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t x)
     return x;
 }
 
-// Block-wide exclusive scan of 32-bit counts in thread order (DPP wavefront
-// scans, then the wavefront totals through LDS); *total gets the sum.
+// Block-wide exclusive prefix sum in thread order; *total gets the sum.
 template <int NT>
-__device__ __forceinline__ uint32_t block_exscan_dpp(uint32_t v, PostShared<NT>& sh, uint32_t* total)
+__device__ __forceinline__ uint32_t block_exscan(uint32_t v, PostShared<NT>& sh, uint32_t* total)
 {
-    const int lane = threadIdx.x & (kWave - 1);
-    const int wid = threadIdx.x >> 6;
+    const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x >> 6;
     const uint32_t inc = wave_incl_scan(v);
     __syncthreads();
     if (lane == kWave - 1) sh.scan[wid] = inc;
@@ -1562,70 +1646,21 @@ __device__ __forceinline__ uint32_t block_exscan_dpp(uint32_t v, PostShared<NT>&
     return before + inc - v;
 }
 
-// Keys of tokens [0, N) of a selection staged into LDS (when in_lds), each
-// also counted in the histogram of the first radix digit, key >> shift (the
-// keys lie in [0, kmax], so the first digit needs no range of its own), which
-// this zeroes first (every thread of the block calls it). U
-// tokens per thread are loaded before any is used, so that the global loads
-// of one thread overlap; indices past N are clamped (and their values
-// dropped) so that no load sits behind a branch.
-template <int NT, int KIND>
-__device__ __forceinline__ void stage_keys(const uint32_t* __restrict__ z, const uint32_t* __restrict__ d,
-                                           const float* __restrict__ imp, int N, uint64_t Ms, uint64_t Mt, uint32_t E,
-                                           bool in_lds, uint64_t* keys, uint32_t* hist, int shift, bool count)
+template <int NT>
+__device__ __forceinline__ void clear_hist(PostShared<NT>& sh)
 {
-    constexpr int U = 8;
-    if (N <= U * NT) {
-        // one batch per thread: its loads are issued first and the histogram
-        // is zeroed while they are in flight (one barrier before the counting)
-        uint32_t zz[U], ee[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int g = min((int)threadIdx.x + u * NT, N - 1);
-            zz[u] = KIND == kKeyZ || KIND == kKeyFull ? z[g] : 0u;
-            ee[u] = KIND == kKeyE || KIND == kKeyFull ? E - d[g] : 0u;
-            if constexpr (KIND == kKeyImp) zz[u] = (uint32_t)imp_key(imp[g]);
-        }
-        for (int b = threadIdx.x; b < kRadixBins; b += NT) hist[b] = 0u;
-        __syncthreads();
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int i = (int)threadIdx.x + u * NT;
-            if (i < N) {
-                uint64_t key = 0ull;
-                if constexpr (KIND == kKeyZ || KIND == kKeyImp) key = zz[u];
-                else if constexpr (KIND == kKeyE) key = ee[u];
-                else if constexpr (KIND == kKeyFull) key = Ms * (uint64_t)zz[u] + Mt * (uint64_t)ee[u];
-                if (in_lds) keys[i] = key;
-                if (count) atomicAdd(&hist[(uint32_t)(key >> shift)], 1u);
-            }
-        }
-        return;
-    }
-    for (int b = threadIdx.x; b < kRadixBins; b += NT) hist[b] = 0u;
-    __syncthreads();
-    for (int i0 = threadIdx.x; i0 < N; i0 += U * NT) {
-        uint32_t zz[U], ee[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int g = min(i0 + u * NT, N - 1);
-            zz[u] = KIND == kKeyZ || KIND == kKeyFull ? z[g] : 0u;
-            ee[u] = KIND == kKeyE || KIND == kKeyFull ? E - d[g] : 0u;
-            if constexpr (KIND == kKeyImp) zz[u] = (uint32_t)imp_key(imp[g]);
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int i = i0 + u * NT;
-            if (i < N) {
-                uint64_t key = 0ull;
-                if constexpr (KIND == kKeyZ || KIND == kKeyImp) key = zz[u];
-                else if constexpr (KIND == kKeyE) key = ee[u];
-                else if constexpr (KIND == kKeyFull) key = Ms * (uint64_t)zz[u] + Mt * (uint64_t)ee[u];
-                if (in_lds) keys[i] = key;
-                if (count) atomicAdd(&hist[(uint32_t)(key >> shift)], 1u);
-            }
-        }
-    }
+    for (int b = threadIdx.x; b < kRadixBins; b += NT) sh.hist[b] = 0u;
+}
+
+// Appends the lanes' keys with `match` to the candidates.
+__device__ __forceinline__ void push_cand(uint64_t* cand, uint32_t* count, uint64_t x, bool match)
+{
+    const uint64_t m = __ballot(match);
+    if (!m) return;
+    uint32_t at = 0;
+    if ((threadIdx.x & (kWave - 1)) == 0) at = atomicAdd(count, (uint32_t)__popcll(m));
+    at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
+    if (match) cand[at + lanes_below(m)] = x;
 }
 
 // MAS-guided keep count (Eq. 11 floor): k = min(N, ceil((1 - MAS) * N)) in double.
@@ -1638,74 +1673,34 @@ __device__ __forceinline__ int guided_keep_count(float mas, int N)
     return (int)kk;
 }
 
-// Where the selection keys are read from: staged in LDS, or recomputed from
-// z and d for selections larger than the LDS staging area.
-struct KeySrc {
-    const uint64_t* keys;
-    const uint32_t* z;
-    const uint32_t* d;
-    const float* imp;
-    int kind;
-    uint64_t Ms, Mt;
-    uint32_t E;
-    template <bool IN_LDS>
-    __device__ __forceinline__ uint64_t at(int i) const
-    {
-        if constexpr (IN_LDS) return keys[i];
-        else return sel_key(z, d, imp, i, kind, Ms, Mt, E);
-    }
-};
-
-// Rank k-1 of the N keys of a selection (range [lo, hi]) by MSD radix
-// select; then this block's slice [s0, s1) of keep flags (at off + i) and
-// ascending kept indices (iadd + i, written from ioff). IN_LDS: every key is
-// staged in LDS.
-template <int NT, bool IN_LDS>
-__device__ void select_and_compact(const PostArgs& a, PostShared<NT>& sh, const KeySrc& src, uint64_t* cand,
-                                   int cand_cap, int N, int k, int off, int ioff, int iadd, uint64_t lo, uint64_t hi,
-                                   int s0, int s1, bool first_hist_ready)
+// Key of rank `rank` among the N keys of src by MSD radix select, and the
+// number of keys below it. All keys have `prefix` above their lowest `bits`
+// bits (bits = the width of the largest key and prefix = 0 for all keys of a
+// selection). cleared: the histogram is already zero (and the block past a
+// barrier since).
+template <int NT, typename Src>
+__device__ __forceinline__ uint64_t radix_rank(PostShared<NT>& sh, const Src& src, int N, uint32_t rank, int bits,
+                                               uint64_t prefix, bool cleared, uint32_t* below_out)
 {
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wid = tid >> 6;
     constexpr int kW = NT / kWave;
-    auto key_at = [&](int i) -> uint64_t { return src.at<IN_LDS>(i); };
-    // radix select of the key of rank k-1 among key - lo, most significant digit
-    // first. Once the candidate range holds at most cand_cap keys, the next
-    // pass also copies them to cand[] and later passes read only those.
+    // Once the candidate range holds at most kMaxCand keys, the next pass
+    // also copies them to cand[] and later passes read only those.
     int ncand = -1;                // -1: passes read every key
     uint32_t in_range = (uint32_t)N;
-    uint64_t prefix = 0;
     uint32_t below = 0;            // keys below the current candidate range
-    uint32_t rank = (uint32_t)k - 1;
-    int bits = hi > lo ? 64 - __clzll((long long)(hi - lo)) : 0;
-    bool built = first_hist_ready;  // the first digit's histogram was counted while staging
-    constexpr int U = 4;
+    bool all = true;               // no digit found yet: every key is in the range
     while (bits > 0) {
         const int db = bits < kRadixBits ? bits : kRadixBits;
         const int shift = bits - db;
-        const uint64_t mask = (1ull << db) - 1ull;
+        const uint32_t mask = (1u << db) - 1u;
         // copy out the candidates once they are few (and fewer than half the keys)
-        const bool collect = ncand < 0 && in_range <= (uint32_t)cand_cap && 2 * in_range < (uint32_t)N;
-        const bool first = in_range == (uint32_t)N && below == 0u && prefix == 0ull;
-        if (!built && collect && in_range <= (uint32_t)kSmallCand) {
+        const bool collect = ncand < 0 && in_range <= (uint32_t)kMaxCand && 2 * in_range < (uint32_t)N;
+        if (!all && collect && in_range <= (uint32_t)kSmallCand) {
             // so few keys are left that a copy of them and a direct rank among
             // them cost less than the remaining digit passes (their count was
             // reset by the digit scan before its barrier)
-            for (int base = wid * kWave; base < N; base += U * NT) {
-                uint64_t x[U];
-#pragma unroll
-                for (int u = 0; u < U; ++u) x[u] = key_at(min(base + u * NT + lane, N - 1)) - lo;
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const bool match = base + u * NT + lane < N && (x[u] >> bits) == prefix;
-                    const uint64_t m = __ballot(match);
-                    if (m) {
-                        uint32_t at = 0;
-                        if (lane == 0) at = atomicAdd(&sh.ncopy, (uint32_t)__popcll(m));
-                        at = (uint32_t)__shfl((int)at, 0);
-                        if (match) cand[at + lanes_below(m)] = x[u];
-                    }
-                }
-            }
+            src.each([&](uint64_t x, bool in) { push_cand(sh.cand, &sh.ncopy, x, in && (x >> bits) == prefix); });
             __syncthreads();
             const int m = (int)sh.ncopy;
             // candidate c = (w % cw) * 64 + lane is counted against the j-range
@@ -1716,11 +1711,11 @@ __device__ void select_and_compact(const PostArgs& a, PostShared<NT>& sh, const 
             const int per = (m + nparts - 1) / nparts, j0 = min(m, part * per), j1 = min(m, j0 + per);
             uint32_t lt = 0, le = 0;
             if (part < nparts && c < m) {
-                const uint64_t v = cand[c];
+                const uint64_t v = sh.cand[c];
                 for (int j = j0; j < j1; j += 4) {
                     uint64_t x[4];
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) x[u] = cand[min(j + u, j1 - 1)];
+                    for (int u = 0; u < 4; ++u) x[u] = sh.cand[min(j + u, j1 - 1)];
 #pragma unroll
                     for (int u = 0; u < 4; ++u) {
                         const bool in = j + u < j1;
@@ -1744,56 +1739,39 @@ __device__ void select_and_compact(const PostArgs& a, PostShared<NT>& sh, const 
                 }
                 // every candidate equal to the one of this rank writes the same values
                 if (lt_all <= rank && rank < le_all) {
-                    sh.vsel = cand[cc];
+                    sh.vsel = sh.cand[cc];
                     sh.below = lt_all;
                 }
             }
             __syncthreads();
             prefix = sh.vsel;
             below += sh.below;
-            bits = 0;
             break;
         }
-        if (!built) {
+        if (!cleared) {
             // (every thread has read the previous digit's fields, which the
             // zeroing does not touch; the histogram was last read before the
             // previous barrier)
-            for (int b = tid; b < kRadixBins; b += NT) sh.hist[b] = 0u;
+            clear_hist(sh);
             if (tid == 0) sh.ncand = 0u;
             __syncthreads();
-            // wave-uniform loop over the keys (or candidates), U x 64 per step
-            const int nscan = ncand >= 0 ? ncand : N;
-            for (int base = wid * kWave; base < nscan; base += U * NT) {
-                uint64_t x[U];
-                // clamped indices: every load is issued before any is used
-                if (ncand >= 0) {
-#pragma unroll
-                    for (int u = 0; u < U; ++u) x[u] = cand[min(base + u * NT + lane, nscan - 1)];
-                } else {
-#pragma unroll
-                    for (int u = 0; u < U; ++u) x[u] = key_at(min(base + u * NT + lane, N - 1)) - lo;
-                }
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    // the first pass (no digit fixed yet) takes every key
-                    const bool match = base + u * NT + lane < nscan &&
-                                       (first || (bits >= 64 ? 0ull : (x[u] >> bits)) == prefix);
-                    if (match) atomicAdd(&sh.hist[(x[u] >> shift) & mask], 1u);
-                    if (collect) {
-                        const uint64_t m = __ballot(match);
-                        if (m) {
-                            uint32_t at = 0;
-                            if (lane == 0) at = atomicAdd(&sh.ncand, (uint32_t)__popcll(m));
-                            at = (uint32_t)__shfl((int)at, 0);
-                            if (match) cand[at + lanes_below(m)] = x[u];
-                        }
-                    }
-                }
-            }
-            __syncthreads();
-            if (collect) ncand = (int)sh.ncand;
         }
-        built = false;
+        cleared = false;
+        if (ncand >= 0) {
+            for (int base = wid * kWave; base < ncand; base += NT) {
+                const uint64_t x = sh.cand[min(base + lane, ncand - 1)];
+                if (base + lane < ncand && (x >> bits) == prefix) atomicAdd(&sh.hist[(uint32_t)(x >> shift) & mask], 1u);
+            }
+        } else {
+            src.each([&](uint64_t x, bool in) {
+                const bool match = in && (all || (x >> bits) == prefix);
+                if (match) atomicAdd(&sh.hist[(uint32_t)(x >> shift) & mask], 1u);
+                if (collect) push_cand(sh.cand, &sh.ncand, x, match);
+            });
+        }
+        __syncthreads();
+        if (collect) ncand = (int)sh.ncand;
+        all = false;
         // the digit of rank `rank`, found by wavefront 0 alone (lane l sums
         // bins [32 l, 32 l + 32) with eight 16-byte reads, taken in a rotated
         // order so that the lanes served together hit different banks; a
@@ -1834,9 +1812,151 @@ __device__ void select_and_compact(const PostArgs& a, PostShared<NT>& sh, const 
         prefix = (prefix << db) | dg;
         bits = shift;
     }
-    const uint64_t vstar = lo + prefix;        // key of rank k-1
-    const uint32_t ties = (uint32_t)k - below; // keys equal to vstar that are kept, lowest index first
+    *below_out = below;
+    return prefix;
+}
 
+// Where a selection's outputs go: keep flags at off + i, kept indices iadd +
+// i from ioff.
+struct SelDest {
+    int off, ioff, iadd;
+};
+
+// Keep flags and kept indices of the keys in registers, given the largest
+// kept key: `ties` keys equal to it are kept, lowest index first; lt0 and eq0
+// keys below and equal to it belong to tokens before the block's.
+template <int NT, int K>
+__device__ __forceinline__ void place_regs(const PostArgs& a, PostShared<NT>& sh, const RegKeys<NT, K>& r, uint64_t vstar,
+                                           uint32_t ties, uint32_t lt0, uint32_t eq0, const SelDest& o)
+{
+    uint32_t ltm = 0, eqm = 0;  // this thread's tokens below and equal to vstar
+#pragma unroll
+    for (int j = 0; j < K; ++j) {
+        const bool in = j >= r.lo && j < r.hi;
+        ltm |= in && r.key[j] < vstar ? 1u << j : 0u;
+        eqm |= in && r.key[j] == vstar ? 1u << j : 0u;
+    }
+    // both counts in one scan: at most 16,384 tokens a block
+    static_assert(NT * K <= 32768, "two 16-bit counts per word");
+    uint32_t tot;
+    const uint32_t ex = block_exscan<NT>((uint32_t)__builtin_popcount(ltm) | ((uint32_t)__builtin_popcount(eqm) << 16), sh, &tot);
+    const uint32_t lt = lt0 + (ex & 0xFFFFu), eq = eq0 + (ex >> 16);
+    // of the equal ones, those whose number among all equal ones is below ties
+    uint32_t left = ties > eq ? ties - eq : 0u;
+    if (left < (uint32_t)__builtin_popcount(eqm)) {
+        uint32_t m = 0;
+#pragma unroll
+        for (int j = 0; j < K; ++j)
+            if ((eqm >> j & 1u) && left) {
+                m |= 1u << j;
+                --left;
+            }
+        eqm = m;
+    }
+    const uint32_t kp = ltm | eqm;
+    int at = o.ioff + (int)(lt + min(eq, ties));
+#pragma unroll
+    for (int j = 0; j < K; ++j)
+        if (kp >> j & 1u) a.sel.kept_idx[at++] = o.iadd + r.base + j;
+    if (a.sel.keep) {
+        uint8_t* f = a.sel.keep + o.off + r.base;
+        if (r.lo == 0 && r.hi == K && ((uintptr_t)f & 3) == 0) {
+#pragma unroll
+            for (int q = 0; q < K / 4; ++q)  // four bits to four bytes
+                reinterpret_cast<uint32_t*>(f)[q] = ((kp >> (4 * q) & 0xFu) * 0x00204081u) & 0x01010101u;
+        } else {
+#pragma unroll
+            for (int j = 0; j < K; ++j)
+                if (j >= r.lo && j < r.hi) f[j] = (uint8_t)(kp >> j & 1u);
+        }
+    }
+}
+
+// Keep count of a selection: fixed, or from the caller's MAS, or from the
+// MAS of its request and modality.
+template <int NT>
+__device__ __forceinline__ int keep_of(const PostArgs& a, const SelUnit& su, PostShared<NT>& sh)
+{
+    if (su.kfix >= 0) return su.kfix;
+    float mas;
+    if (a.mas_in) {
+        mas = a.mas_in[su.request * kNumMod + su.modality];
+    } else {
+        RMAgg g[kNumMod];
+        rm_aggregate_all(a.t, su.request, sh, g);
+        MasTerms o[kNumMod];
+        bool pres[kNumMod];
+        request_terms(a.t, su.request, g, o, pres);
+        mas = 0.0f;
+#pragma unroll
+        for (int m = 0; m < kNumMod; ++m)
+            if (m == su.modality) mas = (float)o[m].mas;
+    }
+    return guided_keep_count(mas, su.N);
+}
+
+__device__ __forceinline__ int key_bits(const SelUnit& su)
+{
+    return su.kmax > 0 ? 64 - __clzll((long long)su.kmax) : 0;
+}
+
+// What every block of a selection does besides: kept_count, its share of the
+// -1 tail after the kept indices, and a selection that keeps none or all of
+// its tokens [s0, s1) (then the block is done: true).
+template <int NT>
+__device__ __forceinline__ bool select_edges(const PostArgs& a, const SelUnit& su, int k, int s0, int s1, SelDest& o)
+{
+    const int N = su.N, f = su.frame, tid = threadIdx.x;
+    const bool framed = f >= 0;
+    if (tid == 0 && f <= 0 && su.part == 0) a.sel.kept_count[su.seg] = k * su.units;
+    o.off = su.off;                                 // keys and keep flags
+    o.ioff = su.seg_off + (framed ? f * k : 0);     // kept indices
+    o.iadd = framed ? f * N : 0;                    // local index of the selection's first token
+    const int fill = su.seg_off + su.units * k + (framed ? f : 0) * (N - k);
+    const int tail = N - k, share = (tail + su.nparts - 1) / su.nparts;
+    const int t0 = min(tail, su.part * share), t1 = min(tail, t0 + share);
+    for (int i = t0 + tid; i < t1; i += NT) a.sel.kept_idx[fill + i] = -1;
+    if (k > 0 && k < N) return false;
+    for (int i = s0 + tid; i < s1; i += NT) {
+        if (a.sel.keep) a.sel.keep[o.off + i] = k > 0 ? 1 : 0;
+        if (k > 0) a.sel.kept_idx[o.ioff + i] = o.iadd + i;
+    }
+    return true;
+}
+
+// A selection of at most NT * K tokens in one block, its keys in registers.
+template <int NT, int K>
+__device__ __forceinline__ void select_in_regs(const PostArgs& a, const SelUnit& su, PostShared<NT>& sh)
+{
+    RegKeys<NT, K> r;
+    load_keys<NT, K>(r, token_keys(a, su), 0, su.N);
+    clear_hist(sh);  // while the keys are in flight
+    const int k = keep_of(a, su, sh);
+    SelDest o;
+    if (select_edges<NT>(a, su, k, 0, su.N, o)) return;
+    __syncthreads();
+    uint32_t below;
+    const uint64_t vstar = radix_rank<NT>(sh, r, su.N, (uint32_t)k - 1, key_bits(su), 0ull, true, &below);
+    place_regs<NT, K>(a, sh, r, vstar, (uint32_t)k - below, 0u, 0u, o);
+}
+
+// A selection of more tokens whose tables leave no room for the two passes of
+// k_big_hist and k_big_cand: nparts blocks, each finding the same key from
+// all of the keys, re-read at every pass, and writing its slice of tokens.
+template <int NT>
+__device__ __forceinline__ void select_from_memory(const PostArgs& a, const SelUnit& su, PostShared<NT>& sh)
+{
+    const int N = su.N, tid = threadIdx.x, lane = tid & (kWave - 1), wid = tid >> 6;
+    constexpr int kW = NT / kWave, U = 4;
+    const int slice = ((N + su.nparts - 1) / su.nparts + kWave - 1) / kWave * kWave;
+    const int s0 = min(N, su.part * slice), s1 = min(N, s0 + slice);
+    const int k = keep_of(a, su, sh);
+    SelDest o;
+    if (select_edges<NT>(a, su, k, s0, s1, o)) return;
+    const TokenKeys tk = token_keys(a, su);
+    uint32_t below;
+    const uint64_t vstar = radix_rank<NT>(sh, MemKeys<NT>{tk, nullptr, N}, N, (uint32_t)k - 1, key_bits(su), 0ull, false, &below);
+    const uint32_t ties = (uint32_t)k - below;
     // counts of keys below and equal to vstar before this block's slice (the
     // prefix [0, s0) split evenly over the wavefronts), and in each
     // wavefront's contiguous range of the slice
@@ -1844,29 +1964,22 @@ __device__ void select_and_compact(const PostArgs& a, PostShared<NT>& sh, const 
     const int per = ((((s1 - s0) + kW - 1) / kW) + kWave - 1) / kWave * kWave;
     const int p0 = min(s0, wid * pw), p1 = min(s0, p0 + pw);
     const int b0 = min(s1, s0 + wid * per), b1 = min(s1, b0 + per);
+    auto count = [&](int i0, int i1, uint32_t& nlt, uint32_t& neq) __attribute__((always_inline)) {
+        for (int base = i0; base < i1; base += U * kWave) {
+            uint64_t kv[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) kv[u] = tk.at(min(base + u * kWave + lane, i1 - 1));
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const bool v = base + u * kWave + lane < i1;
+                nlt += (uint32_t)__popcll(__ballot(v && kv[u] < vstar));
+                neq += (uint32_t)__popcll(__ballot(v && kv[u] == vstar));
+            }
+        }
+    };
     uint32_t plt = 0, peq = 0, nlt = 0, neq = 0;
-    for (int base = p0; base < p1; base += U * kWave) {
-        uint64_t kv[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) kv[u] = key_at(min(base + u * kWave + lane, p1 - 1));
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const bool v = base + u * kWave + lane < p1;
-            plt += (uint32_t)__popcll(__ballot(v && kv[u] < vstar));
-            peq += (uint32_t)__popcll(__ballot(v && kv[u] == vstar));
-        }
-    }
-    for (int base = b0; base < b1; base += U * kWave) {
-        uint64_t kv[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) kv[u] = key_at(min(base + u * kWave + lane, b1 - 1));
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const bool v = base + u * kWave + lane < b1;
-            nlt += (uint32_t)__popcll(__ballot(v && kv[u] < vstar));
-            neq += (uint32_t)__popcll(__ballot(v && kv[u] == vstar));
-        }
-    }
+    count(p0, p1, plt, peq);
+    count(b0, b1, nlt, neq);
     if (lane == 0) {
         sh.wcnt[wid][0] = nlt;
         sh.wcnt[wid][1] = neq;
@@ -1885,7 +1998,7 @@ __device__ void select_and_compact(const PostArgs& a, PostShared<NT>& sh, const 
     for (int base = b0; base < b1; base += U * kWave) {
         uint64_t kv[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) kv[u] = key_at(min(base + u * kWave + lane, b1 - 1));
+        for (int u = 0; u < U; ++u) kv[u] = tk.at(min(base + u * kWave + lane, b1 - 1));
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int i = base + u * kWave + lane;
@@ -1895,98 +2008,222 @@ __device__ void select_and_compact(const PostArgs& a, PostShared<NT>& sh, const 
             const uint64_t me = __ballot(ise);
             const bool kp = isl || (ise && eq_run + lanes_below(me) < ties);
             const uint64_t mk = __ballot(kp);
-            if (v && a.sel.keep) a.sel.keep[off + i] = kp ? 1 : 0;
-            if (kp) a.sel.kept_idx[ioff + (int)(kept_run + lanes_below(mk))] = iadd + i;
+            if (v && a.sel.keep) a.sel.keep[o.off + i] = kp ? 1 : 0;
+            if (kp) a.sel.kept_idx[o.ioff + (int)(kept_run + lanes_below(mk))] = o.iadd + i;
             eq_run += (uint32_t)__popcll(me);
             kept_run += (uint32_t)__popcll(mk);
         }
     }
 }
 
-// Top-k of one selection: the k smallest (key, index) pairs of a segment, or
-// of one frame of a clip under the per-frame scope, kept indices ascending
-// (Sec. 4.1.1 pruning, k from the Eq. 11 floor or a fixed ratio). Keys are
-// staged in LDS when they fit (keys_cap entries), then an MSD radix select
-// finds the key of rank k-1 and each wavefront compacts a contiguous index
-// range of the block's slice with ballot/mbcnt. A selection split over
-// nparts blocks has every block find the same key from all of the keys and
-// write its own slice (and its share of the -1 tail). Frame f of a clip
-// keeping k_f per frame writes its kept indices at positions f k_f.. of the
-// segment's range and its share, P - k_f entries, of the -1 tail after the
-// T k_f kept ones.
-template <int NT>
-__device__ void role_select(const PostArgs& a, int unit, PostShared<NT>& sh, uint64_t* keys, int keys_cap)
+// ---- selections of more than kSelRegTokens tokens
+//
+// Three launches, one block per chunk of kBigChunk tokens in each, so that
+// every pass over the keys is spread over the chip and each key is read three
+// times in all: k_big_hist counts the first radix digit of every chunk;
+// k_big_cand sums the chunks' counts, which gives the digit of the wanted
+// rank and how many smaller keys each chunk follows, and lists the tokens of
+// that digit (the candidates, in token order); the selection block of
+// k_post ranks the candidates and places its chunk. Bound by latency (three
+// launches of 14 blocks for 55,296 tokens): 4.7, 12.4 (6 of them the
+// MAS-guided count's aggregation) and 11.0 us, where blocks that each passed
+// over all keys and wrote a slice of 2,048 tokens took 50 us.
+
+struct BigRefs {
+    BigHead* head;
+    BigPre* pre;      // [chunks]
+    uint32_t* hist;   // [chunks][kRadixBins / 2], two 16-bit counts a word
+    int32_t* cand;    // [N]
+};
+
+__device__ __forceinline__ BigRefs big_refs(const PostArgs& a, const SelUnit& su)
 {
-    const Tables& t = a.t;
-    const SelUnit su = t.sel_unit[unit];
-    const int N = su.N, f = su.frame, tid = threadIdx.x, lane = tid & (kWave - 1);
-    const bool framed = f >= 0;
-    int k = su.kfix;
-    if (k < 0) {
-        float mas;
-        if (a.mas_in) {
-            mas = a.mas_in[su.request * kNumMod + su.modality];
-        } else {
-            RMAgg g[kNumMod];
-            rm_aggregate_all(t, su.request, sh, g);
-            MasTerms o[kNumMod];
-            bool pres[kNumMod];
-            request_terms(t, su.request, g, o, pres);
-            mas = 0.0f;
+    uint8_t* p = a.big + (uint64_t)(su.big - 1u) * 16u;
+    BigRefs r;
+    r.head = (BigHead*)p;
+    r.pre = (BigPre*)(p + sizeof(BigHead));
+    const uint32_t pre_bytes = ((uint32_t)su.nparts * (uint32_t)sizeof(BigPre) + 15u) & ~15u;
+    r.hist = (uint32_t*)(p + sizeof(BigHead) + pre_bytes);
+    r.cand = (int32_t*)(r.hist + (int64_t)su.nparts * (kRadixBins / 2));
+    return r;
+}
+
+__device__ __forceinline__ int first_shift(int bits) { return bits > kRadixBits ? bits - kRadixBits : 0; }
+
+constexpr int kBigBlock = kPostBigBlock;
+constexpr int kBigK = kBigChunk / kBigBlock;
+
+__global__ __launch_bounds__(kBigBlock) void k_big_hist(PostArgs a)
+{
+    __shared__ PostShared<kBigBlock> sh;
+    const SelUnit su = a.t.sel_unit[blockIdx.x];
+    const int t0 = su.part * kBigChunk, n = min(kBigChunk, su.N - t0);
+    RegKeys<kBigBlock, kBigK> r;
+    load_keys<kBigBlock, kBigK>(r, token_keys(a, su), t0, n);
+    clear_hist(sh);
+    __syncthreads();
+    const int shift = first_shift(key_bits(su));
+    r.each([&](uint64_t x, bool in) {
+        if (in) atomicAdd(&sh.hist[(uint32_t)(x >> shift) & (kRadixBins - 1)], 1u);
+    });
+    __syncthreads();
+    uint32_t* out = big_refs(a, su).hist + (int64_t)su.part * (kRadixBins / 2);
+    for (int w = threadIdx.x; w < kRadixBins / 2; w += kBigBlock) out[w] = sh.hist[2 * w] | (sh.hist[2 * w + 1] << 16);
+}
+
+__global__ __launch_bounds__(kBigBlock) void k_big_cand(PostArgs a)
+{
+    __shared__ PostShared<kBigBlock> sh;
+    static_assert(kRadixBins == 2 * kBigBlock, "a thread sums two bins");
+    const SelUnit su = a.t.sel_unit[blockIdx.x];
+    const BigRefs b = big_refs(a, su);
+    const int tid = threadIdx.x, own = su.part;
+    const int t0 = own * kBigChunk, n = min(kBigChunk, su.N - t0);
+    RegKeys<kBigBlock, kBigK> r;
+    load_keys<kBigBlock, kBigK>(r, token_keys(a, su), t0, n);
+    // bins 2 tid and 2 tid + 1 over all chunks, and over those before this one
+    uint32_t tot0 = 0, tot1 = 0, bef0 = 0, bef1 = 0;
+    constexpr int U = 8;
+    for (int c0 = 0; c0 < su.nparts; c0 += U) {
+        uint32_t v[U];
 #pragma unroll
-            for (int m = 0; m < kNumMod; ++m)
-                if (m == su.modality) mas = (float)o[m].mas;
+        for (int u = 0; u < U; ++u) v[u] = b.hist[(int64_t)min(c0 + u, su.nparts - 1) * (kRadixBins / 2) + tid];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (c0 + u >= su.nparts) continue;
+            tot0 += v[u] & 0xFFFFu;
+            tot1 += v[u] >> 16;
+            if (c0 + u < own) {
+                bef0 += v[u] & 0xFFFFu;
+                bef1 += v[u] >> 16;
+            }
         }
-        k = guided_keep_count(mas, N);
     }
-    if (tid == 0 && f <= 0 && su.part == 0) a.sel.kept_count[su.seg] = k * su.units;
-    const int off = su.off;                                     // keys and keep flags
-    const int ioff = su.seg_off + (framed ? f * k : 0);         // kept indices
-    const int iadd = framed ? f * N : 0;                        // local index of the selection's first token
-    const int fill = su.seg_off + su.units * k + (framed ? f : 0) * (N - k);
-    {
-        const int tail = N - k, share = (tail + su.nparts - 1) / su.nparts;
-        const int t0 = min(tail, su.part * share), t1 = min(tail, t0 + share);
-        for (int i = t0 + tid; i < t1; i += NT) a.sel.kept_idx[fill + i] = -1;
-    }
-    if (N == 0) return;
-    // this block's slice of the tokens (whole wavefront chunks)
-    const int slice = ((N + su.nparts - 1) / su.nparts + kWave - 1) / kWave * kWave;
-    const int s0 = min(N, su.part * slice), s1 = min(N, s0 + slice);
-    if (k == 0 || k == N) {
-        for (int i = s0 + tid; i < s1; i += NT) {
-            if (a.sel.keep) a.sel.keep[off + i] = k == N ? 1 : 0;
-            if (k == N) a.sel.kept_idx[ioff + i] = iadd + i;
-        }
+    const int k = keep_of(a, su, sh);
+    if (k == 0 || k == su.N) {
+        if (own == 0 && tid == 0) *b.head = BigHead{k, 0u, 0u, 0u};
         return;
     }
-    const int kind = su.kind;
-    const uint64_t Ms = su.Ms, Mt = su.Mt;
-    const uint32_t E = su.E;
-    const uint32_t* z = a.z + off;
-    const uint32_t* d = a.d ? a.d + off : nullptr;
-    const float* imp = kind == kKeyImp ? t.proj + off : nullptr;  // learned run: Eq. 3 importance
-    const bool in_lds = N <= keys_cap;
-
-    // keys (staged in LDS) in [0, kmax], counted in the first digit's histogram
-    const uint64_t lo = 0ull, hi = su.kmax;
-    const int bits = hi > 0 ? 64 - __clzll((long long)hi) : 0;
-    const int shift0 = bits > kRadixBits ? bits - kRadixBits : 0;
-    switch (kind) {
-    case kKeyZ: stage_keys<NT, kKeyZ>(z, d, imp, N, Ms, Mt, E, in_lds, keys, sh.hist, shift0, bits > 0); break;
-    case kKeyE: stage_keys<NT, kKeyE>(z, d, imp, N, Ms, Mt, E, in_lds, keys, sh.hist, shift0, bits > 0); break;
-    case kKeyFull: stage_keys<NT, kKeyFull>(z, d, imp, N, Ms, Mt, E, in_lds, keys, sh.hist, shift0, bits > 0); break;
-    case kKeyImp: stage_keys<NT, kKeyImp>(z, d, imp, N, Ms, Mt, E, in_lds, keys, sh.hist, shift0, bits > 0); break;
-    default: stage_keys<NT, kKeyZero>(z, d, imp, N, Ms, Mt, E, in_lds, keys, sh.hist, shift0, false); break;
+    const uint32_t rank = (uint32_t)k - 1;
+    uint32_t total;
+    const uint32_t ex = block_exscan<kBigBlock>(tot0 + tot1, sh, &total);
+    if (rank >= ex && rank < ex + tot0 + tot1) {
+        const bool second = rank >= ex + tot0;
+        sh.digit = (uint32_t)(2 * tid + (second ? 1 : 0));
+        sh.below = ex + (second ? tot0 : 0u);
+        sh.in_bin = second ? tot1 : tot0;
+        sh.ncand = second ? bef1 : bef0;  // candidates of the chunks before
     }
+    if (tid == 0) sh.red = 0ull;
     __syncthreads();
+    const uint32_t digit = sh.digit;
+    const uint32_t lt = ((uint32_t)(2 * tid) < digit ? bef0 : 0u) + ((uint32_t)(2 * tid + 1) < digit ? bef1 : 0u);
+    const uint64_t ltw = wave_sum_u64(lt);
+    if ((tid & (kWave - 1)) == 0 && ltw) atomicAdd(&sh.red, (unsigned long long)ltw);
+    const uint32_t inb = sh.ncand;
+    const int shift = first_shift(key_bits(su));
+    uint32_t m = 0;
+#pragma unroll
+    for (int j = 0; j < kBigK; ++j)
+        if (j >= r.lo && j < r.hi && (uint32_t)(r.key[j] >> shift) == digit) m |= 1u << j;
+    uint32_t at = inb + block_exscan<kBigBlock>((uint32_t)__builtin_popcount(m), sh, &total);
+    if (shift > 0) {  // otherwise the digit is the key
+#pragma unroll
+        for (int j = 0; j < kBigK; ++j)
+            if (m >> j & 1u) b.cand[at++] = r.base + j;
+    }
+    if (tid == 0) {
+        b.pre[own] = BigPre{(uint32_t)sh.red, inb};
+        if (own == 0) *b.head = BigHead{k, digit, sh.below, sh.in_bin};
+    }
+}
 
-    const KeySrc src{keys, z, d, imp, kind, Ms, Mt, E};
-    uint64_t* cand = keys + keys_cap;
-    if (in_lds)
-        select_and_compact<NT, true>(a, sh, src, cand, cand_cap_for(keys_cap), N, k, off, ioff, iadd, lo, hi, s0, s1, true);
-    else
-        select_and_compact<NT, false>(a, sh, src, cand, cand_cap_for(keys_cap), N, k, off, ioff, iadd, lo, hi, s0, s1, true);
+template <int NT>
+__device__ __forceinline__ void select_big(const PostArgs& a, const SelUnit& su, PostShared<NT>& sh)
+{
+    constexpr int K = kBigChunk / NT;
+    const BigRefs b = big_refs(a, su);
+    const BigHead head = *b.head;
+    const BigPre pre = b.pre[su.part];
+    const TokenKeys tk = token_keys(a, su);
+    const int t0 = su.part * kBigChunk, n = min(kBigChunk, su.N - t0);
+    RegKeys<NT, K> r;
+    load_keys<NT, K>(r, tk, t0, n);
+    SelDest o;
+    if (select_edges<NT>(a, su, head.k, t0, t0 + n, o)) return;
+    const int shift = first_shift(key_bits(su));
+    uint64_t vstar = head.digit;
+    uint32_t below = head.below, lt0 = pre.below, eq0 = pre.in_bin;
+    if (shift > 0) {
+        const int m = (int)head.in_bin;
+        const uint32_t rank = (uint32_t)head.k - 1 - head.below;
+        uint32_t cb;
+        uint64_t nlt = 0, neq = 0;
+        if (m <= NT * 4) {
+            // four candidates a thread, in registers
+            RegKeys<NT, 4> c;
+            c.base = (int)threadIdx.x * 4;
+            c.lo = 0;
+            c.hi = max(0, min(4, m - c.base));
+#pragma unroll
+            for (int j = 0; j < 4; ++j) c.key[j] = tk.at(b.cand[min(c.base + j, m - 1)]);
+            vstar = radix_rank<NT>(sh, c, m, rank, shift, head.digit, false, &cb);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const bool in = j < c.hi && c.base + j < (int)pre.in_bin;
+                nlt += in && c.key[j] < vstar ? 1u : 0u;
+                neq += in && c.key[j] == vstar ? 1u : 0u;
+            }
+        } else {
+            const MemKeys<NT> src{tk, b.cand, m};
+            vstar = radix_rank<NT>(sh, src, m, rank, shift, head.digit, false, &cb);
+            const MemKeys<NT> first{tk, b.cand, (int)pre.in_bin};
+            first.each([&](uint64_t x, bool in) {
+                nlt += in && x < vstar ? 1u : 0u;
+                neq += in && x == vstar ? 1u : 0u;
+            });
+        }
+        const uint64_t s = block_sum_u64<NT>(nlt | (neq << 32), sh);
+        below += cb;
+        lt0 += (uint32_t)s;
+        eq0 = (uint32_t)(s >> 32);
+    }
+    place_regs<NT, K>(a, sh, r, vstar, (uint32_t)head.k - below, lt0, eq0, o);
+}
+
+// Top-k of one selection: the k smallest (key, index) pairs of a segment, or
+// of one frame of a clip under the per-frame scope, kept indices ascending
+// (Sec. 4.1.1 pruning, k from the Eq. 11 floor or a fixed ratio). An MSD
+// radix select finds the key of rank k-1 and a block scan of the smaller and
+// equal keys before each token gives its place. Frame f of a clip keeping k_f
+// per frame writes its kept indices at positions f k_f.. of the segment's
+// range and its share, P - k_f entries, of the -1 tail after the T k_f kept
+// ones. The number of keys a thread holds follows the selection's size.
+template <int NT>
+__device__ __forceinline__ void role_select(const PostArgs& a, int unit, PostShared<NT>& sh)
+{
+    const SelUnit su = a.t.sel_unit[unit];
+    if constexpr (NT == kPostBigBlock) {
+        // (selections of more than kSelSmallTokens tokens always take these blocks)
+        if (su.big) {
+            select_big<NT>(a, su, sh);
+            return;
+        }
+        if (su.nparts > 1) {
+            select_from_memory<NT>(a, su, sh);
+            return;
+        }
+    } else {
+        static_assert(kSelSmallTokens <= 32 * NT, "32 keys a thread hold the largest selection of the small blocks");
+        if (su.N > 16 * NT) {
+            select_in_regs<NT, 32>(a, su, sh);
+            return;
+        }
+    }
+    static_assert(kSelRegTokens <= 16 * kPostBigBlock, "16 keys a thread hold the largest selection in registers");
+    if (su.N <= 4 * NT) select_in_regs<NT, 4>(a, su, sh);
+    else if (su.N <= 8 * NT) select_in_regs<NT, 8>(a, su, sh);
+    else select_in_regs<NT, 16>(a, su, sh);
 }
 
 // LR: a learned call (request role with head counts, descriptors and the
@@ -1996,12 +2233,11 @@ template <int NT, bool LR>
 __global__ __launch_bounds__(NT) void k_post(PostArgs a)
 {
     __shared__ PostShared<NT> sh;
-    extern __shared__ uint64_t keys[];
     // selection blocks first: they are the longest and are dispatched first
     int b = blockIdx.x;
     if constexpr (!LR) {
         if (b < a.n_sel_blocks) {
-            role_select(a, b, sh, keys, a.keys_cap);
+            role_select(a, b, sh);
             return;
         }
         b -= a.n_sel_blocks;
@@ -2228,32 +2464,32 @@ int launch_score(const ScoreArgs& a, void* stream, void* ev0, void* ev1)
     return launch(k_score<false>, dim3(grid), dim3(kScoreBlock), 0, stream, b, npair > 0 ? nullptr : ev0, ev1);
 }
 
-template <int NT, bool LR>
-static int launch_post_nt(const PostArgs& a, int blocks, size_t lds, void* stream, void* ev0, void* ev1)
-{
-    if (lds > 65536) {
-        const hipError_t e =
-            hipFuncSetAttribute((const void*)k_post<NT, LR>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess) return (int)e;
-    }
-    return launch(k_post<NT, LR>, dim3((unsigned)blocks), dim3(NT), lds, stream, a, ev0, ev1);
-}
-
 // Launches with a selection of kPostBigSegment tokens or more (the host's
 // big_block; the threshold can be changed at context creation) take
-// 1024-thread blocks (their loops are latency-bound with one wavefront per
-// SIMD); otherwise kPostBlock threads, which leave room for the scoring of
-// other batches in flight.
+// 1024-thread blocks (a selection is a chain of passes over its keys in one
+// block); otherwise kPostBlock threads, which leave room for the scoring of
+// other batches in flight. The blocks of selections of more than
+// kSelRegTokens tokens lead the list, and their two passes go first; ev0 is
+// recorded at the first launch's start, ev1 at the last one's end.
 int launch_post(const PostArgs& a, void* stream, void* ev0, void* ev1)
 {
     const int blocks = a.n_req_blocks + a.n_frame_blocks + a.n_sel_blocks;
     if (blocks <= 0) return kNoLaunch;
-    const size_t lds = (size_t)(a.keys_cap + cand_cap_for(a.keys_cap)) * sizeof(uint64_t);
     if (a.learned && (!a.t.partial_x || !a.t.head_count || (a.use_mlp && !a.mlp_u))) return (int)hipErrorInvalidValue;
-    if (a.learned) return launch_post_nt<kPostBlock, true>(a, a.n_req_blocks + a.n_frame_blocks, lds, stream, ev0, ev1);
+    if (a.learned)
+        return launch(k_post<kPostBlock, true>, dim3((unsigned)(a.n_req_blocks + a.n_frame_blocks)), dim3(kPostBlock), 0,
+                      stream, a, ev0, ev1);
+    if (a.n_big_blocks > 0) {
+        if (!a.big || a.n_big_blocks > a.n_sel_blocks) return (int)hipErrorInvalidValue;
+        const dim3 grid((unsigned)a.n_big_blocks), block(kBigBlock);
+        int rc = launch(k_big_hist, grid, block, 0, stream, a, ev0, nullptr);
+        if (rc == 0) rc = launch(k_big_cand, grid, block, 0, stream, a, nullptr, nullptr);
+        if (rc != 0) return rc;
+        ev0 = nullptr;
+    }
     if (a.n_sel_blocks > 0 && a.big_block)
-        return launch_post_nt<1024, false>(a, blocks, lds, stream, ev0, ev1);
-    return launch_post_nt<kPostBlock, false>(a, blocks, lds, stream, ev0, ev1);
+        return launch(k_post<kPostBigBlock, false>, dim3((unsigned)blocks), dim3(kPostBigBlock), 0, stream, a, ev0, ev1);
+    return launch(k_post<kPostBlock, false>, dim3((unsigned)blocks), dim3(kPostBlock), 0, stream, a, ev0, ev1);
 }
 
 int launch_head(const HeadArgs& a, void* stream, void* ev0, void* ev1)
