@@ -167,7 +167,7 @@ typedef struct {
  * chain pass over clips, 0 = automatic), MSAO_XCD_ORDER (scoring block order:
  * -1 automatic, 0 dispatch order, 1 one range per XCD), MSAO_CLIP_FUSE (1:
  * the run with SimHash scores and hashes its clips in one pass), MSAO_PAIR
- * (1: bf16 clips with rows of 512 to 2,048 bytes take the paired pass) and
+ * (1: clips with rows of at most 4 KiB take the paired pass) and
  * MSAO_POST_BIG_SEGMENT (selections of at least this many tokens take
  * 1,024-thread blocks, 4096: lower latency per batch; a larger value favours
  * throughput with several batches in flight). */

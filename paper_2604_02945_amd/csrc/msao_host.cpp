@@ -47,7 +47,7 @@ struct msao_ctx {
     int chain_frames = 0;       // frames per temporal work item; 0 = automatic
     int xcd_order = -1;         // scoring block order: -1 automatic, 0 dispatch order, 1 one range per XCD
     int clip_fuse = 1;          // the SimHash run scores and hashes its clips in one pass (k_clip)
-    int pair_path = 1;          // bf16 clips with rows of at most 2 KiB are scored by k_pair
+    int pair_path = 1;          // clips with rows of at most 4 KiB are scored by k_pair
     int post_big_segment = kPostBigSegment;  // selections this large take 1024-thread blocks
 };
 
@@ -168,6 +168,7 @@ struct Plan {
     int n_cl = 0;                  // k_clip blocks
     int n_wi_score = 0;            // k_score's work items [0, n_wi_score); the fused clips' follow
     int n_wi_pair = 0;             // k_pair's work items [0, n_wi_pair), whole blocks
+    bool pair_wide = false;        // some of them are fp32 or have rows over kPairNarrowRowBytes
     size_t copy_bytes = 0, table_bytes = 0, off_partial = 0, total_bytes = 0;
 };
 
@@ -392,8 +393,8 @@ void build_plan(const msao_ctx* ctx, const msao_segment* segs, int n, int R, con
         // scoring work items, one wavefront each
         int items = 0;
         const int64_t row_bytes = (int64_t)s.hidden * es;
-        if (d.temporal && !d.fused && !learned && !d.copy_in_score && (!ctx || ctx->pair_path) && s.dtype == MSAO_BF16 &&
-            row_bytes <= kPairMaxRowBytes && row_bytes % 512 == 0 && s.tokens_per_frame >= 2 &&
+        if (d.temporal && !d.fused && !learned && !d.copy_in_score && (!ctx || ctx->pair_path) &&
+            row_bytes <= kPairMaxRowBytes && s.tokens_per_frame >= 2 &&
             d.stride_bytes + row_bytes <= (1 << 30)) {
             // k_pair: one wavefront per pair of positions and range of at most
             // kPairMaxFrames frames (a range after the first reads the frame
@@ -424,6 +425,7 @@ void build_plan(const msao_ctx* ctx, const msao_segment* segs, int n, int R, con
                 ((int64_t)((s.tokens_per_frame + 1) / 2) * tblk + kPairWaves - 1) / kPairWaves * kPairWaves;
             if (pitems <= N) {
                 d.pair = 1;
+                if (s.dtype != MSAO_BF16 || row_bytes > kPairNarrowRowBytes) pl.pair_wide = true;
                 d.tblk = tblk;
                 d.per_item = F;
                 items = (int)pitems;
@@ -1059,6 +1061,7 @@ msao_status msao_mas_score(msao_ctx* ctx, const msao_segment* segs, int n, int R
     sa.tok = token_out(tok);
     sa.out = nullptr;
     sa.mode = kModeScore;
+    sa.pair_wide = pl.pair_wide ? 1 : 0;
     sa.xcd_order = xcd_order_for(ctx, false);
     MSAO_TRY(launched(ctx, MSAO_KERNEL_SCORE, st, run_score, &sa));
     PostArgs pa;
@@ -1098,6 +1101,7 @@ msao_status msao_temporal_redundancy(msao_ctx* ctx, const msao_segment* segs, in
     sa.tok.d = d;
     sa.tok.res = res;
     sa.mode = kModeTemporal;
+    sa.pair_wide = pl.pair_wide ? 1 : 0;
     sa.xcd_order = xcd_order_for(ctx, false);
     MSAO_TRY(launched(ctx, MSAO_KERNEL_SCORE, st, run_score, &sa));
     PostArgs pa;
@@ -1274,6 +1278,7 @@ msao_status msao_mas_score_learned(msao_ctx* ctx, const msao_segment* segs, int 
     sa.t = device_tables(pl, ws, n, R, params);
     sa.tok = token_out(tok);
     sa.mode = kModeScore;
+    sa.pair_wide = pl.pair_wide ? 1 : 0;
     sa.xcd_order = xcd_order_for(ctx, false);
     sa.learned = 1;
     sa.importance = importance;
@@ -1405,6 +1410,7 @@ msao_status enqueue_run(msao_ctx* ctx, const Plan& pl, const Tables& t, const ms
     if (pl.clip_fused) sa.tok.sig = sig;
     sa.out = (uint8_t*)out;
     sa.mode = kModeScore;
+    sa.pair_wide = pl.pair_wide ? 1 : 0;
     sa.xcd_order = xcd_order_for(ctx, out && pl.any_copy);
     MSAO_TRY(launched(ctx, MSAO_KERNEL_SCORE, st, run_score, &sa));
     if (pl.clip_fused) {
@@ -1583,6 +1589,7 @@ msao_status msao_run_learned(msao_ctx* ctx, const msao_segment* segs, int n, int
     sa.tok = token_out(tok);
     sa.out = (uint8_t*)out;
     sa.mode = kModeScore;
+    sa.pair_wide = pl.pair_wide ? 1 : 0;
     sa.xcd_order = xcd_order_for(ctx, out && pl.any_copy);
     sa.learned = 1;
     sa.importance = importance;

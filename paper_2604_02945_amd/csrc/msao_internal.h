@@ -58,7 +58,7 @@ struct DevSeg {
     int32_t fused;
     uint64_t key_ms, key_mt;
     int32_t cl_begin, ntiles;
-    // a bf16 clip with rows of at most 2 KiB scored by k_pair: a wavefront
+    // a clip with rows of at most 4 KiB scored by k_pair: a wavefront
     // takes two adjacent positions over a range of per_item frames (tblk
     // ranges cover the clip; its items are rounded up to whole blocks)
     int32_t pair, tblk;
@@ -230,6 +230,7 @@ struct ScoreArgs {
     int32_t xcd_order;    // 1: each XCD takes one contiguous range of workgroups
     int32_t learned;      // learned call: projections, importance of head-less tokens, PartialX
     float* importance;    // [Ntot] (learned calls; NULL: not written)
+    int32_t pair_wide;    // k_pair's instance for fp32 rows and rows over kPairNarrowRowBytes
     int32_t wi_first;     // k_score's first work item (set by the launcher: the pair items precede it)
 };
 
@@ -365,18 +366,26 @@ constexpr int kScoreBlock = 256;   // 4 wavefronts, one work item each
 // k_pair block: wavefronts on consecutive pairs of positions over the same
 // frames (four: a clip batch of 1,024 wavefronts puts one on every SIMD)
 constexpr int kPairWaves = MSAO_PAIR_WAVES;
-// k_pair's register budget: a ring of four frames needs about 146 VGPRs
+// k_pair's register budget: a ring of four frames of four units needs about
+// 146 VGPRs, of eight units about 250
 constexpr int kPairWavesPerEU = 2;
+// work items of other segments that run in k_pair's launch: a launch of their
+// own for the text of one request costs 4-6 us; more than about one per SIMD
+// would be slower at k_pair's occupancy than in k_score
+constexpr int kPairRestItems = 1024;
 constexpr int kPairRing = 4;                  // frames in registers per k_pair wavefront (even)
-constexpr int kPairMaxRowBytes = 2048;        // rows k_pair takes: four 512-byte units per half-wavefront
+constexpr int kPairMaxRowBytes = 4096;        // rows k_pair takes: eight 512-byte units per half-wavefront
+constexpr int kPairNarrowRowBytes = 2048;     // bf16 rows its narrow instance takes: four units
 #ifndef MSAO_PAIR_MAX_FRAMES
 #define MSAO_PAIR_MAX_FRAMES 32
 #endif
 constexpr int kPairMaxFrames = MSAO_PAIR_MAX_FRAMES;  // frames per k_pair wavefront (the token buffer holds 2 per frame)
 static_assert(kPairMaxFrames >= 1 && kPairMaxFrames <= 32, "k_pair parks two tokens per frame in 64 lanes");
 // k_pair range length: halved from kPairMaxFrames down to kPairMinFrames to
-// spread a batch's frames evenly over kPairTargetWaves SIMDs
-constexpr int kPairMinFrames = 8;
+// spread a batch's frames evenly over kPairTargetWaves SIMDs (down to two
+// frames rather than eight: one clip of 32 x 256 x 1,024 bf16 8.0 -> 6.5 us, 8
+// frames of 64 x 768 7.5 -> 5, larger batches keep longer ranges either way)
+constexpr int kPairMinFrames = 2;
 constexpr int kPairTargetWaves = 1024;
 #ifndef MSAO_POST_BLOCK
 #define MSAO_POST_BLOCK 256

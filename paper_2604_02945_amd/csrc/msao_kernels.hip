@@ -3,7 +3,7 @@
 //
 // The path is HBM-bandwidth bound: every input byte is read once with 128-bit
 // loads, no step is a dense contraction (no MFMA). Three launch slots:
-//   scoring  k_pair for bf16 clips with rows of 512-2,048 bytes (a wavefront
+//   scoring  k_pair for clips with rows of at most 4 KiB (a wavefront
 //            streams two neighbouring patch positions through a range of
 //            frames, a ring of frames in registers), k_score for the rest
 //            (one wavefront per work item: a run of rows, or one patch's run
@@ -720,18 +720,10 @@ __device__ __forceinline__ int score_block(const ScoreArgs& a)
     return x * per + min(x, rem) + (b >> 3);
 }
 
-// LR: a learned call (Eq. 3 head projections, density importance of tokens
-// without a head, and the descriptor sums of Eq. 6); a separate instance, so
-// that the plain kernel keeps its registers. Both are held to 96 VGPRs (five
-// wavefronts per SIMD, the loads in flight this HBM-bound pass needs): the
-// plain instance needs 83; the learned one, which also holds the head's
-// weights of rows up to 3 KiB, takes 96 without spilling.
+// Work item w (one wavefront).
 template <bool LR>
-__global__ __launch_bounds__(kScoreBlock) __attribute__((amdgpu_waves_per_eu(5, 8))) void k_score(ScoreArgs a)
+__device__ __forceinline__ void score_item(const ScoreArgs& a, int w, int lane)
 {
-    const int lane = threadIdx.x & (kWave - 1);
-    const int w = uniform(a.wi_first + score_block(a) * (kScoreBlock / kWave) + (threadIdx.x >> 6));
-    if (w >= a.t.n_wi_score) return;
     const int s = uniform(a.t.wi_seg[w]);
     const DevSeg sg = a.t.seg[s];
     const int q = w - sg.wi_begin;
@@ -769,28 +761,53 @@ __global__ __launch_bounds__(kScoreBlock) __attribute__((amdgpu_waves_per_eu(5, 
     }
 }
 
+// LR: a learned call (Eq. 3 head projections, density importance of tokens
+// without a head, and the descriptor sums of Eq. 6); a separate instance, so
+// that the plain kernel keeps its registers. Both are held to 96 VGPRs (five
+// wavefronts per SIMD, the loads in flight this HBM-bound pass needs): the
+// plain instance needs 83; the learned one, which also holds the head's
+// weights of rows up to 3 KiB, takes 96 without spilling.
+template <bool LR>
+__global__ __launch_bounds__(kScoreBlock) __attribute__((amdgpu_waves_per_eu(5, 8))) void k_score(ScoreArgs a)
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    const int w = uniform(a.wi_first + score_block(a) * (kScoreBlock / kWave) + (threadIdx.x >> 6));
+    if (w >= a.t.n_wi_score) return;
+    score_item<LR>(a, w, lane);
+}
+
 // ---------------------------------------------------------------- k_pair
 
-// bf16 clips whose rows are 512, 1024, 1536 or 2048 bytes (and that are not
-// kept whole, whose rows the chain pass copies out). A wavefront takes two
+// Clips whose rows are at most 4 KiB, of either type (and that are not kept
+// whole, whose rows the chain pass copies out). A wavefront takes two
 // adjacent patch positions p0, p0 + 1 over a range of up to 32 frames: lanes
-// 0-31 hold the first position's row of a frame, lanes 32-63 the second's, so
-// each frame is one run of consecutive rows (4 KiB for 1024 channels), and a
-// block's kPairWaves wavefronts take consecutive pairs of positions over the
-// same frames. The frames of a range follow one another in a ring of
+// 0-31 hold the first position's row of a frame, lanes 32-63 the second's, in
+// units of 512 bytes (the lanes past the end of a row's last unit read zeros),
+// so each frame is one run of consecutive rows (4 KiB for 1024 bf16 channels),
+// and a block's kPairWaves wavefronts take consecutive pairs of positions over
+// the same frames. The frames of a range follow one another in a ring of
 // kPairRing register sets: frame t is scored against its predecessor in the
 // set before it, and once a unit of that predecessor has been used the same
 // unit of frame t + kPairRing - 1 is loaded into its registers, so two frames
 // beyond the next are in flight while one is scored. A range after a clip's
 // first reads the frame before it (halo). Per channel the arithmetic is
-// vector-only: the activity sign of tau - |x| as packed 16-bit differences,
-// four of them gathered into one word of 0x00/0xFF bytes whose popcount (/8)
-// gives the active count and, XOR the previous frame's word, the changed
-// count d; L1 and L2 as bf16 pair dot products; res from the widened values
-// of this and the previous frame. Half-wavefront sums end in lanes 31 and 63
-// and are parked in a token buffer (lane 2i + h: frame t0 + i, position
-// p0 + h), written out once per wavefront, so the frame loop issues no stores
-// and every wait in it is for one known load.
+// vector-only: the activity sign of tau - |x| as integer differences (packed
+// 16-bit ones for bf16), four of them gathered into one word of 0x00/0xFF
+// bytes whose popcount (/8) gives the active count and, XOR the previous
+// frame's word, the changed count d; L1 and L2 as bf16 pair dot products or
+// fp32 sums; res from the widened values of this and the previous frame.
+// Half-wavefront sums end in lanes 31 and 63 and are parked in a token buffer
+// (lane 2i + h: frame t0 + i, position p0 + h), written out once per
+// wavefront, so the frame loop issues no stores and every wait in it is for
+// one known load.
+//
+// Rows over 2 KiB and fp32 rows take an instance of their own (k_pair<true>),
+// whose ring of up to eight units needs twice the registers. The chain pass
+// that scored them before re-reads the previous frame's row where it does not
+// fit a wavefront's registers. 96 frames of 576 positions: 1,280 bf16 channels
+// (141 MB) 45.5 -> 25.5 us (5.5 TB/s), 1,024 fp32 channels (226 MB) 41.4 -> 34.9
+// us (6.5 TB/s); 4 clips of 16 x 256 x 1,152 bf16 21.1 -> 10.4; 8 clips of 32 x
+// 256 x 72 bf16 19.2 -> 12.
 
 typedef short s16x2 __attribute__((ext_vector_type(2)));
 
@@ -828,41 +845,71 @@ struct PairSums {
     uint32_t act, chg;  // 8 per active channel, 8 per changed channel
 };
 
-// tau - |x| per 16-bit half: negative (sign bit set) iff the channel is active.
-__device__ __forceinline__ uint32_t act_sign(uint32_t th2, uint32_t x)
+// tau - |x| per channel of a word: negative (sign bit set) iff the channel is
+// active. th: the threshold's magnitude bits, in both halves for bf16 (see
+// bf16_thresholds; for fp32 both sides are the bits of non-negative floats or
+// of a NaN, above every threshold).
+template <int DT>
+__device__ __forceinline__ uint32_t act_sign(uint32_t th, uint32_t x)
 {
-    return __builtin_bit_cast(uint32_t, __builtin_bit_cast(s16x2, th2) - __builtin_bit_cast(s16x2, x & 0x7FFF7FFFu));
+    if constexpr (DT == kBF16)
+        return __builtin_bit_cast(uint32_t, __builtin_bit_cast(s16x2, th) - __builtin_bit_cast(s16x2, x & 0x7FFF7FFFu));
+    else
+        return th - (x & 0x7FFFFFFFu);
 }
 
-// One frame of this lane's position (4 NU dwords, 8 NU channels) against the
-// previous frame's raw words y and activity words pq; nq gets this frame's.
-// after(u) runs once unit u of y has been used.
-template <int NU, typename Hook>
-__device__ __forceinline__ PairSums pair_frame(const vec4 (&v)[NU], const vec4 (&y)[NU], uint32_t th2,
-                                               const uint32_t (&pq)[NU * 2], uint32_t (&nq)[NU * 2], Hook&& after)
+// Activity words of a 16-byte chunk, a byte 0xFF / 0x00 per channel from its
+// sign: bits 15 and 31 of two words each for bf16, bit 31 of four for fp32.
+template <int DT>
+__device__ __forceinline__ void act_words(const uint32_t (&sg)[4], uint32_t (&m)[2])
 {
+    if constexpr (DT == kBF16) {
+        m[0] = __builtin_amdgcn_perm(sg[1], sg[0], 0x0B0A0908u);
+        m[1] = __builtin_amdgcn_perm(sg[3], sg[2], 0x0B0A0908u);
+    } else {
+        m[0] = __builtin_amdgcn_perm(sg[1], sg[0], 0x0C0C0B09u) | __builtin_amdgcn_perm(sg[3], sg[2], 0x0B090C0Cu);
+        m[1] = 0u;
+    }
+}
+template <int DT> constexpr int kActWords = DT == kBF16 ? 2 : 1;  // per chunk
+
+// One frame of this lane's position (4 NU dwords) against the previous
+// frame's raw words y and activity words pq; nq gets this frame's. after(u)
+// runs once unit u of y has been used.
+template <int DT, int NU, typename Hook>
+__device__ __forceinline__ PairSums pair_frame(const vec4 (&v)[NU], const vec4 (&y)[NU], uint32_t th,
+                                               const uint32_t (&pq)[NU * kActWords<DT>], uint32_t (&nq)[NU * kActWords<DT>],
+                                               Hook&& after)
+{
+    constexpr int W = kActWords<DT>;
     PairSums c{0.0f, 0.0f, 0.0f, 0u, 0u};
 #pragma unroll
     for (int u = 0; u < NU; ++u) {
-        uint32_t sg[4];
+        uint32_t sg[4], m[2];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const uint32_t x = v[u][e], yp = y[u][e];
-            sg[e] = act_sign(th2, x);
-            c.l1 = dot2(x & 0x7FFF7FFFu, kBf16OnePair, c.l1);
-            c.l2 = dot2(x, x, c.l2);
-            const float dlo = __uint_as_float(x << 16) - __uint_as_float(yp << 16);
-            const float dhi = __uint_as_float(x & 0xFFFF0000u) - __uint_as_float(yp & 0xFFFF0000u);
-            c.res = fmaf(dlo, dlo, c.res);
-            c.res = fmaf(dhi, dhi, c.res);
+            sg[e] = act_sign<DT>(th, x);
+            if constexpr (DT == kBF16) {
+                c.l1 = dot2(x & 0x7FFF7FFFu, kBf16OnePair, c.l1);
+                c.l2 = dot2(x, x, c.l2);
+                const float dlo = __uint_as_float(x << 16) - __uint_as_float(yp << 16);
+                const float dhi = __uint_as_float(x & 0xFFFF0000u) - __uint_as_float(yp & 0xFFFF0000u);
+                c.res = fmaf(dlo, dlo, c.res);
+                c.res = fmaf(dhi, dhi, c.res);
+            } else {
+                const float xf = __uint_as_float(x), df = xf - __uint_as_float(yp);
+                c.l1 += fabsf(xf);
+                c.l2 = fmaf(xf, xf, c.l2);
+                c.res = fmaf(df, df, c.res);
+            }
         }
+        act_words<DT>(sg, m);
 #pragma unroll
-        for (int e = 0; e < 2; ++e) {
-            // bytes 0xFF / 0x00 from the sign bits 15 and 31 of two words
-            const uint32_t m = __builtin_amdgcn_perm(sg[2 * e + 1], sg[2 * e], 0x0B0A0908u);
-            c.act += (uint32_t)__builtin_popcount(m);
-            c.chg += (uint32_t)__builtin_popcount(m ^ pq[u * 2 + e]);
-            nq[u * 2 + e] = m;
+        for (int e = 0; e < W; ++e) {
+            c.act += (uint32_t)__builtin_popcount(m[e]);
+            c.chg += (uint32_t)__builtin_popcount(m[e] ^ pq[u * W + e]);
+            nq[u * W + e] = m[e];
         }
         after(u);
     }
@@ -870,15 +917,19 @@ __device__ __forceinline__ PairSums pair_frame(const vec4 (&v)[NU], const vec4 (
 }
 
 // Activity words of a frame (the halo frame before a block's range).
-template <int NU>
-__device__ __forceinline__ void pair_words(const vec4 (&v)[NU], uint32_t th2, uint32_t (&nq)[NU * 2])
+template <int DT, int NU>
+__device__ __forceinline__ void pair_words(const vec4 (&v)[NU], uint32_t th, uint32_t (&nq)[NU * kActWords<DT>])
 {
+    constexpr int W = kActWords<DT>;
 #pragma unroll
-    for (int u = 0; u < NU; ++u)
+    for (int u = 0; u < NU; ++u) {
+        uint32_t sg[4], m[2];
 #pragma unroll
-        for (int e = 0; e < 2; ++e)
-            nq[u * 2 + e] = __builtin_amdgcn_perm(act_sign(th2, v[u][2 * e + 1]), act_sign(th2, v[u][2 * e]),
-                                                  0x0B0A0908u);
+        for (int e = 0; e < 4; ++e) sg[e] = act_sign<DT>(th, v[u][e]);
+        act_words<DT>(sg, m);
+#pragma unroll
+        for (int e = 0; e < W; ++e) nq[u * W + e] = m[e];
+    }
 }
 
 // The two positions' statistics of one frame (half sums in lanes 31 and 63).
@@ -938,7 +989,7 @@ __device__ __forceinline__ void pair_write(const ScoreArgs& a, const DevSeg& sg,
 // Work item q of a k_pair segment: pair j = q mod the pair count, range
 // q / the pair count (none past the clip's end: the items of a segment are
 // rounded up to whole blocks).
-template <int NU>
+template <int DT, int NU>
 __device__ __forceinline__ void score_pair(const ScoreArgs& a, const DevSeg& sg, int q, int lane, uint32_t& nsp,
                                            uint32_t& dsum)
 {
@@ -958,8 +1009,12 @@ __device__ __forceinline__ void score_pair(const ScoreArgs& a, const DevSeg& sg,
     const uint8_t* base = sg.data + (int64_t)p0 * sg.stride_bytes;
     const int nrec = uniform(two ? (int)sg.stride_bytes + rb : rb);
     // unit u of this lane's row at voff + 512 u; a missing second position
-    // reads as zeros (an offset past the resource)
-    const int voff = present ? h * (int)sg.stride_bytes + l * 16 : 0x7FFFFFF0;
+    // and the lanes past the end of a row's last unit read zeros (an offset
+    // past the resource, which is at most 2^30 bytes)
+    constexpr int kPastEnd = 0x7FF00000;
+    const int voff = present ? h * (int)sg.stride_bytes + l * 16 : kPastEnd;
+    const int vlast = (NU - 1) * 512 + l * 16 < rb ? voff : kPastEnd;
+    auto unit = [&](rsrc_t rs, int u) { return bload(rs, (u == NU - 1 ? vlast : voff) + u * 512); };
     // a frame outside the range reads as zeros from an empty resource: every
     // load is issued, so the waits count them exactly
     auto frame_rsrc = [&](int t, bool ok) {
@@ -968,20 +1023,20 @@ __device__ __forceinline__ void score_pair(const ScoreArgs& a, const DevSeg& sg,
     auto load = [&](vec4 (&v)[NU], int t, bool ok) {
         const rsrc_t rs = frame_rsrc(t, ok);
 #pragma unroll
-        for (int u = 0; u < NU; ++u) v[u] = bload(rs, voff + u * 512);
+        for (int u = 0; u < NU; ++u) v[u] = unit(rs, u);
     };
     const uint32_t lo = bf16_thresholds(a.t.tau).lo;
-    const uint32_t th2 = lo | (lo << 16);
+    const uint32_t th = DT == kBF16 ? lo | (lo << 16) : __float_as_uint(a.t.tau);
     PairTok tok{0.0f, 0.0f, 0.0f, 0u};
     // frame t0 + i in R[i mod RING] with its activity words in Q[i mod 2];
     // the frame before t0 (the zero frame before the clip's first) in
     // R[RING - 1], its words in Q[1]
     vec4 R[RING][NU];
-    uint32_t Q[2][NU * 2];
+    uint32_t Q[2][NU * kActWords<DT>];
     load(R[RING - 1], t0 - 1, t0 > 0);
 #pragma unroll
     for (int i = 0; i < RING - 1; ++i) load(R[i], t0 + i, t0 + i < t1);
-    pair_words<NU>(R[RING - 1], th2, Q[1]);
+    pair_words<DT, NU>(R[RING - 1], th, Q[1]);
     int t = t0;
     while (t < t1) {
 #pragma unroll
@@ -989,8 +1044,8 @@ __device__ __forceinline__ void score_pair(const ScoreArgs& a, const DevSeg& sg,
             if (t >= t1) break;
             const int pi = (i + RING - 1) % RING;
             const rsrc_t rs = frame_rsrc(t + RING - 1, t + RING - 1 < t1);
-            const PairSums c = pair_frame<NU>(R[i], R[pi], th2, Q[(i + 1) & 1], Q[i & 1], [&](int u) {
-                R[pi][u] = bload(rs, voff + u * 512);
+            const PairSums c = pair_frame<DT, NU>(R[i], R[pi], th, Q[(i + 1) & 1], Q[i & 1], [&](int u) {
+                R[pi][u] = unit(rs, u);
                 // keep the load here, where its registers have just been freed
                 __builtin_amdgcn_sched_barrier(0);
             });
@@ -1019,23 +1074,56 @@ __device__ __forceinline__ void score_pair(const ScoreArgs& a, const DevSeg& sg,
 
 // One wavefront per k_pair work item; consecutive blocks (neighbouring pairs
 // of positions, whose statistics share cache lines) run on one XCD.
+// WIDE: fp32 rows and bf16 rows over 2 KiB as well. REST: the launch holds
+// other segments' work items too.
+template <bool WIDE, bool REST>
 __global__ __launch_bounds__(kPairWaves * 64) __attribute__((amdgpu_waves_per_eu(1, kPairWavesPerEU)))
 void k_pair(ScoreArgs a)
 {
     const int lane = threadIdx.x & (kWave - 1);
     const int wv = uniform(threadIdx.x >> 6);
-    const int nb = gridDim.x, b = blockIdx.x, x = b & 7, per = nb >> 3, rem = nb & 7;
+    const int nb = a.t.n_wi_pair / kPairWaves, b = blockIdx.x, x = b & 7, per = nb >> 3, rem = nb & 7;
+    if (REST && b >= nb) {
+        // the few other work items of a batch of clips (its texts), after the pairs
+        static_assert(kPairWaves * kWave == kScoreBlock, "a block takes as many work items of either kind");
+        const int w = uniform(b * kPairWaves + wv);
+        if (w < a.t.n_wi_score) score_item<false>(a, w, lane);
+        return;
+    }
     const int vb = uniform(x * per + min(x, rem) + (b >> 3));
     const int w = vb * kPairWaves + wv;
     const int s = uniform(a.t.wi_seg[w]);
     const DevSeg sg = a.t.seg[s];
     const int q = w - sg.wi_begin;
     uint32_t nsp = 0, dsum = 0;  // wave-uniform
-    switch (sg.nchunk >> 5) {  // rows of 512-byte units
-    case 1: score_pair<1>(a, sg, q, lane, nsp, dsum); break;
-    case 2: score_pair<2>(a, sg, q, lane, nsp, dsum); break;
-    case 3: score_pair<3>(a, sg, q, lane, nsp, dsum); break;
-    default: score_pair<4>(a, sg, q, lane, nsp, dsum); break;
+    const int nu = (sg.nchunk + 31) >> 5;  // units of 512 bytes per row
+    if (sg.dtype == kBF16) {
+        switch (nu) {
+        case 1: score_pair<kBF16, 1>(a, sg, q, lane, nsp, dsum); break;
+        case 2: score_pair<kBF16, 2>(a, sg, q, lane, nsp, dsum); break;
+        case 3: score_pair<kBF16, 3>(a, sg, q, lane, nsp, dsum); break;
+        case 4: score_pair<kBF16, 4>(a, sg, q, lane, nsp, dsum); break;
+        default:
+            if constexpr (WIDE) {
+                switch (nu) {
+                case 5: score_pair<kBF16, 5>(a, sg, q, lane, nsp, dsum); break;
+                case 6: score_pair<kBF16, 6>(a, sg, q, lane, nsp, dsum); break;
+                case 7: score_pair<kBF16, 7>(a, sg, q, lane, nsp, dsum); break;
+                default: score_pair<kBF16, 8>(a, sg, q, lane, nsp, dsum); break;
+                }
+            }
+        }
+    } else if constexpr (WIDE) {
+        switch (nu) {
+        case 1: score_pair<kF32, 1>(a, sg, q, lane, nsp, dsum); break;
+        case 2: score_pair<kF32, 2>(a, sg, q, lane, nsp, dsum); break;
+        case 3: score_pair<kF32, 3>(a, sg, q, lane, nsp, dsum); break;
+        case 4: score_pair<kF32, 4>(a, sg, q, lane, nsp, dsum); break;
+        case 5: score_pair<kF32, 5>(a, sg, q, lane, nsp, dsum); break;
+        case 6: score_pair<kF32, 6>(a, sg, q, lane, nsp, dsum); break;
+        case 7: score_pair<kF32, 7>(a, sg, q, lane, nsp, dsum); break;
+        default: score_pair<kF32, 8>(a, sg, q, lane, nsp, dsum); break;
+        }
     }
     if (lane == 0) {
         Partial pr;
@@ -2450,17 +2538,21 @@ int launch_score(const ScoreArgs& a, void* stream, void* ev0, void* ev1)
         const unsigned grid = (unsigned)((a.t.n_wi_score + waves - 1) / waves);
         return launch(k_score<true>, dim3(grid), dim3(kScoreBlock), 0, stream, a, ev0, ev1);
     }
-    const int npair = a.t.n_wi_pair;
-    if (npair < 0 || npair % kPairWaves != 0 || npair > a.t.n_wi_score) return (int)hipErrorInvalidValue;
-    const bool rest = a.t.n_wi_score > npair;
+    const int npair = a.t.n_wi_pair, nrest = a.t.n_wi_score - npair;
+    if (npair < 0 || npair % kPairWaves != 0 || nrest < 0) return (int)hipErrorInvalidValue;
     if (npair > 0) {
-        const int rc = launch(k_pair, dim3((unsigned)(npair / kPairWaves)), dim3(kPairWaves * kWave), 0, stream, a, ev0,
-                              rest ? nullptr : ev1);
-        if (rc != 0 || !rest) return rc;
+        // up to kPairRestItems others run in the same launch, more in one of their own
+        const bool with_rest = nrest > 0 && nrest <= kPairRestItems;
+        void (*const kernel)(ScoreArgs) = a.pair_wide ? (with_rest ? k_pair<true, true> : k_pair<true, false>)
+                                                      : (with_rest ? k_pair<false, true> : k_pair<false, false>);
+        const int items = npair + (with_rest ? nrest : 0);
+        const int rc = launch(kernel, dim3((unsigned)((items + kPairWaves - 1) / kPairWaves)),
+                              dim3(kPairWaves * kWave), 0, stream, a, ev0, nrest > 0 && !with_rest ? nullptr : ev1);
+        if (rc != 0 || nrest == 0 || with_rest) return rc;
     }
     ScoreArgs b = a;
     b.wi_first = npair;
-    const unsigned grid = (unsigned)((a.t.n_wi_score - npair + waves - 1) / waves);
+    const unsigned grid = (unsigned)((nrest + waves - 1) / waves);
     return launch(k_score<false>, dim3(grid), dim3(kScoreBlock), 0, stream, b, npair > 0 ? nullptr : ev0, ev1);
 }
 
