@@ -149,6 +149,7 @@ struct Plan {
     int n_big_blk = 0;             // the first of them: chunks of large selections
     size_t off_big = 0;            // what their passes hand on
     bool lean = false;             // no room for that
+    bool no_select = false;        // a call without a selection: no records
     int n_hi = 0;                  // SimHash calls: hash tiles
     bool any_temporal = false, any_guided = false;
     bool any_copy = false;         // some segment is compacted by the scoring pass
@@ -321,6 +322,7 @@ void build_plan(const msao_ctx* ctx, const msao_segment* segs, int n, int R, con
         const int kind = by_imp ? kKeyImp
                          : d.temporal && L_t > 0 ? (L_s > 0 ? kKeyFull : kKeyE) : (L_s > 0 ? kKeyZ : kKeyZero);
         auto push_selection = [&](int frame, int n_u, int kfix) {
+            if (pl.no_select) return;
             SelUnit u;
             std::memset(&u, 0, sizeof u);
             u.Ms = d.key_ms;
@@ -616,13 +618,19 @@ void wait_stage(msao_ctx* ctx, int slot)
 // error instead of a new pinned allocation (msao_run_noalloc allocates nothing).
 msao_status upload(msao_ctx* ctx, const Plan& pl, int n, void* ws, hipStream_t stream, bool grow = true)
 {
+    // small tables go into the launch itself, larger ones through a slot
+    const bool small = pl.copy_bytes <= kUploadInline;
+    alignas(16) uint8_t small_tables[kUploadInline];
     const int slot = ctx->next_slot;
-    if (!grow && ctx->stage_cap[slot] < pl.copy_bytes)
-        return fail(&ctx->err, MSAO_ERR_UNSUPPORTED, "per-call tables larger than the context's reserved staging");
-    ctx->next_slot = (slot + 1) % kStageSlots;
-    wait_stage(ctx, slot);
-    if (ctx->stage_cap[slot] < pl.copy_bytes) MSAO_TRY(reserve_stage(ctx, slot, pl.copy_bytes));
-    uint8_t* h = (uint8_t*)ctx->stage[slot];
+    uint8_t* h = small_tables;
+    if (!small) {
+        if (!grow && ctx->stage_cap[slot] < pl.copy_bytes)
+            return fail(&ctx->err, MSAO_ERR_UNSUPPORTED, "per-call tables larger than the context's reserved staging");
+        ctx->next_slot = (slot + 1) % kStageSlots;
+        wait_stage(ctx, slot);
+        if (ctx->stage_cap[slot] < pl.copy_bytes) MSAO_TRY(reserve_stage(ctx, slot, pl.copy_bytes));
+        h = (uint8_t*)ctx->stage[slot];
+    }
     auto put = [&](size_t off, const void* src, size_t bytes) {
         if (bytes) std::memcpy(h + off, src, bytes);
     };
@@ -650,10 +658,13 @@ msao_status upload(msao_ctx* ctx, const Plan& pl, int n, void* ws, hipStream_t s
     a.frame_seg = (int32_t*)(b + pl.off_frseg);
     a.cl_seg = (int32_t*)(b + pl.off_clseg);
     a.hi_seg = (int32_t*)(b + pl.off_hiseg);
-    // a graph's replays read the slot again, whenever they come: no word from them
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(stream, &cap) != hipSuccess) (void)hipGetLastError();
-    const bool tracked = cap == hipStreamCaptureStatusNone;
+    bool tracked = false;
+    if (!small) {
+        // a graph's replays read the slot again, whenever they come: no word from them
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(stream, &cap) != hipSuccess) (void)hipGetLastError();
+        tracked = cap == hipStreamCaptureStatusNone;
+    }
     if (tracked) {
         a.done = ctx->stage_done + slot * kUploadMaxBlocks;
         a.ticket = ++ctx->stage_ticket[slot];
@@ -1043,7 +1054,7 @@ msao_status msao_mas_score(msao_ctx* ctx, const msao_segment* segs, int n, int R
     if (!ctx) return fail(&g_err, MSAO_ERR_INVALID_ARG, "ctx is NULL");
     MSAO_TRY(validate_impl(segs, n, R, params, &ctx->err));
     Plan pl;
-    pl.lean = true;  // no selection
+    pl.no_select = true;
     build_plan(ctx, segs, n, R, params, alpha, nullptr, pl);
     MSAO_TRY(check_ws(ctx, pl, ws, ws_bytes));
     const bool want_frames = frm && (frm->dframe || frm->sim || frm->gamma) && pl.nframes > 0;
@@ -1085,7 +1096,7 @@ msao_status msao_temporal_redundancy(msao_ctx* ctx, const msao_segment* segs, in
     if (!ctx) return fail(&g_err, MSAO_ERR_INVALID_ARG, "ctx is NULL");
     MSAO_TRY(validate_impl(segs, n, R, params, &ctx->err));
     Plan pl;
-    pl.lean = true;  // no selection
+    pl.no_select = true;
     build_plan(ctx, segs, n, R, params, nullptr, nullptr, pl);
     MSAO_TRY(check_ws(ctx, pl, ws, ws_bytes));
     const bool want_frames = frm && (frm->dframe || frm->sim || frm->gamma) && pl.nframes > 0;
@@ -1124,7 +1135,7 @@ msao_status msao_temporal_simhash(msao_ctx* ctx, const msao_segment* segs, int n
     MSAO_TRY(validate_impl(segs, n, R, params, &ctx->err));
     MSAO_TRY(check_hashes(ctx, segs, n, hashes));
     Plan pl;
-    pl.lean = true;  // no selection
+    pl.no_select = true;
     build_plan(ctx, segs, n, R, params, nullptr, nullptr, pl, false, nullptr, false, 0, hashes);
     MSAO_TRY(check_ws(ctx, pl, ws, ws_bytes));
     if (pl.ntok > 0 && (!sig || !d)) return fail(&ctx->err, MSAO_ERR_INVALID_ARG, "sig and d are required");
@@ -1189,7 +1200,7 @@ msao_status msao_compact(msao_ctx* ctx, const msao_segment* segs, int n, const i
     msao_params p = msao_default_params();
     MSAO_TRY(validate_impl(segs, n, R, &p, &ctx->err));
     Plan pl;
-    pl.lean = true;  // no selection
+    pl.no_select = true;
     build_plan(ctx, segs, n, R, &p, nullptr, out_byte_off, pl, false, nullptr, false, 0, nullptr, true);
     MSAO_TRY(check_ws(ctx, pl, ws, ws_bytes));
     if (pl.ntok > 0 && (!kept_idx || !kept_count))
@@ -1260,7 +1271,7 @@ msao_status msao_mas_score_learned(msao_ctx* ctx, const msao_segment* segs, int 
     MSAO_TRY(validate_impl(segs, n, R, params, &ctx->err));
     MSAO_TRY(check_learned(ctx, segs, n, heads, mlp));
     Plan pl;
-    pl.lean = true;  // no selection
+    pl.no_select = true;
     build_plan(ctx, segs, n, R, params, alpha, nullptr, pl, false, heads, true, mlp ? mlp->hidden : 0);
     MSAO_TRY(check_ws(ctx, pl, ws, ws_bytes));
     const bool want_frames = frm && (frm->dframe || frm->sim || frm->gamma) && pl.nframes > 0;

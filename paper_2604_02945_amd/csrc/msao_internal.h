@@ -310,7 +310,8 @@ struct GatherArgs {
 // (msao_upload.hip). copy_bytes lead the tables and are staged; the arrays
 // that name the segment of each item are written from the segment records.
 struct UploadArgs {
-    const uint8_t* src;      // pinned staging slot (the segment records first)
+    const uint8_t* src;      // the staged tables (the segment records first): a pinned slot, or
+                             // any host memory for copy_bytes <= kUploadInline
     uint8_t* dst;            // workspace
     uint32_t copy_bytes;     // a multiple of 16
     int32_t n;               // segments
@@ -324,6 +325,11 @@ constexpr int kUploadBlock = 256;
 constexpr int kUploadCopyBytes = 8192;   // staged bytes per unit
 constexpr int kUploadFill = 8192;        // entries per stripe of a run
 constexpr int kUploadMaxBlocks = 256;
+constexpr uint32_t kUploadInline = 3072;
+struct UploadInline {
+    UploadArgs a;            // src and done not used
+    alignas(16) uint8_t tables[kUploadInline];
+};
 int launch_upload(const UploadArgs& a, int blocks, void* stream);
 
 // Draft-model confidence (msao_entropy.hip): one row of logits per workgroup.

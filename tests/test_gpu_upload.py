@@ -92,10 +92,12 @@ def test_uploads_waiting_on_the_gpu(entry, dev):
     ctx.close()
 
 
-def test_call_recorded_into_a_graph(dev):
+@pytest.mark.parametrize("which", [0, 3])
+def test_call_recorded_into_a_graph(which, dev):
+    """Tables in the launch's arguments (table 0), and in a staging slot."""
     print("[upload] graph", flush=True)
     ctx = msao.Context(0)
-    segs, R = table(3)
+    segs, R = table(which)
     ds = to_device(segs, dev)
     o = msao.Outputs(ds, R, workspace=False)
     call = B.prepare("msao_run_noalloc", ds, R, o, default_params(), ctx=ctx)
