@@ -616,7 +616,11 @@ void wait_stage(msao_ctx* ctx, int slot)
 // Put the tables into a pinned slot and enqueue the kernel that brings them
 // into the workspace. With grow false a slot smaller than the tables is an
 // error instead of a new pinned allocation (msao_run_noalloc allocates nothing).
-msao_status upload(msao_ctx* ctx, const Plan& pl, int n, void* ws, hipStream_t stream, bool grow = true)
+// With `in_score` and tables of at most kUploadInline bytes nothing is
+// enqueued: the arguments and the tables are put there for the scoring launch
+// to bring along, and *deferred says so.
+msao_status upload(msao_ctx* ctx, const Plan& pl, int n, void* ws, hipStream_t stream, bool grow = true,
+                   ScoreInline* in_score = nullptr, bool* deferred = nullptr)
 {
     // small tables go into the launch itself, larger ones through a slot
     const bool small = pl.copy_bytes <= kUploadInline;
@@ -668,6 +672,12 @@ msao_status upload(msao_ctx* ctx, const Plan& pl, int n, void* ws, hipStream_t s
     if (tracked) {
         a.done = ctx->stage_done + slot * kUploadMaxBlocks;
         a.ticket = ++ctx->stage_ticket[slot];
+    }
+    if (in_score && small && pl.n_wi_score > 0) {
+        in_score->up = a;
+        std::memcpy(in_score->tables, h, pl.copy_bytes);
+        *deferred = true;
+        return MSAO_OK;
     }
     const int64_t units = a.copy_units + (int64_t)n * a.fill_parts;
     const int blocks = (int)std::min<int64_t>(units, kUploadMaxBlocks);
@@ -793,6 +803,10 @@ msao_status launched(msao_ctx* ctx, int kernel, hipStream_t stream, int (*fn)(co
 }
 
 int run_score(const void* a, void* s, void* e0, void* e1) { return launch_score(*(const ScoreArgs*)a, s, e0, e1); }
+int run_score_inline(const void* a, void* s, void* e0, void* e1)
+{
+    return launch_score_inline(*(const ScoreInline*)a, s, e0, e1);
+}
 int run_post(const void* a, void* s, void* e0, void* e1) { return launch_post(*(const PostArgs*)a, s, e0, e1); }
 int run_gather(const void* a, void* s, void* e0, void* e1) { return launch_gather(*(const GatherArgs*)a, s, e0, e1); }
 int run_entropy(const void* a, void* s, void* e0, void* e1) { return launch_entropy(*(const EntArgs*)a, s, e0, e1); }
@@ -803,6 +817,13 @@ int run_read(const void* a, void* s, void* e0, void* e1) { return launch_read(*(
 int run_hash_post(const void* a, void* s, void* e0, void* e1)
 {
     return launch_hash_post(*(const HashArgs*)a, s, e0, e1);
+}
+
+// The scoring launch, with the tables that upload() left for it if it did.
+msao_status score_launch(msao_ctx* ctx, hipStream_t stream, const ScoreInline& si, bool inline_tables)
+{
+    return inline_tables ? launched(ctx, MSAO_KERNEL_SCORE, stream, run_score_inline, &si)
+                         : launched(ctx, MSAO_KERNEL_SCORE, stream, run_score, &si.a);
 }
 
 // Scoring block order. The order with one contiguous range of work items per
@@ -1065,8 +1086,10 @@ msao_status msao_mas_score(msao_ctx* ctx, const msao_segment* segs, int n, int R
     if (req) MSAO_TRY(check_out_alignment(ctx, {{req->agg, 8}, {req->rho, 4}, {req->temporal, 4}, {req->beta, 4}, {req->mas, 4}}));
     DeviceGuard guard(ctx->device);
     hipStream_t st = (hipStream_t)stream;
-    MSAO_TRY(upload(ctx, pl, n, ws, st));
-    ScoreArgs sa;
+    ScoreInline si;
+    bool deferred = false;
+    MSAO_TRY(upload(ctx, pl, n, ws, st, true, &si, &deferred));
+    ScoreArgs& sa = si.a;
     std::memset(&sa, 0, sizeof sa);
     sa.t = device_tables(pl, ws, n, R, params);
     sa.tok = token_out(tok);
@@ -1074,7 +1097,7 @@ msao_status msao_mas_score(msao_ctx* ctx, const msao_segment* segs, int n, int R
     sa.mode = kModeScore;
     sa.pair_wide = pl.pair_wide ? 1 : 0;
     sa.xcd_order = xcd_order_for(ctx, false);
-    MSAO_TRY(launched(ctx, MSAO_KERNEL_SCORE, st, run_score, &sa));
+    MSAO_TRY(score_launch(ctx, st, si, deferred));
     PostArgs pa;
     std::memset(&pa, 0, sizeof pa);
     pa.t = sa.t;
@@ -1105,8 +1128,10 @@ msao_status msao_temporal_redundancy(msao_ctx* ctx, const msao_segment* segs, in
     if (frm) MSAO_TRY(check_out_alignment(ctx, {{frm->dframe, 8}, {frm->sim, 4}, {frm->gamma, 4}}));
     DeviceGuard guard(ctx->device);
     hipStream_t st = (hipStream_t)stream;
-    MSAO_TRY(upload(ctx, pl, n, ws, st));
-    ScoreArgs sa;
+    ScoreInline si;
+    bool deferred = false;
+    MSAO_TRY(upload(ctx, pl, n, ws, st, true, &si, &deferred));
+    ScoreArgs& sa = si.a;
     std::memset(&sa, 0, sizeof sa);
     sa.t = device_tables(pl, ws, n, R, params);
     sa.tok.d = d;
@@ -1114,7 +1139,7 @@ msao_status msao_temporal_redundancy(msao_ctx* ctx, const msao_segment* segs, in
     sa.mode = kModeTemporal;
     sa.pair_wide = pl.pair_wide ? 1 : 0;
     sa.xcd_order = xcd_order_for(ctx, false);
-    MSAO_TRY(launched(ctx, MSAO_KERNEL_SCORE, st, run_score, &sa));
+    MSAO_TRY(score_launch(ctx, st, si, deferred));
     PostArgs pa;
     std::memset(&pa, 0, sizeof pa);
     pa.t = sa.t;
@@ -1412,9 +1437,11 @@ msao_status check_run_outputs(msao_ctx* ctx, const Plan& pl, const std::vector<m
 // sampling's before MAS, the per-frame terms and selection read them.
 msao_status enqueue_run(msao_ctx* ctx, const Plan& pl, const Tables& t, const msao_token_out* tok,
                         const msao_frame_out* frm, const msao_req_out* req, const msao_select_out* sel, void* out,
-                        int64_t out_bytes, hipStream_t st, uint64_t* sig = nullptr)
+                        int64_t out_bytes, hipStream_t st, uint64_t* sig = nullptr, ScoreInline* in_score = nullptr)
 {
-    ScoreArgs sa;
+    ScoreInline own;
+    ScoreInline& si = in_score ? *in_score : own;
+    ScoreArgs& sa = si.a;
     std::memset(&sa, 0, sizeof sa);
     sa.t = t;
     sa.tok = token_out(tok);
@@ -1423,7 +1450,7 @@ msao_status enqueue_run(msao_ctx* ctx, const Plan& pl, const Tables& t, const ms
     sa.mode = kModeScore;
     sa.pair_wide = pl.pair_wide ? 1 : 0;
     sa.xcd_order = xcd_order_for(ctx, out && pl.any_copy);
-    MSAO_TRY(launched(ctx, MSAO_KERNEL_SCORE, st, run_score, &sa));
+    MSAO_TRY(score_launch(ctx, st, si, in_score != nullptr));
     if (pl.clip_fused) {
         // the clips: statistics, signatures, d and partials in one pass
         ClipArgs ca;
@@ -1509,8 +1536,11 @@ msao_status msao_run(msao_ctx* ctx, const msao_segment* segs, int n, int R, cons
     MSAO_TRY(check_run_outputs(ctx, pl, sv, tok, frm, req, sel, out, out_byte_off, out_bytes));
     DeviceGuard guard(ctx->device);
     hipStream_t st = (hipStream_t)stream;
-    MSAO_TRY(upload(ctx, pl, n, ws, st));
-    return enqueue_run(ctx, pl, device_tables(pl, ws, n, R, params), tok, frm, req, sel, out, out_bytes, st);
+    ScoreInline si;
+    bool deferred = false;
+    MSAO_TRY(upload(ctx, pl, n, ws, st, true, &si, &deferred));
+    return enqueue_run(ctx, pl, device_tables(pl, ws, n, R, params), tok, frm, req, sel, out, out_bytes, st, nullptr,
+                       deferred ? &si : nullptr);
 }
 
 static_assert(kNoAllocScratchBytes == MSAO_NOALLOC_SCRATCH_BYTES && kNoAllocTableBytes == MSAO_NOALLOC_TABLE_BYTES,
@@ -1541,8 +1571,11 @@ msao_status msao_run_noalloc(msao_ctx* ctx, const msao_segment* segs, int n, int
     if (!ws) return fail(&ctx->err, MSAO_ERR_HIP, "the scratch array of this device was not set up");
     DeviceGuard guard(ctx->device);
     hipStream_t st = (hipStream_t)stream;
-    MSAO_TRY(upload(ctx, pl, n, ws, st, false));
-    return enqueue_run(ctx, pl, device_tables(pl, ws, n, R, params), tok, frm, req, sel, out, out_bytes, st);
+    ScoreInline si;
+    bool deferred = false;
+    MSAO_TRY(upload(ctx, pl, n, ws, st, false, &si, &deferred));
+    return enqueue_run(ctx, pl, device_tables(pl, ws, n, R, params), tok, frm, req, sel, out, out_bytes, st, nullptr,
+                       deferred ? &si : nullptr);
 }
 
 msao_status msao_run_simhash(msao_ctx* ctx, const msao_segment* segs, int n, int R, const msao_params* params,

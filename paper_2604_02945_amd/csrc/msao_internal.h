@@ -332,6 +332,17 @@ struct UploadInline {
 };
 int launch_upload(const UploadArgs& a, int blocks, void* stream);
 
+// A scoring launch that brings its call's small tables along: its blocks read
+// the segment records from the arguments and write the tables for the
+// launches that follow.
+struct ScoreInline {
+    ScoreArgs a;
+    UploadArgs up;           // src and done not used
+    alignas(16) uint8_t tables[kUploadInline];
+};
+static_assert(sizeof(ScoreInline) <= 4096, "a launch takes 4 KiB of arguments");
+int launch_score_inline(const ScoreInline& u, void* stream, void* ev0, void* ev1);
+
 // Draft-model confidence (msao_entropy.hip): one row of logits per workgroup.
 struct EntArgs {
     const uint8_t* logits;   // row r starts at logits + r * row_bytes

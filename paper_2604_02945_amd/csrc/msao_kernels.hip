@@ -26,6 +26,7 @@
 
 #include "msao_device.h"
 #include "msao_internal.h"
+#include "msao_upload.h"
 
 namespace msao {
 namespace {
@@ -720,12 +721,39 @@ __device__ __forceinline__ int score_block(const ScoreArgs& a)
     return x * per + min(x, rem) + (b >> 3);
 }
 
-// Work item w (one wavefront).
+// The segment of a work item, from the tables in the workspace, or, where the
+// launch itself brings them, from the records in its arguments (a dozen at
+// most, searched; scalar loads either way).
+struct TableSegs {
+    const Tables& t;
+    __device__ __forceinline__ DevSeg of(int w) const { return t.seg[uniform(t.wi_seg[w])]; }
+};
+struct ArgSegs {
+    args_ptr rec;
+    int n;
+    __device__ __forceinline__ DevSeg of(int w) const
+    {
+        constexpr int kWords = (int)sizeof(DevSeg) / 4;
+        typedef const __attribute__((address_space(4))) uint32_t* words;
+        const words r = (words)rec;
+        int s = 0;
+        for (int i = 0; i < n; ++i) {
+            const int begin = (int)r[i * kWords + (int)offsetof(DevSeg, wi_begin) / 4];
+            const int items = (int)r[i * kWords + (int)offsetof(DevSeg, n_items) / 4];
+            if (w >= begin && w < begin + items) s = i;
+        }
+        s = uniform(s);
+        struct { uint32_t v[kWords]; } raw;
+#pragma unroll
+        for (int k = 0; k < kWords; ++k) raw.v[k] = r[s * kWords + k];
+        return __builtin_bit_cast(DevSeg, raw);
+    }
+};
+
+// Work item w (one wavefront) of segment sg.
 template <bool LR>
-__device__ __forceinline__ void score_item(const ScoreArgs& a, int w, int lane)
+__device__ __forceinline__ void score_item(const ScoreArgs& a, const DevSeg& sg, int w, int lane)
 {
-    const int s = uniform(a.t.wi_seg[w]);
-    const DevSeg sg = a.t.seg[s];
     const int q = w - sg.wi_begin;
     uint32_t nsp = 0;
     uint64_t dsum = 0;
@@ -773,7 +801,22 @@ __global__ __launch_bounds__(kScoreBlock) __attribute__((amdgpu_waves_per_eu(5, 
     const int lane = threadIdx.x & (kWave - 1);
     const int w = uniform(a.wi_first + score_block(a) * (kScoreBlock / kWave) + (threadIdx.x >> 6));
     if (w >= a.t.n_wi_score) return;
-    score_item<LR>(a, w, lane);
+    score_item<LR>(a, TableSegs{a.t}.of(w), w, lane);
+}
+
+// k_score<false> with the call's tables in its arguments, so that a small call
+// is one launch shorter: an image request 17.6 -> 13.3 us in all (the upload's
+// 2.9 us on the GPU and its launch on the host), this kernel 4.5 -> 5.2. The
+// tables for the following launches are written last: before the work item
+// they would keep scalar registers busy through it.
+__global__ __launch_bounds__(kScoreBlock) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_score_inline(ScoreInline u)
+{
+    static_assert(kScoreBlock == kUploadBlock && kPairWaves * kWave == kUploadBlock, "the blocks write tables too");
+    const args_ptr tables = kernel_args() + offsetof(ScoreInline, tables);
+    const int lane = threadIdx.x & (kWave - 1);
+    const int w = uniform(score_block(u.a) * (kScoreBlock / kWave) + (threadIdx.x >> 6));
+    if (w < u.a.t.n_wi_score) score_item<false>(u.a, ArgSegs{tables, u.up.n}.of(w), w, lane);
+    upload_tables(u.up, (const uint8_t*)tables);
 }
 
 // ---------------------------------------------------------------- k_pair
@@ -1076,9 +1119,8 @@ __device__ __forceinline__ void score_pair(const ScoreArgs& a, const DevSeg& sg,
 // of positions, whose statistics share cache lines) run on one XCD.
 // WIDE: fp32 rows and bf16 rows over 2 KiB as well. REST: the launch holds
 // other segments' work items too.
-template <bool WIDE, bool REST>
-__global__ __launch_bounds__(kPairWaves * 64) __attribute__((amdgpu_waves_per_eu(1, kPairWavesPerEU)))
-void k_pair(ScoreArgs a)
+template <bool WIDE, bool REST, typename Segs>
+__device__ __forceinline__ void pair_block(const ScoreArgs& a, const Segs& segs)
 {
     const int lane = threadIdx.x & (kWave - 1);
     const int wv = uniform(threadIdx.x >> 6);
@@ -1087,13 +1129,12 @@ void k_pair(ScoreArgs a)
         // the few other work items of a batch of clips (its texts), after the pairs
         static_assert(kPairWaves * kWave == kScoreBlock, "a block takes as many work items of either kind");
         const int w = uniform(b * kPairWaves + wv);
-        if (w < a.t.n_wi_score) score_item<false>(a, w, lane);
+        if (w < a.t.n_wi_score) score_item<false>(a, segs.of(w), w, lane);
         return;
     }
     const int vb = uniform(x * per + min(x, rem) + (b >> 3));
     const int w = vb * kPairWaves + wv;
-    const int s = uniform(a.t.wi_seg[w]);
-    const DevSeg sg = a.t.seg[s];
+    const DevSeg sg = segs.of(w);
     const int q = w - sg.wi_begin;
     uint32_t nsp = 0, dsum = 0;  // wave-uniform
     const int nu = (sg.nchunk + 31) >> 5;  // units of 512 bytes per row
@@ -1132,6 +1173,23 @@ void k_pair(ScoreArgs a)
         pr.dsum = dsum;
         a.t.partial[w] = pr;
     }
+}
+
+template <bool WIDE, bool REST>
+__global__ __launch_bounds__(kPairWaves * 64) __attribute__((amdgpu_waves_per_eu(1, kPairWavesPerEU)))
+void k_pair(ScoreArgs a)
+{
+    pair_block<WIDE, REST>(a, TableSegs{a.t});
+}
+
+// k_pair<WIDE, true> with the call's tables in its arguments.
+template <bool WIDE>
+__global__ __launch_bounds__(kPairWaves * 64) __attribute__((amdgpu_waves_per_eu(1, kPairWavesPerEU)))
+void k_pair_inline(ScoreInline u)
+{
+    const args_ptr tables = kernel_args() + offsetof(ScoreInline, tables);
+    upload_tables(u.up, (const uint8_t*)tables);
+    pair_block<WIDE, true>(u.a, ArgSegs{tables, u.up.n});
 }
 
 // ---------------------------------------------------------------- k_post
@@ -2554,6 +2612,29 @@ int launch_score(const ScoreArgs& a, void* stream, void* ev0, void* ev1)
     b.wi_first = npair;
     const unsigned grid = (unsigned)((nrest + waves - 1) / waves);
     return launch(k_score<false>, dim3(grid), dim3(kScoreBlock), 0, stream, b, npair > 0 ? nullptr : ev0, ev1);
+}
+
+// The same with the tables in the arguments of its first launch.
+int launch_score_inline(const ScoreInline& u, void* stream, void* ev0, void* ev1)
+{
+    const ScoreArgs& a = u.a;
+    const int waves = kScoreBlock / kWave;
+    const int npair = a.t.n_wi_pair, nrest = a.t.n_wi_score - npair;
+    if (a.learned || a.t.n_wi_score <= 0 || npair < 0 || npair % kPairWaves != 0 || nrest < 0 || u.up.n < 1)
+        return (int)hipErrorInvalidValue;
+    if (npair == 0)
+        return launch(k_score_inline, dim3((unsigned)((nrest + waves - 1) / waves)), dim3(kScoreBlock), 0, stream, u, ev0, ev1);
+    const bool with_rest = nrest <= kPairRestItems;
+    const int items = npair + (with_rest ? nrest : 0);
+    ScoreInline p = u;
+    if (!with_rest) p.a.t.n_wi_score = npair;
+    const int rc = launch(a.pair_wide ? k_pair_inline<true> : k_pair_inline<false>,
+                          dim3((unsigned)((items + kPairWaves - 1) / kPairWaves)), dim3(kPairWaves * kWave), 0, stream, p, ev0,
+                          with_rest ? ev1 : nullptr);
+    if (rc != 0 || with_rest) return rc;
+    ScoreArgs b = a;
+    b.wi_first = npair;
+    return launch(k_score<false>, dim3((unsigned)((nrest + waves - 1) / waves)), dim3(kScoreBlock), 0, stream, b, nullptr, ev1);
 }
 
 // Launches with a selection of kPostBigSegment tokens or more (the host's

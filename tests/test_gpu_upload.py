@@ -125,3 +125,36 @@ def test_call_recorded_into_a_graph(which, dev):
     got = snapshot(o, R, len(ds), ds)
     assert all(np.array_equal(got[k].view(np.uint8), v.view(np.uint8)) for k, v in want.items())
     ctx.close()
+
+
+@pytest.mark.parametrize("kind", ["rows", "clips", "clips and many rows"])
+@pytest.mark.parametrize("n", [1, 2, 6, 8, 9, 10, 11, 12, 13, 16])
+def test_tables_with_the_scoring_launch(n, kind, dev):
+    """Calls on both sides of the table size that travels with the scoring
+    launch (about ten segments), against the same run from a plan's tables."""
+    print(f"[upload] {n} segments, {kind}", flush=True)
+    rng = np.random.default_rng(n)
+    segs = []
+    for i in range(n):
+        if kind != "rows" and i % 2 == 0:
+            segs.append(_rand_seg(rng, i % 3, VIDEO, 2 + i, 3 + i % 4, 64 * (1 + i % 3), "bf16" if i % 4 else "f32", 0.4))
+        else:
+            rows = 5000 if kind == "clips and many rows" and i == 1 else 20 + 9 * i
+            segs.append(_rand_seg(rng, i % 3, IMAGE, 1, rows, 1024 if rows == 5000 else 72, "bf16", 1.0 if i % 5 == 3 else -1.0, "relu_bg"))
+    ds, p, R = to_device(segs, dev), default_params(), 3
+    ctx = msao.Context(0)
+    o, q = msao.Outputs(ds, R), msao.Outputs(ds, R)
+    plan = msao.Plan(ds, R, q, p, ctx=ctx)
+    for out in (o, q):
+        out.workspace.fill_(0xA5) if out is o else None
+        out.out.zero_()
+    plan()
+    call = B.prepare("msao_run", ds, R, o, p, ctx=ctx)
+    for _ in range(2):
+        call()
+    torch.cuda.synchronize()
+    want, got = snapshot(q, R, n, ds), snapshot(o, R, n, ds)
+    for k, v in want.items():
+        assert np.array_equal(got[k].view(np.uint8), v.view(np.uint8)), k
+    plan.close()
+    ctx.close()
