@@ -148,7 +148,7 @@ struct Plan {
     std::vector<SelUnit> sel_unit; // selection blocks: a segment, or a frame (per-frame scope), or a part of one
     int n_big_blk = 0;             // the first of them: chunks of large selections
     size_t off_big = 0;            // what their passes hand on
-    bool lean = false;             // no room for that
+    bool lean = false;             // no room for that, nor for k_pair's short ranges and wide rows
     bool no_select = false;        // a call without a selection: no records
     int n_hi = 0;                  // SimHash calls: hash tiles
     bool any_temporal = false, any_guided = false;
@@ -395,8 +395,10 @@ void build_plan(const msao_ctx* ctx, const msao_segment* segs, int n, int R, con
         // scoring work items, one wavefront each
         int items = 0;
         const int64_t row_bytes = (int64_t)s.hidden * es;
+        // (a lean plan leaves the wide rows to the chain pass, whose items are fewer on clips of over 64 frames)
+        const bool lean_wide = pl.lean && (s.dtype != MSAO_BF16 || row_bytes > kPairNarrowRowBytes || row_bytes % 512 != 0);
         if (d.temporal && !d.fused && !learned && !d.copy_in_score && (!ctx || ctx->pair_path) &&
-            row_bytes <= kPairMaxRowBytes && s.tokens_per_frame >= 2 &&
+            row_bytes <= kPairMaxRowBytes && !lean_wide && s.tokens_per_frame >= 2 &&
             d.stride_bytes + row_bytes <= (1 << 30)) {
             // k_pair: one wavefront per pair of positions and range of at most
             // kPairMaxFrames frames (a range after the first reads the frame
@@ -418,7 +420,7 @@ void build_plan(const msao_ctx* ctx, const msao_segment* segs, int n, int R, con
                         best_cost = cost;
                         best = f;
                     }
-                    if (f <= kPairMinFrames) break;
+                    if (f <= (pl.lean ? kPairLeanMinFrames : kPairMinFrames)) break;
                 }
                 F = best;
             }
@@ -734,15 +736,19 @@ Tables device_tables(const Plan& pl, void* ws, int n, int R, const msao_params* 
 }
 
 // Builds a plan within `limit` bytes of workspace and `table_limit` of
-// tables where one exists: without the areas of large selections if it does
-// not fit with them (the tables are then larger, one record per
-// kSelPartTokens tokens instead of kBigChunk).
+// tables where one exists: if it does not fit, without the areas of large
+// selections (whose tables are then larger, one record per kSelPartTokens
+// tokens instead of kBigChunk) and with the clips' scoring cut into fewer
+// work items.
 template <typename Build>
 void build_within(Plan& pl, size_t table_limit, size_t limit, Build&& build)
 {
+    const bool no_select = pl.no_select;
     build(pl);
-    if (pl.n_big_blk == 0 || (pl.table_bytes <= table_limit && pl.total_bytes <= limit)) return;
+    if (pl.table_bytes <= table_limit && pl.total_bytes <= limit) return;
+    if (pl.n_big_blk == 0 && pl.n_wi_pair == 0) return;
     pl = Plan{};
+    pl.no_select = no_select;
     pl.lean = true;
     build(pl);
 }
@@ -1076,7 +1082,7 @@ msao_status msao_mas_score(msao_ctx* ctx, const msao_segment* segs, int n, int R
     MSAO_TRY(validate_impl(segs, n, R, params, &ctx->err));
     Plan pl;
     pl.no_select = true;
-    build_plan(ctx, segs, n, R, params, alpha, nullptr, pl);
+    build_within(pl, SIZE_MAX, ws_bytes, [&](Plan& q) { build_plan(ctx, segs, n, R, params, alpha, nullptr, q); });
     MSAO_TRY(check_ws(ctx, pl, ws, ws_bytes));
     const bool want_frames = frm && (frm->dframe || frm->sim || frm->gamma) && pl.nframes > 0;
     if (want_frames && !(tok && tok->d))
@@ -1120,7 +1126,7 @@ msao_status msao_temporal_redundancy(msao_ctx* ctx, const msao_segment* segs, in
     MSAO_TRY(validate_impl(segs, n, R, params, &ctx->err));
     Plan pl;
     pl.no_select = true;
-    build_plan(ctx, segs, n, R, params, nullptr, nullptr, pl);
+    build_within(pl, SIZE_MAX, ws_bytes, [&](Plan& q) { build_plan(ctx, segs, n, R, params, nullptr, nullptr, q); });
     MSAO_TRY(check_ws(ctx, pl, ws, ws_bytes));
     const bool want_frames = frm && (frm->dframe || frm->sim || frm->gamma) && pl.nframes > 0;
     if (want_frames && !d) return fail(&ctx->err, MSAO_ERR_INVALID_ARG, "per-frame outputs need d");
@@ -1161,7 +1167,9 @@ msao_status msao_temporal_simhash(msao_ctx* ctx, const msao_segment* segs, int n
     MSAO_TRY(check_hashes(ctx, segs, n, hashes));
     Plan pl;
     pl.no_select = true;
-    build_plan(ctx, segs, n, R, params, nullptr, nullptr, pl, false, nullptr, false, 0, hashes);
+    build_within(pl, SIZE_MAX, ws_bytes, [&](Plan& q) {
+        build_plan(ctx, segs, n, R, params, nullptr, nullptr, q, false, nullptr, false, 0, hashes);
+    });
     MSAO_TRY(check_ws(ctx, pl, ws, ws_bytes));
     if (pl.ntok > 0 && (!sig || !d)) return fail(&ctx->err, MSAO_ERR_INVALID_ARG, "sig and d are required");
     MSAO_TRY(check_out_alignment(ctx, {{sig, 8}, {d, 4}, {temporal, 4}}));
@@ -1226,7 +1234,9 @@ msao_status msao_compact(msao_ctx* ctx, const msao_segment* segs, int n, const i
     MSAO_TRY(validate_impl(segs, n, R, &p, &ctx->err));
     Plan pl;
     pl.no_select = true;
-    build_plan(ctx, segs, n, R, &p, nullptr, out_byte_off, pl, false, nullptr, false, 0, nullptr, true);
+    build_within(pl, SIZE_MAX, ws_bytes, [&](Plan& q) {
+        build_plan(ctx, segs, n, R, &p, nullptr, out_byte_off, q, false, nullptr, false, 0, nullptr, true);
+    });
     MSAO_TRY(check_ws(ctx, pl, ws, ws_bytes));
     if (pl.ntok > 0 && (!kept_idx || !kept_count))
         return fail(&ctx->err, MSAO_ERR_INVALID_ARG, "kept_idx and kept_count are required");

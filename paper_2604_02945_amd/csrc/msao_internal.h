@@ -403,6 +403,7 @@ static_assert(kPairMaxFrames >= 1 && kPairMaxFrames <= 32, "k_pair parks two tok
 // frames rather than eight: one clip of 32 x 256 x 1,024 bf16 8.0 -> 6.5 us, 8
 // frames of 64 x 768 7.5 -> 5, larger batches keep longer ranges either way)
 constexpr int kPairMinFrames = 2;
+constexpr int kPairLeanMinFrames = 8;         // the same where the workspace has no room for more items
 constexpr int kPairTargetWaves = 1024;
 #ifndef MSAO_POST_BLOCK
 #define MSAO_POST_BLOCK 256

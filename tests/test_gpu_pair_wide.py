@@ -5,6 +5,8 @@ padded strides, specials; and the other segments of a batch in the same launch
 (up to 1,024 work items) or in one of their own. The bar of the parity tests
 against the oracle (integers bit-exact, sums within 2e-3 for bf16 and 1e-5 for
 fp32), and the chain pass (MSAO_PAIR=0) gives the same integers."""
+import re
+
 import numpy as np
 import pytest
 import torch
@@ -69,3 +71,44 @@ def test_chain_pass_gives_the_same_integers(dtype, dev, monkeypatch):
         ctx.close()
     for k in ("z", "d", "kept_idx", "keep", "kept_count", "agg", "dframe"):
         assert np.array_equal(outs[0][k], outs[1][k]), k
+
+
+@pytest.mark.parametrize("dtype,C", [("f32", 64), ("bf16", 72), ("bf16", 1032)])
+@pytest.mark.parametrize("entry", ["msao_run", "msao_mas_score", "Plan"])
+def test_workspace_with_room_for_the_chain_pass_only(entry, dtype, C, dev, monkeypatch):
+    """k_pair's short ranges are more work items than the chain pass has (300
+    against 150 here): a workspace that holds only the latter is still enough."""
+    log(f"[pair wide] workspace {entry} {dtype} {C}")
+    segs, p = clips(4, [(200, 6, C)], dtype), default_params()
+    ds = to_device(segs, dev)
+    ctxs = []
+    for flag in ("0", "1"):
+        monkeypatch.setenv("MSAO_PAIR", flag)
+        ctxs.append(B.Context(0))
+    chain, pair = ctxs
+
+    def call(o, ctx):
+        if entry == "Plan":
+            plan = msao.Plan(ds, 1, o, p, ctx=ctx)
+            plan()
+            torch.cuda.synchronize()
+            plan.close()
+        else:
+            B.prepare(entry, ds, 1, o, p, ctx=ctx)()
+            torch.cuda.synchronize()
+    o, want = msao.Outputs(ds, 1), msao.Outputs(ds, 1)
+    o.ws_bytes = 256
+    with pytest.raises(Exception, match="needed") as e:
+        call(o, chain)
+    o.ws_bytes = int(re.search(r"(\d+) needed", str(e.value)).group(1))
+    call(o, pair)
+    call(want, pair)
+    names = ["z", "d", "agg", "dframe"] + ([] if entry == "msao_mas_score" else ["keep", "kept_idx", "kept_count"])
+    got, ref = o.results(1, 1), want.results(1, 1)
+    for k in names:
+        a, b = host(got[k]), host(ref[k])
+        if k == "kept_idx":
+            a, b = a[:host(ref["kept_count"])[0]], b[:host(ref["kept_count"])[0]]
+        assert np.array_equal(a, b), k
+    for c in ctxs:
+        c.close()
