@@ -12,9 +12,17 @@
 // it exceeds m are s and t rescaled (and the arg max searched), which after
 // the first batches is rare. Lane states merge by shuffles, then across the
 // block's wavefronts through LDS.
+//
+// With a few rows (a decode step) one workgroup per row is bound by one CU's
+// latency, so a row is cut into up to 64 parts of at least one batch (16 KiB):
+// each workgroup leaves its state in a slot of device memory and the last to
+// arrive at a row merges them. Nothing waits on the device.
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+
+#include <algorithm>
+#include <mutex>
 
 #include "msao_internal.h"
 
@@ -163,16 +171,59 @@ __device__ __forceinline__ void acc_add(Acc& a, const float (&x)[N], IndexOf ind
     a.u = u;
 }
 
-template <int DT, int U>
+// The state that the row's workgroups merge to, in every lane of the last of
+// them to come here; false in the others. Called by one whole wavefront, whose
+// lane 0 holds the workgroup's state. The parts are written through to where
+// every XCD reads them, and the counters order them.
+__device__ __forceinline__ bool meet(const EntArgs& a, int row, int part, Acc& acc)
+{
+    const int lane = threadIdx.x & (kEntWave - 1);
+    EntPart* parts = a.slot->part + row * a.parts;
+    uint32_t before = 0;
+    if (lane == 0) {
+        const uint32_t w[4] = {__float_as_uint(acc.m), __float_as_uint(acc.s), __float_as_uint(acc.u), (uint32_t)acc.idx};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) __hip_atomic_store(&parts[part].w[i], w[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        before = __hip_atomic_fetch_add(&a.slot->row_count[row], 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if ((int)__shfl(before, 0) != a.parts - 1) return false;
+    acc = Acc{-INFINITY, 0.0f, 0.0f, 0x7FFFFFFF};  // empty: never the lower index
+    if (lane < a.parts) {
+        uint32_t w[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) w[i] = __hip_atomic_load(&parts[lane].w[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        acc = Acc{__uint_as_float(w[0]), __uint_as_float(w[1]), __uint_as_float(w[2]), (int)w[3]};
+    }
+#pragma unroll
+    for (int o = 1; o < kEntWave; o <<= 1) acc = acc_merge(acc, acc_shfl_xor(acc, o));
+    return true;
+}
+
+// After the row's parts are read: the counters back to zero, and the slot
+// back to the host with the last row.
+__device__ __forceinline__ void leave(const EntArgs& a, int row)
+{
+    __hip_atomic_store(&a.slot->row_count[row], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const uint32_t before = __hip_atomic_fetch_add(&a.slot->rows_done, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+    if (before != (uint32_t)a.rows - 1u) return;
+    __hip_atomic_store(&a.slot->rows_done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(a.done, a.ticket, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+template <int DT, int U, bool SPLIT>
 __global__ __launch_bounds__(kEntBlock) void k_entropy(EntArgs a)
 {
     using L = EntLane<DT>;
     constexpr int EPC = L::EPC;
     constexpr int STEP = U * kEntBlock;  // chunks per batch of the block
-    const int row = blockIdx.x;
+    const int row = SPLIT ? (int)blockIdx.x / a.parts : (int)blockIdx.x;
+    const int part = SPLIT ? (int)blockIdx.x - row * a.parts : 0;
     const int tid = threadIdx.x, lane = tid & (kEntWave - 1), wid = tid >> 6;
-    const uint8_t* base = a.logits + (int64_t)row * a.row_bytes;
-    const int nfull = a.vocab / EPC;         // whole 16-byte chunks
+    const int c_lo = SPLIT ? part * a.per : 0;           // the part's first chunk
+    const int e_lo = c_lo * EPC;                         // and element
+    const uint8_t* base = a.logits + (int64_t)row * a.row_bytes + (int64_t)c_lo * 16;
+    const int row_chunks = a.vocab / EPC;                // whole 16-byte chunks of the row
+    const int nfull = SPLIT ? min(a.per, row_chunks - c_lo) : row_chunks;  // and of the part
     const int npair = nfull / (2 * STEP) * (2 * STEP);  // chunks of whole pairs of batches
     const ent_rsrc_t rs = ent_rsrc(base, nfull * 16);
     Acc acc{-INFINITY, 0.0f, 0.0f, 0};
@@ -190,7 +241,7 @@ __global__ __launch_bounds__(kEntBlock) void k_entropy(EntArgs a)
         for (int u = 0; u < U; ++u) b[u] = ent_load(rs, (c0 + u * kEntBlock + tid) * 16);
     };
     auto reduce = [&](int c0) {
-        acc_add<U * EPC>(acc, x, [&](int j) { return (c0 + (j / EPC) * kEntBlock + tid) * EPC + j % EPC; });
+        acc_add<U * EPC>(acc, x, [&](int j) { return e_lo + (c0 + (j / EPC) * kEntBlock + tid) * EPC + j % EPC; });
     };
     // widen a set whose chunks may pass the row's last whole chunk: those read as -inf
     auto widen_masked = [&](const ent_vec4 (&b)[U], int c0) {
@@ -227,21 +278,26 @@ __global__ __launch_bounds__(kEntBlock) void k_entropy(EntArgs a)
         reduce(npair + STEP);
     }
     // the elements past the last whole chunk, one per thread
-    const int tail = a.vocab - nfull * EPC;
+    const int tail = c_lo + nfull == row_chunks ? a.vocab - row_chunks * EPC : 0;
     if (tid < tail) {
         const int i = nfull * EPC + tid;
         float x1[1] = {L::element(base, i)};
-        acc_add<1>(acc, x1, [&](int) { return i; });
+        acc_add<1>(acc, x1, [&](int) { return e_lo + i; });
     }
 #pragma unroll
     for (int o = 1; o < kEntWave; o <<= 1) acc = acc_merge(acc, acc_shfl_xor(acc, o));
-    __shared__ Acc part[kEntBlock / kEntWave];
-    if (lane == 0) part[wid] = acc;
+    __shared__ Acc wave_acc[kEntBlock / kEntWave];
+    if (lane == 0) wave_acc[wid] = acc;
     __syncthreads();
-    if (tid != 0) return;
-    Acc r = part[0];
+    if (tid >= (SPLIT ? kEntWave : 1)) return;
+    Acc r = wave_acc[0];
 #pragma unroll
-    for (int w = 1; w < kEntBlock / kEntWave; ++w) r = acc_merge(r, part[w]);
+    for (int w = 1; w < kEntBlock / kEntWave; ++w) r = acc_merge(r, wave_acc[w]);
+    if (SPLIT) {
+        if (!meet(a, row, part, r)) return;
+        if (tid != 0) return;
+        leave(a, row);
+    }
     // Eq. 9: H = -sum p ln p = ln s - t / s with p = exp(x - m) / s and t = u / L
     const float H = __logf(r.s) - (r.u * 0.6931471805599453f) / r.s;
     const float Hn = H * a.inv_log_vocab;
@@ -251,25 +307,88 @@ __global__ __launch_bounds__(kEntBlock) void k_entropy(EntArgs a)
     if (a.speculate) a.speculate[row] = Hn <= a.theta ? 1 : 0;  // Eq. 10
 }
 
+template <int DT, bool SPLIT>
+void enqueue(const EntArgs& a, hipStream_t st, void* ev0, void* ev1)
+{
+    const dim3 grid((unsigned)a.rows * (unsigned)a.parts), block(kEntBlock);
+    if (ev0 && ev1)
+        hipExtLaunchKernelGGL((k_entropy<DT, kEntUnits, SPLIT>), grid, block, 0, st, (hipEvent_t)ev0, (hipEvent_t)ev1, 0, a);
+    else
+        hipLaunchKernelGGL((k_entropy<DT, kEntUnits, SPLIT>), grid, block, 0, st, a);
+}
+
+std::mutex g_slot_mu;
+uint64_t g_slot_taken[kMaxScratchDevices] = {};
+static_assert(kEntDeviceSlots <= 64, "a bit each");
+
 }  // namespace
+
+static __device__ __align__(256) EntSlot slots[kEntDeviceSlots];  // zero when the code object is loaded
+
+int ent_slots_take(int device, int want, EntSlot** out)
+{
+    if (device < 0 || device >= kMaxScratchDevices) return 0;
+    std::lock_guard<std::mutex> lock(g_slot_mu);
+    void* p = nullptr;
+    if (hipGetSymbolAddress(&p, HIP_SYMBOL(slots)) != hipSuccess || !p) {
+        (void)hipGetLastError();
+        return 0;
+    }
+    int n = 0;
+    for (int i = 0; i < kEntDeviceSlots && n < want; ++i)
+        if (!(g_slot_taken[device] >> i & 1)) {
+            g_slot_taken[device] |= 1ull << i;
+            out[n++] = (EntSlot*)p + i;
+        }
+    return n;
+}
+
+void ent_slots_give(int device, int n, EntSlot* const* given)
+{
+    if (n <= 0) return;
+    std::lock_guard<std::mutex> lock(g_slot_mu);
+    void* p = nullptr;
+    if (hipGetSymbolAddress(&p, HIP_SYMBOL(slots)) != hipSuccess) {
+        (void)hipGetLastError();
+        return;
+    }
+    for (int i = 0; i < n; ++i)
+        if (given[i]) g_slot_taken[device] &= ~(1ull << (given[i] - (EntSlot*)p));
+}
+
+// Workgroups per row that a call of these sizes is worth. A workgroup takes 0.4
+// us a batch (fp32; 0.8 bf16) and 3 us besides; a split adds 4 us and about 0.05
+// us for every workgroup, whose release writes back an L2. So the shares are 64
+// workgroups in all, and rows that take a workgroup less than 9 us or so (16
+// batches of fp32, 12 of bf16) are not split: 65,536 fp32 logits 9.5 -> 7.4 us,
+// but 32,000 6.6 -> 7.6. Of 151,936 logits, one row of fp32 18.1 -> 7.7 us and of
+// bf16 17.6 -> 8.0, 16 rows 19.7 -> 11.4 and 19.2 -> 11.3; with up to 1,024
+// workgroups 16 rows took 16.7 and 64 rows 22.6 against 19.8.
+void ent_split(int64_t rows, int64_t vocab, int dtype, int* parts, int* per)
+{
+    const int64_t chunks = vocab / (dtype == kBF16 ? 8 : 4), batch = (int64_t)kEntUnits * kEntBlock;
+    int64_t p = 1;
+    if (rows <= kEntSplitRows && chunks >= (dtype == kBF16 ? kEntSplitBatchesBF16 : kEntSplitBatchesF32) * batch)
+        p = std::min<int64_t>(kEntSplitBlocks / rows, (chunks + batch - 1) / batch);
+    *parts = 1;
+    *per = (int)chunks;
+    if (p < 2) return;
+    const int64_t c = ((chunks + p - 1) / p + kEntWave - 1) / kEntWave * kEntWave;
+    *per = (int)c;
+    *parts = (int)((chunks + c - 1) / c);  // every part has a chunk
+}
 
 int launch_entropy(const EntArgs& a, void* stream, void* ev0, void* ev1)
 {
     if (a.rows <= 0) return kNoLaunch;
-    const dim3 grid((unsigned)a.rows), block(kEntBlock);
-    if (a.dtype == kBF16) {
-        if (ev0 && ev1)
-            hipExtLaunchKernelGGL((k_entropy<kBF16, kEntUnits>), grid, block, 0, (hipStream_t)stream, (hipEvent_t)ev0,
-                                  (hipEvent_t)ev1, 0, a);
-        else
-            hipLaunchKernelGGL((k_entropy<kBF16, kEntUnits>), grid, block, 0, (hipStream_t)stream, a);
-    } else {
-        if (ev0 && ev1)
-            hipExtLaunchKernelGGL((k_entropy<kF32, kEntUnits>), grid, block, 0, (hipStream_t)stream, (hipEvent_t)ev0,
-                                  (hipEvent_t)ev1, 0, a);
-        else
-            hipLaunchKernelGGL((k_entropy<kF32, kEntUnits>), grid, block, 0, (hipStream_t)stream, a);
-    }
+    const hipStream_t st = (hipStream_t)stream;
+    if (a.parts < 1 || (a.parts > 1 && (!a.slot || !a.done || a.rows > kEntSplitRows ||
+                                        (int64_t)a.rows * a.parts > kEntSplitBlocks)))
+        return (int)hipErrorInvalidValue;
+    if (a.dtype == kBF16)
+        a.parts > 1 ? enqueue<kBF16, true>(a, st, ev0, ev1) : enqueue<kBF16, false>(a, st, ev0, ev1);
+    else
+        a.parts > 1 ? enqueue<kF32, true>(a, st, ev0, ev1) : enqueue<kF32, false>(a, st, ev0, ev1);
     return (int)hipGetLastError();
 }
 

@@ -38,6 +38,12 @@ struct msao_ctx {
     uint32_t stage_ticket[kStageSlots] = {};
     int stage_blocks[kStageSlots] = {};
     int next_slot = 0;
+    // slots in which the workgroups of a split row of logits meet. A call takes
+    // one whose last user has set ent_done[slot] to ent_ticket[slot]
+    EntSlot* ent_slot[kEntSlots] = {};
+    uint32_t* ent_done = nullptr;     // pinned, behind stage_done
+    uint32_t ent_ticket[kEntSlots] = {};
+    int n_ent = 0, next_ent = 0;
     // profiling: an event pair around every launch, averaged per kernel on query
     bool profiling = false;
     std::vector<hipEvent_t> pool;                       // free events
@@ -992,13 +998,14 @@ msao_status msao_create(msao_ctx** out, int device)
     msao_ctx* c = new msao_ctx();
     c->device = device;
     DeviceGuard guard(device);
-    if ((e = hipHostMalloc((void**)&c->stage_done, sizeof(uint32_t) * kStageSlots * kUploadMaxBlocks,
+    if ((e = hipHostMalloc((void**)&c->stage_done, sizeof(uint32_t) * (kStageSlots * kUploadMaxBlocks + kEntSlots),
                            hipHostMallocDefault)) != hipSuccess) {
         g_err = std::string("hipHostMalloc: ") + hipGetErrorString(e);
         msao_destroy(c);
         return MSAO_ERR_HIP;
     }
-    std::memset(c->stage_done, 0, sizeof(uint32_t) * kStageSlots * kUploadMaxBlocks);
+    std::memset(c->stage_done, 0, sizeof(uint32_t) * (kStageSlots * kUploadMaxBlocks + kEntSlots));
+    c->ent_done = c->stage_done + kStageSlots * kUploadMaxBlocks;
     // set-up of msao_run_noalloc, which allocates nothing: the staging slots
     // hold its largest tables, and this device's copy of the library's
     // scratch array has its device address looked up
@@ -1020,6 +1027,7 @@ msao_status msao_create(msao_ctx** out, int device)
     if (const char* v = std::getenv("MSAO_CLIP_FUSE")) c->clip_fuse = std::atoi(v) ? 1 : 0;
     if (const char* v = std::getenv("MSAO_PAIR")) c->pair_path = std::atoi(v) ? 1 : 0;
     if (const char* v = std::getenv("MSAO_POST_BIG_SEGMENT")) c->post_big_segment = std::max(1, std::atoi(v));
+    c->n_ent = ent_slots_take(device, kEntSlots, c->ent_slot);
     *out = c;
     return MSAO_OK;
 }
@@ -1032,6 +1040,10 @@ void msao_destroy(msao_ctx* ctx)
         wait_stage(ctx, i);
         if (ctx->stage[i]) (void)hipHostFree(ctx->stage[i]);
     }
+    for (int i = 0; i < ctx->n_ent; ++i)
+        for (int spin = 0; ctx->ent_slot[i] && __atomic_load_n(&ctx->ent_done[i], __ATOMIC_ACQUIRE) != ctx->ent_ticket[i]; ++spin)
+            if (spin >= 4096) std::this_thread::yield();
+    ent_slots_give(ctx->device, ctx->n_ent, ctx->ent_slot);
     if (ctx->stage_done) (void)hipHostFree(ctx->stage_done);
     for (int k = 0; k < MSAO_NUM_KERNELS; ++k)
         for (auto& pr : ctx->rec[k]) {
@@ -1415,7 +1427,31 @@ msao_status msao_draft_entropy(msao_ctx* ctx, const void* logits, int64_t rows, 
     a.entropy_norm = out->entropy_norm;
     a.draft_token = out->draft_token;
     a.speculate = out->speculate;
-    return launched(ctx, MSAO_KERNEL_ENTROPY, (hipStream_t)stream, run_entropy, &a);
+    // few rows are split over workgroups that meet in a slot that no call uses;
+    // a graph, whose replays come whenever they like, holds none
+    ent_split(rows, vocab, dtype, &a.parts, &a.per);
+    int slot = -1;
+    if (a.parts > 1) {
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing((hipStream_t)stream, &cap) != hipSuccess) {
+            (void)hipGetLastError();
+            cap = hipStreamCaptureStatusActive;
+        }
+        for (int q = 0; q < ctx->n_ent && slot < 0 && cap == hipStreamCaptureStatusNone; ++q) {
+            const int i = (ctx->next_ent + q) % ctx->n_ent;
+            if (__atomic_load_n(&ctx->ent_done[i], __ATOMIC_ACQUIRE) == ctx->ent_ticket[i] && ctx->ent_slot[i]) slot = i;
+        }
+        if (slot < 0) a.parts = 1;
+    }
+    if (slot < 0) return launched(ctx, MSAO_KERNEL_ENTROPY, (hipStream_t)stream, run_entropy, &a);
+    a.slot = ctx->ent_slot[slot];
+    a.done = ctx->ent_done + slot;
+    a.ticket = ctx->ent_ticket[slot] + 1;
+    ctx->next_ent = (slot + 1) % ctx->n_ent;
+    const msao_status rc = launched(ctx, MSAO_KERNEL_ENTROPY, (hipStream_t)stream, run_entropy, &a);
+    if (rc == MSAO_OK) ctx->ent_ticket[slot] = a.ticket;
+    else ctx->ent_slot[slot] = nullptr;  // not known to be free: never used again
+    return rc;
 }
 
 }  // extern "C"

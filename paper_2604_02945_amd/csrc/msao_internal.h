@@ -343,8 +343,32 @@ struct ScoreInline {
 static_assert(sizeof(ScoreInline) <= 4096, "a launch takes 4 KiB of arguments");
 int launch_score_inline(const ScoreInline& u, void* stream, void* ev0, void* ev1);
 
-// Draft-model confidence (msao_entropy.hip): one row of logits per workgroup.
+// Draft-model confidence (msao_entropy.hip): one row of logits per workgroup,
+// or, for few rows, one row over the `parts` workgroups that meet in a slot.
+constexpr int kEntSplitRows = 16;                     // most rows of a split call
+constexpr int kEntSplitBlocks = 64;                   // most workgroups of one (one wavefront merges those of a row)
+constexpr int kEntSplitBatchesF32 = 16;               // fewest batches of loads of its rows
+constexpr int kEntSplitBatchesBF16 = 12;
+constexpr int kEntSlots = 4;                          // slots a context holds
+constexpr int kEntDeviceSlots = 64;                   // slots of a device
+struct EntPart {
+    uint32_t w[4];           // the bits of m, s, u and the index
+};
+struct EntSlot {
+    EntPart part[kEntSplitBlocks];
+    uint32_t row_count[kEntSplitRows];  // workgroups of the row that have written their part
+    uint32_t rows_done;                 // rows whose result is written
+    uint32_t pad_[47];
+};
+// Claims up to `want` slots of `device` (which is current; their counters are
+// zero) and returns how many; gives slots back. Neither fails otherwise.
+int ent_slots_take(int device, int want, EntSlot** out);
+void ent_slots_give(int device, int n, EntSlot* const* slots);
 struct EntArgs {
+    EntSlot* slot;           // split call: its slot, and the pinned word set to ticket when it is free again
+    uint32_t* done;
+    uint32_t ticket;
+    int32_t parts, per;      // workgroups per row (1: no slot); whole 16-byte chunks of each
     const uint8_t* logits;   // row r starts at logits + r * row_bytes
     int64_t row_bytes;
     int32_t rows, vocab, dtype;
@@ -363,6 +387,7 @@ struct EntArgs {
 #endif
 constexpr int kEntBlock = MSAO_ENT_BLOCK;  // threads per row of logits
 constexpr int kEntUnits = MSAO_ENT_UNITS;  // 16-byte chunks per thread per batch
+void ent_split(int64_t rows, int64_t vocab, int dtype, int* parts, int* per);
 int launch_entropy(const EntArgs& a, void* stream, void* ev0, void* ev1);
 
 // Launchers (msao_kernels.hip). Return the HIP error code of the launch, or

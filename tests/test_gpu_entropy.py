@@ -161,3 +161,87 @@ def test_entropy_feeds_algorithm_1(dev):
     p = s.params
     odec, oth, _ = oracle.sched_run(hn[200:].astype(np.float64), theta0, nd, p.delta, p.theta_min, p.alpha)
     assert np.array_equal(dec, odec) and np.array_equal(th, oth)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("rows,batches,extra", [
+    (1, 1, 1), (1, 12, -1), (2, 12, 0), (1, 16, -1), (1, 16, 0), (1, 16, 1), (2, 31, -3), (1, 64, 5), (3, 64, 64), (1, 130, 7), (15, 17, 3),
+    (16, 16, 7), (17, 16, 1)])
+def test_rows_split_over_workgroups(rows, batches, extra, dtype, dev):
+    """Vocabularies around whole batches of a workgroup's loads (4,096 float32
+    or 8,192 bf16 logits), from too few to be split
+    to many, for one row up to past the most rows that are split."""
+    vocab = batches * (4096 if dtype == "f32" else 8192) + extra
+    log(f"[entropy split] {rows} x {vocab} {dtype}")
+    stride = -(-vocab // 8) * 8
+    x = draft_logits(min(rows, 20), stride, seed=rows + batches, dtype=dtype)
+    x = np.tile(x, (-(-rows // len(x)), 1))[:rows]
+    check(x, dtype, vocab, dev, rows_to_check=np.unique([0, rows // 2, rows - 1, min(rows - 1, 19)]))
+
+
+def test_split_rows_special_values(dev):
+    """A row of -inf, one finite logit in every part of a row in turn, equal
+    maxima in several parts (the first counts) and NaN in the last part."""
+    V = 20 * 4096 + 3  # 4 parts for each of 16 rows
+    log("[entropy split] special")
+    x = np.full((16, V + 1), -np.inf, np.float32)
+    for r in range(1, 8):
+        x[r, min(V - 1, (r - 1) * 16384 + 17)] = 2.0
+    x[8, [5000, 45000, V - 1]] = 1.0
+    x[9:] = 0.0
+    x[10, V - 1] = np.nan
+    x[11, [4096, 30000, 70000]] = 3.0
+    t = torch.from_numpy(x).to(dev)
+    out = msao.msao_draft_entropy(t, 0.3, vocab=V)
+    torch.cuda.synchronize()
+    tok, H = out["draft_token"].cpu().numpy(), out["entropy"].cpu().numpy()
+    # each row alone beside 256 others takes the path of one workgroup per row
+    whole = msao.msao_draft_entropy(t.repeat(17, 1), 0.3, vocab=V)
+    torch.cuda.synchronize()
+    assert np.array_equal(tok, whole["draft_token"].cpu().numpy()[:16])
+    np.testing.assert_allclose(H, whole["entropy"].cpu().numpy()[:16], rtol=0, atol=H_TOL)
+    assert tok[8] == 5000 and tok[11] == 4096 and np.isnan(H[10])
+
+
+def test_split_rows_in_flight_and_in_a_graph(dev):
+    """More split calls in flight than a context has slots, on two streams; then
+    one recorded into a graph; every result is the same call's made alone."""
+    log("[entropy split] in flight")
+    ctx = B.Context(0)
+    xs = [torch.from_numpy(draft_logits(1 + i % 3, 151936, seed=i, dtype="f32")).to(dev) for i in range(12)]
+
+    def buffers(rows):
+        return {"entropy": torch.zeros(rows, device=dev), "entropy_norm": torch.zeros(rows, device=dev),
+                "draft_token": torch.zeros(rows, dtype=torch.int32, device=dev),
+                "speculate": torch.zeros(rows, dtype=torch.uint8, device=dev)}
+    want, got = [], [buffers(len(x)) for x in xs]
+    for x in xs:
+        want.append(msao.msao_draft_entropy(x, 0.3, ctx=ctx))
+        torch.cuda.synchronize()
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    a = torch.randn(4096, 4096, device=dev)
+    torch.cuda.synchronize()
+    for s in streams:
+        with torch.cuda.stream(s):
+            for _ in range(10):
+                a @ a
+    for i, x in enumerate(xs):
+        msao.msao_draft_entropy(x, 0.3, ctx=ctx, stream=streams[i % 2], outputs=got[i])
+    torch.cuda.synchronize()
+
+    def same(g, w):
+        assert np.array_equal(g["draft_token"].cpu().numpy(), w["draft_token"].cpu().numpy())
+        np.testing.assert_allclose(g["entropy"].cpu().numpy(), w["entropy"].cpu().numpy(), rtol=0, atol=H_TOL)
+    for g, w in zip(got, want):
+        same(g, w)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        msao.msao_draft_entropy(xs[0], 0.3, ctx=ctx, outputs=got[0])
+    for _ in range(3):
+        got[0]["entropy"].zero_()
+        graph.replay()
+        msao.msao_draft_entropy(xs[1], 0.3, ctx=ctx, outputs=got[1])
+        torch.cuda.synchronize()
+        same(got[0], want[0])
+        same(got[1], want[1])
+    ctx.close()
