@@ -626,16 +626,31 @@ void wait_stage(msao_ctx* ctx, int slot)
 // error instead of a new pinned allocation (msao_run_noalloc allocates nothing).
 // With `in_score` and tables of at most kUploadInline bytes nothing is
 // enqueued: the arguments and the tables are put there for the scoring launch
-// to bring along, and *deferred says so.
+// to bring along, and *deferred says so. On a stream that is being captured
+// larger tables go in pieces, each in its launch's arguments, and take no slot.
 msao_status upload(msao_ctx* ctx, const Plan& pl, int n, void* ws, hipStream_t stream, bool grow = true,
                    ScoreInline* in_score = nullptr, bool* deferred = nullptr)
 {
-    // small tables go into the launch itself, larger ones through a slot
     const bool small = pl.copy_bytes <= kUploadInline;
+    bool captured = false;
+    if (!small) {
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(stream, &cap) != hipSuccess) {
+            (void)hipGetLastError();
+            cap = hipStreamCaptureStatusActive;  // not known: the way that is right for either
+        }
+        captured = cap != hipStreamCaptureStatusNone;
+    }
+    const bool slotted = !small && !captured;
     alignas(16) uint8_t small_tables[kUploadInline];
+    std::vector<uint8_t> captured_tables;
     const int slot = ctx->next_slot;
     uint8_t* h = small_tables;
-    if (!small) {
+    if (captured) {
+        captured_tables.resize(pl.copy_bytes);
+        h = captured_tables.data();
+    }
+    if (slotted) {
         if (!grow && ctx->stage_cap[slot] < pl.copy_bytes)
             return fail(&ctx->err, MSAO_ERR_UNSUPPORTED, "per-call tables larger than the context's reserved staging");
         ctx->next_slot = (slot + 1) % kStageSlots;
@@ -670,14 +685,7 @@ msao_status upload(msao_ctx* ctx, const Plan& pl, int n, void* ws, hipStream_t s
     a.frame_seg = (int32_t*)(b + pl.off_frseg);
     a.cl_seg = (int32_t*)(b + pl.off_clseg);
     a.hi_seg = (int32_t*)(b + pl.off_hiseg);
-    bool tracked = false;
-    if (!small) {
-        // a graph's replays read the slot again, whenever they come: no word from them
-        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-        if (hipStreamIsCapturing(stream, &cap) != hipSuccess) (void)hipGetLastError();
-        tracked = cap == hipStreamCaptureStatusNone;
-    }
-    if (tracked) {
+    if (slotted) {
         a.done = ctx->stage_done + slot * kUploadMaxBlocks;
         a.ticket = ++ctx->stage_ticket[slot];
     }
@@ -689,9 +697,9 @@ msao_status upload(msao_ctx* ctx, const Plan& pl, int n, void* ws, hipStream_t s
     }
     const int64_t units = a.copy_units + (int64_t)n * a.fill_parts;
     const int blocks = (int)std::min<int64_t>(units, kUploadMaxBlocks);
-    const int rc = launch_upload(a, blocks, stream);
+    const int rc = captured ? launch_upload_pieces(a, blocks, stream) : launch_upload(a, blocks, stream);
     if (rc != 0) return hip_fail(ctx, (hipError_t)rc, "table upload");
-    if (tracked) ctx->stage_blocks[slot] = blocks;
+    if (slotted) ctx->stage_blocks[slot] = blocks;
     return MSAO_OK;
 }
 

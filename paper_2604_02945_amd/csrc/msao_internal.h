@@ -310,8 +310,8 @@ struct GatherArgs {
 // (msao_upload.hip). copy_bytes lead the tables and are staged; the arrays
 // that name the segment of each item are written from the segment records.
 struct UploadArgs {
-    const uint8_t* src;      // the staged tables (the segment records first): a pinned slot, or
-                             // any host memory for copy_bytes <= kUploadInline
+    const uint8_t* src;      // the staged tables (the segment records first): a pinned slot, or any
+                             // host memory for copy_bytes <= kUploadInline and for pieces
     uint8_t* dst;            // workspace
     uint32_t copy_bytes;     // a multiple of 16
     int32_t n;               // segments
@@ -331,6 +331,20 @@ struct UploadInline {
     alignas(16) uint8_t tables[kUploadInline];
 };
 int launch_upload(const UploadArgs& a, int blocks, void* stream);
+
+// A piece of larger tables in a launch's arguments, for a call that is being
+// recorded into a graph: the graph holds its own copy of everything that its
+// replays read.
+constexpr uint32_t kUploadPiece = 3840;
+struct UploadPiece {
+    uint8_t* dst;            // workspace
+    uint32_t bytes;          // a multiple of 16
+    alignas(16) uint8_t tables[kUploadPiece];
+};
+static_assert(sizeof(UploadPiece) <= 4096, "a launch takes 4 KiB of arguments");
+// The tables of `a` (staged in any host memory) in pieces, then the arrays of
+// item segments from the segment records in the workspace.
+int launch_upload_pieces(const UploadArgs& a, int blocks, void* stream);
 
 // A scoring launch that brings its call's small tables along: its blocks read
 // the segment records from the arguments and write the tables for the

@@ -14,7 +14,9 @@
 //
 // Each block that has read the staging slot says so with its own word in
 // host memory, so that the host can reuse the slot without an event on the
-// stream (which is a barrier packet of its own).
+// stream (which is a barrier packet of its own). A call that is being recorded
+// into a graph takes no slot: the graph's replays come whenever they like, and
+// would find other tables there.
 #include <hip/hip_runtime.h>
 #include <stddef.h>
 #include <stdint.h>
@@ -48,6 +50,14 @@ __global__ __launch_bounds__(kUploadBlock) void k_upload_inline(UploadInline u)
     upload_tables(u.a, (const uint8_t*)(kernel_args() + offsetof(UploadInline, tables)));
 }
 
+// One block per piece: 3,840 bytes are 240 threads' 16 bytes.
+__global__ __launch_bounds__(kUploadBlock) void k_upload_piece(UploadPiece u)
+{
+    static_assert(kUploadPiece <= 16 * kUploadBlock, "one 16-byte chunk a thread");
+    const uvec4* src = (const uvec4*)(const uint8_t*)(kernel_args() + offsetof(UploadPiece, tables));
+    if (threadIdx.x * 16u < u.bytes) ((uvec4*)u.dst)[threadIdx.x] = src[threadIdx.x];
+}
+
 }  // namespace
 
 int launch_upload(const UploadArgs& a, int blocks, void* stream)
@@ -61,6 +71,26 @@ int launch_upload(const UploadArgs& a, int blocks, void* stream)
         return (int)hipGetLastError();
     }
     hipLaunchKernelGGL(k_upload, dim3((unsigned)blocks), dim3(kUploadBlock), 0, (hipStream_t)stream, a);
+    return (int)hipGetLastError();
+}
+
+int launch_upload_pieces(const UploadArgs& a, int blocks, void* stream)
+{
+    if (blocks < 1 || blocks > kUploadMaxBlocks || a.copy_bytes % 16 != 0 || !a.src || !a.dst) return (int)hipErrorInvalidValue;
+    for (uint32_t at = 0; at < a.copy_bytes; at += kUploadPiece) {
+        UploadPiece u;
+        u.dst = a.dst + at;
+        u.bytes = a.copy_bytes - at < kUploadPiece ? a.copy_bytes - at : kUploadPiece;
+        memcpy(u.tables, a.src + at, u.bytes);
+        hipLaunchKernelGGL(k_upload_piece, dim3(1), dim3(kUploadBlock), 0, (hipStream_t)stream, u);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return (int)e;
+    }
+    UploadArgs fill = a;  // the segment records now lead the workspace
+    fill.src = a.dst;
+    fill.copy_units = 0;
+    fill.done = nullptr;
+    hipLaunchKernelGGL(k_upload, dim3((unsigned)blocks), dim3(kUploadBlock), 0, (hipStream_t)stream, fill);
     return (int)hipGetLastError();
 }
 

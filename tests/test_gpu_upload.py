@@ -1,9 +1,10 @@
 """Table upload of the entry points that build their tables per call: staging
 slots used again while earlier uploads wait on the GPU, tables of one, several
 and many copy units, runs of one segment longer than a fill stripe, calls on
-two streams, and a call recorded into a HIP graph. The same kernels run on the
-same inputs either way, so every output equals the same call made alone, bit
-for bit (and one of them the oracle's)."""
+two streams, and calls recorded into a HIP graph, whose replays come after
+other calls with other tables. The same kernels run on the same inputs either
+way, so every output equals the same call made alone, bit for bit (and one of
+them the oracle's)."""
 import numpy as np
 import pytest
 import torch
@@ -94,7 +95,7 @@ def test_uploads_waiting_on_the_gpu(entry, dev):
 
 @pytest.mark.parametrize("which", [0, 3])
 def test_call_recorded_into_a_graph(which, dev):
-    """Tables in the launch's arguments (table 0), and in a staging slot."""
+    """Tables in the scoring launch's arguments (table 0), and in pieces."""
     print("[upload] graph", flush=True)
     ctx = msao.Context(0)
     segs, R = table(which)
@@ -124,6 +125,91 @@ def test_call_recorded_into_a_graph(which, dev):
     torch.cuda.synchronize()
     got = snapshot(o, R, len(ds), ds)
     assert all(np.array_equal(got[k].view(np.uint8), v.view(np.uint8)) for k, v in want.items())
+    ctx.close()
+
+
+def prepared(i, entry, dev, ctx, p):
+    """Table i (i % 4 of 2 or 3: more than 3 KiB of tables) with its calls, outputs and the outputs of the calls made alone."""
+    segs, R = table(i)
+    ds = to_device(segs, dev)
+    o, alone = msao.Outputs(ds, R), msao.Outputs(ds, R)
+
+    def calls(out):
+        if entry == "stages":
+            return [B.prepare("msao_mas_score", ds, R, out, p, ctx=ctx),
+                    B.prepare("msao_select_tokens", ds, R, out, p, ctx=ctx, mas=out.req["mas"]),
+                    B.prepare("msao_compact", ds, R, out, ctx=ctx)]
+        return [B.prepare("msao_run", ds, R, out, p, ctx=ctx)]
+    for c in calls(alone):
+        c()
+    torch.cuda.synchronize()
+    return ds, R, o, calls(o), snapshot(alone, R, len(ds), ds)
+
+
+def cleared(*outs):
+    for o in outs:
+        for group in (o.tok, o.frm, o.req, o.sel):
+            for t in group.values():
+                t.fill_(0)
+        o.out.zero_()
+        if o.workspace is not None:
+            o.workspace.fill_(0)
+    torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("entry", ["msao_run", "stages"])
+def test_many_calls_in_one_graph(entry, dev):
+    """More calls with large tables in one graph than the context has staging
+    slots (four), each with tables of its own, and replays after eager calls
+    that use every slot."""
+    print(f"[upload] many calls in a graph, {entry}", flush=True)
+    ctx, p = msao.Context(0), default_params()
+    inside = [prepared(i, entry, dev, ctx, p) for i in (2, 3, 6, 7, 10, 11, 14)]
+    between = [prepared(i, "msao_run", dev, ctx, p) for i in (15, 18, 19, 22, 23)]
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        for _, _, _, cs, _ in inside:
+            for c in cs:
+                c(torch.cuda.current_stream())
+    for rep in range(3):
+        cleared(*[x[2] for x in inside + between])
+        for _, _, _, cs, _ in between:
+            cs[0]()
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        for i, (ds, R, o, _, want) in enumerate(inside + between):
+            got = snapshot(o, R, len(ds), ds)
+            for k, v in want.items():
+                assert np.array_equal(got[k].view(np.uint8), v.view(np.uint8)), f"replay {rep}, call {i}: {k}"
+    ctx.close()
+
+
+def test_noalloc_call_in_a_graph_after_other_calls(dev):
+    """A recorded msao_run_noalloc is replayed after more calls with other
+    large tables than there are staging slots."""
+    print("[upload] noalloc in a graph", flush=True)
+    ctx, p = msao.Context(0), default_params()
+    segs, R = table(3)
+    ds = to_device(segs, dev)
+    o = msao.Outputs(ds, R, workspace=False)
+    call = B.prepare("msao_run_noalloc", ds, R, o, p, ctx=ctx)
+    call()
+    torch.cuda.synchronize()
+    want = snapshot(o, R, len(ds), ds)
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        call(torch.cuda.current_stream())
+    others = [prepared(i, "msao_run", dev, ctx, p) for i in (6, 7, 10, 11, 14, 15, 18, 19)]
+    for rep in range(3):
+        cleared(o)
+        for _, _, _, cs, _ in others:
+            cs[0]()
+        g.replay()
+        torch.cuda.synchronize()
+        got = snapshot(o, R, len(ds), ds)
+        for k, v in want.items():
+            assert np.array_equal(got[k].view(np.uint8), v.view(np.uint8)), f"replay {rep}: {k}"
     ctx.close()
 
 
