@@ -168,9 +168,8 @@ typedef struct {
  * -1 automatic, 0 dispatch order, 1 one range per XCD), MSAO_CLIP_FUSE (1:
  * the run with SimHash scores and hashes its clips in one pass), MSAO_PAIR
  * (1: clips with rows of at most 4 KiB take the paired pass) and
- * MSAO_POST_BIG_SEGMENT (selections of at least this many tokens take
- * 1,024-thread blocks, 4096: lower latency per batch; a larger value favours
- * throughput with several batches in flight). */
+ * MSAO_POST_BIG_SEGMENT (a launch with a selection of at least this many
+ * tokens takes 1,024-thread blocks, 4096; one of more than 4,096 always does). */
 msao_status msao_create(msao_ctx** ctx, int device);
 /* Destroy a context (NULL is ignored). Waits for the context's pending uploads. */
 void msao_destroy(msao_ctx* ctx);

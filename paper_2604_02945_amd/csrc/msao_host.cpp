@@ -149,10 +149,10 @@ struct Plan {
     std::vector<float> alpha;
     int64_t ntok = 0, nframes = 0;
     int n_wi = 0, n_gwi = 0;
-    int max_n = 0;                 // largest selection (LDS key staging)
-    int big_seg = kPostBigSegment; // selections this large take 1024-thread blocks
-    std::vector<SelUnit> sel_unit; // selection blocks: a segment, or a frame (per-frame scope), or a part of one
-    int n_big_blk = 0;             // the first of them: chunks of large selections
+    std::vector<SelUnit> sel_unit; // selections: a segment, or a frame (per-frame scope); those over kSelRegTokens in parts
+    int n_listed = 0, n_big_blk = 0; // the first of them: parts of those; and of these the first: chunks of large selections
+    int sel_parts = 1;             // blocks for each of the others
+    bool big_block = false;        // the selections take 1,024-thread blocks
     size_t off_big = 0;            // what their passes hand on
     bool lean = false;             // no room for that, nor for k_pair's short ranges and wide rows
     bool no_select = false;        // a call without a selection: no records
@@ -244,10 +244,8 @@ void build_plan(const msao_ctx* ctx, const msao_segment* segs, int n, int R, con
                 bool select_imp = false)
 {
     const bool per_frame = (p->flags & MSAO_FLAG_SELECT_PER_FRAME) != 0;
-    pl.big_seg = ctx ? ctx->post_big_segment : kPostBigSegment;
     pl.sel_unit.clear();
     pl.n_hi = 0;
-    pl.max_n = 0;
     pl.learned = learned;
     pl.mlp_hidden = learned ? mlp_hidden : 0;
     pl.n_hb = 0;
@@ -284,7 +282,20 @@ void build_plan(const msao_ctx* ctx, const msao_segment* segs, int n, int R, con
             chains_total += segs[i].tokens_per_frame;
             pairs_total += (segs[i].tokens_per_frame + 1) / 2;
         }
-    std::vector<SelUnit> big_units;  // chunks of large selections, ahead of the others
+    // the sizes of the selections, for the blocks that they take
+    int64_t n_sels = 0;
+    int max_n = 0, max_reg_n = 0;
+    for (int i = 0; i < n; ++i) {
+        const bool framed = per_frame && segs[i].n_frames >= 2 && segs[i].tokens_per_frame > 0;
+        const int n_u = framed ? segs[i].tokens_per_frame : segs[i].n_frames * segs[i].tokens_per_frame;
+        n_sels += framed ? segs[i].n_frames : 1;
+        max_n = std::max(max_n, n_u);
+        if (n_u <= kSelRegTokens) max_reg_n = std::max(max_reg_n, n_u);
+    }
+    pl.big_block = max_n >= (ctx ? ctx->post_big_segment : kPostBigSegment) || max_n > kSelSmallTokens;
+    const int round = 4 * (pl.big_block ? kPostBigBlock : kPostBlock);
+    pl.sel_parts = n_sels < kSelSplitMax ? std::max(1, (max_reg_n + round - 1) / round) : 1;
+    std::vector<SelUnit> big_units, mem_units;  // parts of large selections, ahead of the others
     size_t big_bytes = 0;
     for (int i = 0; i < n; ++i) {
         const msao_segment& s = segs[i];
@@ -355,7 +366,7 @@ void build_plan(const msao_ctx* ctx, const msao_segment* segs, int n, int R, con
                 u.big = (uint32_t)(1 + big_bytes / 16);
                 big_bytes += big_area_bytes(n_u);
             }
-            std::vector<SelUnit>& to = big ? big_units : pl.sel_unit;
+            std::vector<SelUnit>& to = big ? big_units : n_u > kSelRegTokens ? mem_units : pl.sel_unit;
             for (int q = 0; q < u.nparts; ++q) {
                 u.part = q;
                 to.push_back(u);
@@ -365,12 +376,10 @@ void build_plan(const msao_ctx* ctx, const msao_segment* segs, int n, int R, con
             d.kf = s.keep_ratio < 0.0f ? -1 : (int32_t)keep_count(s.keep_ratio, s.tokens_per_frame);
             d.k = d.kf < 0 ? -1 : d.kf * s.n_frames;
             for (int f = 0; f < s.n_frames; ++f) push_selection(f, s.tokens_per_frame, d.kf);
-            pl.max_n = std::max(pl.max_n, s.tokens_per_frame);
         } else {
             d.kf = -1;
             d.k = s.keep_ratio < 0.0f ? -1 : (int32_t)keep_count(s.keep_ratio, N);
             push_selection(-1, (int)N, d.k);
-            pl.max_n = std::max(pl.max_n, (int)N);
         }
         d.cap = d.k < 0 ? (int32_t)N : d.k;
         // a compaction that does not know the selection's scope (msao_compact)
@@ -510,6 +519,8 @@ void build_plan(const msao_ctx* ctx, const msao_segment* segs, int n, int R, con
         pl.n_cl += (items + kClipWaves - 1) / kClipWaves;
     }
     pl.n_big_blk = (int)big_units.size();
+    big_units.insert(big_units.end(), mem_units.begin(), mem_units.end());
+    pl.n_listed = (int)big_units.size();
     pl.sel_unit.insert(pl.sel_unit.begin(), big_units.begin(), big_units.end());
     pl.ntok = tok;
     pl.nframes = frame;
@@ -854,6 +865,17 @@ int32_t xcd_order_for(const msao_ctx* ctx, bool copies_rows)
 {
     if (ctx->xcd_order >= 0) return ctx->xcd_order ? 1 : 0;
     return copies_rows ? 0 : 1;
+}
+
+// The selections of a post-scoring launch.
+void put_selections(PostArgs& a, const Plan& pl, void* ws)
+{
+    a.n_sel_listed = pl.n_listed;
+    a.sel_parts = pl.sel_parts;
+    a.n_sel_blocks = pl.n_listed + ((int)pl.sel_unit.size() - pl.n_listed) * pl.sel_parts;
+    a.n_big_blocks = pl.n_big_blk;
+    a.big = pl.n_big_blk > 0 ? (uint8_t*)ws + pl.off_big : nullptr;
+    a.big_block = pl.big_block ? 1 : 0;
 }
 
 TokenOut token_out(const msao_token_out* t)
@@ -1236,10 +1258,7 @@ msao_status msao_select_tokens(msao_ctx* ctx, const msao_segment* segs, int n, i
     pa.z = z;
     pa.d = d;
     pa.mas_in = mas;
-    pa.n_sel_blocks = (int)pl.sel_unit.size();
-    pa.n_big_blocks = pl.n_big_blk;
-    pa.big = pl.n_big_blk > 0 ? (uint8_t*)ws + pl.off_big : nullptr;
-    pa.big_block = pl.max_n >= pl.big_seg || pl.max_n > kSelSmallTokens ? 1 : 0;
+    put_selections(pa, pl, ws);
     return launched(ctx, MSAO_KERNEL_POST, st, run_post, &pa);
 }
 
@@ -1545,11 +1564,8 @@ msao_status enqueue_run(msao_ctx* ctx, const Plan& pl, const Tables& t, const ms
     const bool want_frames = frm && (frm->dframe || frm->sim || frm->gamma) && pl.nframes > 0;
     pa.n_req_blocks = want_req ? t.R : 0;
     pa.n_frame_blocks = want_frames ? (int)pl.nframes : 0;
-    pa.n_sel_blocks = (int)pl.sel_unit.size();
-    pa.n_big_blocks = pl.n_big_blk;
     // (the workspace begins off_seg before the segment records)
-    pa.big = pl.n_big_blk > 0 ? (uint8_t*)t.seg - pl.off_seg + pl.off_big : nullptr;
-    pa.big_block = pl.max_n >= pl.big_seg || pl.max_n > kSelSmallTokens ? 1 : 0;
+    put_selections(pa, pl, (uint8_t*)t.seg - pl.off_seg);
     MSAO_TRY(launched(ctx, MSAO_KERNEL_POST, st, run_post, &pa));
     if (!out || t.n_gwi == 0) return MSAO_OK;
     GatherArgs ga;
@@ -1738,10 +1754,7 @@ msao_status msao_run_learned(msao_ctx* ctx, const msao_segment* segs, int n, int
     ps.z = tok ? tok->z : nullptr;
     ps.d = tok ? tok->d : nullptr;
     ps.mas_in = mas_ws;
-    ps.n_sel_blocks = (int)pl.sel_unit.size();
-    ps.n_big_blocks = pl.n_big_blk;
-    ps.big = pl.n_big_blk > 0 ? (uint8_t*)ws + pl.off_big : nullptr;
-    ps.big_block = pl.max_n >= pl.big_seg || pl.max_n > kSelSmallTokens ? 1 : 0;
+    put_selections(ps, pl, ws);
     MSAO_TRY(launched(ctx, MSAO_KERNEL_POST, st, run_post, &ps));
     if (!out || t.n_gwi == 0) return MSAO_OK;
     GatherArgs ga;

@@ -1218,6 +1218,7 @@ struct PostShared {
     static_assert(kRadixBins % NT == 0, "every thread owns the same number of radix bins");
     alignas(16) uint32_t hist[kRadixBins];  // read 16 bytes at a time by the digit scan
     uint32_t scan[kWaves];
+    uint32_t tot[kWave];      // selection: counts of each round of quads and wavefront
     uint32_t wcnt[kWaves][4];
     unsigned long long lo, hi, red;
     uint64_t vsel;            // selection: key of the wanted rank among few candidates
@@ -1646,7 +1647,24 @@ struct TokenKeys {
         return Ms * (uint64_t)z + (d ? Mt * (uint64_t)(E - dd) : 0ull);
     }
     __device__ __forceinline__ uint64_t at(int i) const { return of(first ? first[i] : 0u, d ? d[i] : 0u); }
+    // the same for every kind but kKeyFull, whose keys alone need more than 32 bits
+    __device__ __forceinline__ uint32_t of32(uint32_t z, uint32_t dd) const
+    {
+        if (kind == kKeyImp) return imp_key(__uint_as_float(z));
+        return z + (d ? E - dd : 0u);
+    }
 };
+
+// Appends the lanes' keys with `match` to the candidates.
+__device__ __forceinline__ void push_cand(uint64_t* cand, uint32_t* count, uint64_t x, bool match)
+{
+    const uint64_t m = __ballot(match);
+    if (!m) return;
+    uint32_t at = 0;
+    if ((threadIdx.x & (kWave - 1)) == 0) at = atomicAdd(count, (uint32_t)__popcll(m));
+    at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
+    if (match) cand[at + lanes_below(m)] = x;
+}
 
 __device__ __forceinline__ TokenKeys token_keys(const PostArgs& a, const SelUnit& su)
 {
@@ -1660,103 +1678,6 @@ __device__ __forceinline__ TokenKeys token_keys(const PostArgs& a, const SelUnit
     t.Mt = full ? su.Mt : 1ull;
     t.E = su.E;
     return t;
-}
-
-// A selection's keys as the radix search reads them: each() calls f(key, in)
-// the same number of times in every lane, in = the lane has a key there.
-// All of them, from memory at every pass:
-template <int NT>
-struct MemKeys {
-    TokenKeys t;
-    const int32_t* idx;  // the tokens (NULL: tokens 0 .. N - 1)
-    int N;
-    template <typename F>
-    __device__ __forceinline__ void each(F&& f) const
-    {
-        const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x >> 6;
-        constexpr int U = 4;
-        for (int base = wid * kWave; base < N; base += U * NT) {
-            uint64_t x[U];
-            // clamped indices: every load is issued before any is used
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int i = min(base + u * NT + lane, N - 1);
-                x[u] = t.at(idx ? idx[i] : i);
-            }
-#pragma unroll
-            for (int u = 0; u < U; ++u) f(x[u], base + u * NT + lane < N);
-        }
-    }
-};
-
-// Read once and kept in registers: lane t of the block has those of tokens
-// base + lo .. base + hi - 1, K of them at most, and every thread's tokens
-// follow the thread's before it. A selection is a chain of passes over its
-// keys in one block, bound by the latency of its steps and the instructions
-// of its passes: four consecutive tokens per load, no copy of the keys in LDS
-// and one scan of the counts instead of a counting and a placing pass. The
-// launch of 8 clips of 8,192 tokens (1,024 threads, one block each) takes
-// 10.6 us where four blocks a clip with the keys staged in LDS took 11.6;
-// 96 selections of at most 1,500 (256 threads) 6.3 against 6.4.
-template <int NT, int K>
-struct RegKeys {
-    uint64_t key[K];
-    int base, lo, hi;
-    template <typename F>
-    __device__ __forceinline__ void each(F&& f) const
-    {
-#pragma unroll
-        for (int j = 0; j < K; ++j) f(key[j], j >= lo && j < hi);
-    }
-};
-
-typedef unsigned int sel_u32x4 __attribute__((ext_vector_type(4), aligned(4)));
-
-// This thread's K of the tokens [t0, t0 + n) (keys of t), thread 0 first. A
-// last thread with fewer than K left reads the K before the end and uses
-// only its own; a range of fewer than K tokens is read one by one.
-template <int NT, int K>
-__device__ __forceinline__ void load_keys(RegKeys<NT, K>& r, const TokenKeys& t, int t0, int n)
-{
-    uint32_t zz[K], dd[K];
-#pragma unroll
-    for (int j = 0; j < K; ++j) zz[j] = dd[j] = 0u;
-    const int i0 = (int)threadIdx.x * K;
-    if (n >= K) {
-        const int b = min(i0, n - K);
-        r.base = t0 + b;
-        r.lo = min(K, i0 - b);
-        r.hi = K;
-        if (i0 < n) {
-            if (t.first) {
-#pragma unroll
-                for (int q = 0; q < K / 4; ++q) {
-                    const sel_u32x4 v = *reinterpret_cast<const sel_u32x4*>(t.first + r.base + 4 * q);
-                    zz[4 * q] = v.x; zz[4 * q + 1] = v.y; zz[4 * q + 2] = v.z; zz[4 * q + 3] = v.w;
-                }
-            }
-            if (t.d) {
-#pragma unroll
-                for (int q = 0; q < K / 4; ++q) {
-                    const sel_u32x4 v = *reinterpret_cast<const sel_u32x4*>(t.d + r.base + 4 * q);
-                    dd[4 * q] = v.x; dd[4 * q + 1] = v.y; dd[4 * q + 2] = v.z; dd[4 * q + 3] = v.w;
-                }
-            }
-        }
-    } else {
-        r.base = t0;
-        r.lo = 0;
-        r.hi = threadIdx.x == 0 ? n : 0;
-#pragma unroll
-        for (int j = 0; j < K; ++j) {
-            if (j < r.hi) {
-                if (t.first) zz[j] = t.first[t0 + j];
-                if (t.d) dd[j] = t.d[t0 + j];
-            }
-        }
-    }
-#pragma unroll
-    for (int j = 0; j < K; ++j) r.key[j] = t.of(zz[j], dd[j]);
 }
 
 template <int CTRL, int ROW_MASK>
@@ -1777,6 +1698,133 @@ __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t x)
     x += dpp_u<0x142, 0xA>(0u, x);
     x += dpp_u<0x143, 0xC>(0u, x);
     return x;
+}
+
+// A selection's keys as the radix search reads them: each() calls f(key, in)
+// the same number of times in every lane, in = the lane has a key there;
+// copy() appends those that pred holds for to cand. All of them, from memory
+// at every pass:
+template <int NT>
+struct MemKeys {
+    using Key = uint64_t;
+    TokenKeys t;
+    const int32_t* idx;  // the tokens (NULL: tokens 0 .. N - 1)
+    int N;
+    template <typename F>
+    __device__ __forceinline__ void each(F&& f) const
+    {
+        const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x >> 6;
+        constexpr int U = 4;
+        for (int base = wid * kWave; base < N; base += U * NT) {
+            uint64_t x[U];
+            // clamped indices: every load is issued before any is used
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int i = min(base + u * NT + lane, N - 1);
+                x[u] = t.at(idx ? idx[i] : i);
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) f(x[u], base + u * NT + lane < N);
+        }
+    }
+    template <typename P>
+    __device__ __forceinline__ void copy(uint64_t* cand, uint32_t* count, P&& pred) const
+    {
+        each([&](uint64_t x, bool in) { push_cand(cand, count, x, in && pred(x)); });
+    }
+};
+
+// Read once and kept in registers, in quads of four consecutive tokens: quad q
+// of thread t is the (q NT + t)-th of the selection, so that loads and stores
+// of a wavefront meet in few cache lines and the tokens' order is that of
+// (q, t). 32 bits a key but for two-term ones.
+//
+// A selection is a chain of passes over its keys in one block, bound by the
+// latency of its steps and the instructions of its passes. Post launches of a
+// plan, with each thread's tokens consecutive and 64-bit keys and one block a
+// selection -> quads and 32 bits -> a block per round of quads: 8 clips of
+// 8,192 tokens 11.6 -> 10.4 -> 10.5 us, 16 x 3,000 7.4 -> 6.2 -> 5.6, 64 x 2,880
+// 7.3 -> 6.5 -> 5.7, 32 x (576 + 1,500) 5.6 -> 5.1 -> 4.9.
+template <int NT, int K, typename KT>
+struct RegKeys {
+    using Key = KT;
+    KT key[K];
+    uint32_t in;  // bit j: key j is a token of this thread
+    template <typename F>
+    __device__ __forceinline__ void each(F&& f) const
+    {
+#pragma unroll
+        for (int j = 0; j < K; ++j) f(key[j], (in >> j & 1u) != 0u);
+    }
+    template <typename P>
+    __device__ __forceinline__ void copy(uint64_t* cand, uint32_t* count, P&& pred) const
+    {
+        uint32_t m = 0;
+#pragma unroll
+        for (int j = 0; j < K; ++j) m |= pred(key[j]) ? 1u << j : 0u;
+        m &= in;
+        if (!__ballot(m != 0u)) return;
+        const uint32_t c = (uint32_t)__builtin_popcount(m), inc = wave_incl_scan(c);
+        uint32_t at = 0;
+        if ((threadIdx.x & (kWave - 1)) == kWave - 1) at = atomicAdd(count, inc);
+        at = (uint32_t)__builtin_amdgcn_readlane((int)at, kWave - 1) + inc - c;
+#pragma unroll
+        for (int j = 0; j < K; ++j)
+            if (m >> j & 1u) cand[at++] = (uint64_t)key[j];
+    }
+};
+
+typedef unsigned int sel_u32x4 __attribute__((ext_vector_type(4), aligned(4)));
+
+// First token of quad q of this thread among n: past the last whole quad the
+// four tokens before the end (of which the thread has only its own, if any).
+template <int NT>
+__device__ __forceinline__ int quad_first(int q, int n) { return min(4 * (q * NT + (int)threadIdx.x), max(n - 4, 0)); }
+
+// This thread's of the tokens [t0, t0 + n) (keys of t), at most NT K of them.
+template <int NT, int K, typename KT>
+__device__ __forceinline__ void load_keys(RegKeys<NT, K, KT>& r, const TokenKeys& t, int t0, int n)
+{
+    uint32_t zz[K], dd[K];
+#pragma unroll
+    for (int j = 0; j < K; ++j) zz[j] = dd[j] = 0u;
+    r.in = 0u;
+    if (n >= 4) {
+        // every load is in bounds and issued before any is used
+        if (t.first) {
+#pragma unroll
+            for (int q = 0; q < K / 4; ++q) {
+                const sel_u32x4 v = *reinterpret_cast<const sel_u32x4*>(t.first + t0 + quad_first<NT>(q, n));
+                zz[4 * q] = v.x; zz[4 * q + 1] = v.y; zz[4 * q + 2] = v.z; zz[4 * q + 3] = v.w;
+            }
+        }
+        if (t.d) {
+#pragma unroll
+            for (int q = 0; q < K / 4; ++q) {
+                const sel_u32x4 v = *reinterpret_cast<const sel_u32x4*>(t.d + t0 + quad_first<NT>(q, n));
+                dd[4 * q] = v.x; dd[4 * q + 1] = v.y; dd[4 * q + 2] = v.z; dd[4 * q + 3] = v.w;
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < K / 4; ++q) {
+            const int skip = 4 * (q * NT + (int)threadIdx.x) - quad_first<NT>(q, n);  // tokens of other threads
+            r.in |= (skip < 4 ? 0xFu << skip & 0xFu : 0u) << (4 * q);
+        }
+    } else {
+        if (threadIdx.x == 0) r.in = (1u << n) - 1u;
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            if (r.in >> j & 1u) {
+                if (t.first) zz[j] = t.first[t0 + j];
+                if (t.d) dd[j] = t.d[t0 + j];
+            }
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < K; ++j) {
+        if constexpr (sizeof(KT) == 4) r.key[j] = t.of32(zz[j], dd[j]);
+        else r.key[j] = t.of(zz[j], dd[j]);
+    }
 }
 
 // Block-wide exclusive prefix sum in thread order; *total gets the sum.
@@ -1805,17 +1853,6 @@ __device__ __forceinline__ void clear_hist(PostShared<NT>& sh)
     for (int b = threadIdx.x; b < kRadixBins; b += NT) sh.hist[b] = 0u;
 }
 
-// Appends the lanes' keys with `match` to the candidates.
-__device__ __forceinline__ void push_cand(uint64_t* cand, uint32_t* count, uint64_t x, bool match)
-{
-    const uint64_t m = __ballot(match);
-    if (!m) return;
-    uint32_t at = 0;
-    if ((threadIdx.x & (kWave - 1)) == 0) at = atomicAdd(count, (uint32_t)__popcll(m));
-    at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
-    if (match) cand[at + lanes_below(m)] = x;
-}
-
 // MAS-guided keep count (Eq. 11 floor): k = min(N, ceil((1 - MAS) * N)) in double.
 __device__ __forceinline__ int guided_keep_count(float mas, int N)
 {
@@ -1831,9 +1868,9 @@ __device__ __forceinline__ int guided_keep_count(float mas, int N)
 // bits (bits = the width of the largest key and prefix = 0 for all keys of a
 // selection). cleared: the histogram is already zero (and the block past a
 // barrier since).
-template <int NT, typename Src>
-__device__ __forceinline__ uint64_t radix_rank(PostShared<NT>& sh, const Src& src, int N, uint32_t rank, int bits,
-                                               uint64_t prefix, bool cleared, uint32_t* below_out)
+template <int NT, typename Src, typename X = typename Src::Key>
+__device__ __forceinline__ X radix_rank(PostShared<NT>& sh, const Src& src, int N, uint32_t rank, int bits, X prefix,
+                                        bool cleared, uint32_t* below_out)
 {
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wid = tid >> 6;
     constexpr int kW = NT / kWave;
@@ -1853,7 +1890,7 @@ __device__ __forceinline__ uint64_t radix_rank(PostShared<NT>& sh, const Src& sr
             // so few keys are left that a copy of them and a direct rank among
             // them cost less than the remaining digit passes (their count was
             // reset by the digit scan before its barrier)
-            src.each([&](uint64_t x, bool in) { push_cand(sh.cand, &sh.ncopy, x, in && (x >> bits) == prefix); });
+            src.copy(sh.cand, &sh.ncopy, [&](X x) { return (X)(x >> bits) == prefix; });
             __syncthreads();
             const int m = (int)sh.ncopy;
             // candidate c = (w % cw) * 64 + lane is counted against the j-range
@@ -1897,7 +1934,7 @@ __device__ __forceinline__ uint64_t radix_rank(PostShared<NT>& sh, const Src& sr
                 }
             }
             __syncthreads();
-            prefix = sh.vsel;
+            prefix = (X)sh.vsel;
             below += sh.below;
             break;
         }
@@ -1912,15 +1949,14 @@ __device__ __forceinline__ uint64_t radix_rank(PostShared<NT>& sh, const Src& sr
         cleared = false;
         if (ncand >= 0) {
             for (int base = wid * kWave; base < ncand; base += NT) {
-                const uint64_t x = sh.cand[min(base + lane, ncand - 1)];
+                const X x = (X)sh.cand[min(base + lane, ncand - 1)];
                 if (base + lane < ncand && (x >> bits) == prefix) atomicAdd(&sh.hist[(uint32_t)(x >> shift) & mask], 1u);
             }
         } else {
-            src.each([&](uint64_t x, bool in) {
-                const bool match = in && (all || (x >> bits) == prefix);
-                if (match) atomicAdd(&sh.hist[(uint32_t)(x >> shift) & mask], 1u);
-                if (collect) push_cand(sh.cand, &sh.ncand, x, match);
+            src.each([&](X x, bool in) {
+                if (in && (all || (X)(x >> bits) == prefix)) atomicAdd(&sh.hist[(uint32_t)(x >> shift) & mask], 1u);
             });
+            if (collect) src.copy(sh.cand, &sh.ncand, [&](X x) { return (X)(x >> bits) == prefix; });
         }
         __syncthreads();
         if (collect) ncand = (int)sh.ncand;
@@ -1977,50 +2013,71 @@ struct SelDest {
 
 // Keep flags and kept indices of the keys in registers, given the largest
 // kept key: `ties` keys equal to it are kept, lowest index first; lt0 and eq0
-// keys below and equal to it belong to tokens before the block's.
-template <int NT, int K>
-__device__ __forceinline__ void place_regs(const PostArgs& a, PostShared<NT>& sh, const RegKeys<NT, K>& r, uint64_t vstar,
-                                           uint32_t ties, uint32_t lt0, uint32_t eq0, const SelDest& o)
+// keys below and equal to it belong to tokens before the block's. only: the
+// round of quads that this block writes (-1: all of them).
+template <int NT, int K, typename KT>
+__device__ __forceinline__ void place_regs(const PostArgs& a, PostShared<NT>& sh, const RegKeys<NT, K, KT>& r, int t0, int n,
+                                           KT vstar, uint32_t ties, uint32_t lt0, uint32_t eq0, const SelDest& o, int only)
 {
+    constexpr int Q = K / 4, kW = NT / kWave;
+    static_assert(Q * kW <= kWave && NT * K <= 32768, "a total per lane, two 16-bit counts per word");
+    const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x >> 6;
     uint32_t ltm = 0, eqm = 0;  // this thread's tokens below and equal to vstar
 #pragma unroll
     for (int j = 0; j < K; ++j) {
-        const bool in = j >= r.lo && j < r.hi;
-        ltm |= in && r.key[j] < vstar ? 1u << j : 0u;
-        eqm |= in && r.key[j] == vstar ? 1u << j : 0u;
+        ltm |= r.key[j] < vstar ? 1u << j : 0u;
+        eqm |= r.key[j] == vstar ? 1u << j : 0u;
     }
-    // both counts in one scan: at most 16,384 tokens a block
-    static_assert(NT * K <= 32768, "two 16-bit counts per word");
-    uint32_t tot;
-    const uint32_t ex = block_exscan<NT>((uint32_t)__builtin_popcount(ltm) | ((uint32_t)__builtin_popcount(eqm) << 16), sh, &tot);
-    const uint32_t lt = lt0 + (ex & 0xFFFFu), eq = eq0 + (ex >> 16);
-    // of the equal ones, those whose number among all equal ones is below ties
-    uint32_t left = ties > eq ? ties - eq : 0u;
-    if (left < (uint32_t)__builtin_popcount(eqm)) {
-        uint32_t m = 0;
+    ltm &= r.in;
+    eqm &= r.in;
+    // both counts of every quad before each quad, in the order (q, thread)
+    uint32_t before[Q];
 #pragma unroll
-        for (int j = 0; j < K; ++j)
-            if ((eqm >> j & 1u) && left) {
-                m |= 1u << j;
-                --left;
+    for (int q = 0; q < Q; ++q) {
+        const uint32_t c = (uint32_t)__builtin_popcount(ltm >> (4 * q) & 0xFu) |
+                           ((uint32_t)__builtin_popcount(eqm >> (4 * q) & 0xFu) << 16);
+        const uint32_t inc = wave_incl_scan(c);
+        if (lane == kWave - 1) sh.tot[q * kW + wid] = inc;
+        before[q] = inc - c;
+    }
+    __syncthreads();
+    const uint32_t tot = lane < Q * kW ? sh.tot[lane] : 0u;
+    const uint32_t ex = wave_incl_scan(tot) - tot;
+    const int w = uniform(wid);
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        if (only >= 0 && q != only) continue;
+        const uint32_t b = before[q] + (uint32_t)__builtin_amdgcn_readlane((int)ex, q * kW + w);
+        const uint32_t lt = lt0 + (b & 0xFFFFu), eq = eq0 + (b >> 16);
+        uint32_t eqk = eqm >> (4 * q) & 0xFu;
+        // of the equal ones, those whose number among all equal ones is below ties
+        uint32_t left = ties > eq ? ties - eq : 0u;
+        if (left < (uint32_t)__builtin_popcount(eqk)) {
+            uint32_t m = 0;
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if ((eqk >> e & 1u) && left) {
+                    m |= 1u << e;
+                    --left;
+                }
+            eqk = m;
+        }
+        const uint32_t kp = (ltm >> (4 * q) & 0xFu) | eqk;
+        const int first = t0 + quad_first<NT>(q, n);
+        int at = o.ioff + (int)(lt + min(eq, ties));
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (kp >> e & 1u) a.sel.kept_idx[at++] = o.iadd + first + e;
+        if (a.sel.keep) {
+            uint8_t* f = a.sel.keep + o.off + first;
+            const uint32_t in = r.in >> (4 * q) & 0xFu;
+            if (in == 0xFu && ((uintptr_t)f & 3) == 0) {
+                *reinterpret_cast<uint32_t*>(f) = (kp * 0x00204081u) & 0x01010101u;  // four bits to four bytes
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (in >> e & 1u) f[e] = (uint8_t)(kp >> e & 1u);
             }
-        eqm = m;
-    }
-    const uint32_t kp = ltm | eqm;
-    int at = o.ioff + (int)(lt + min(eq, ties));
-#pragma unroll
-    for (int j = 0; j < K; ++j)
-        if (kp >> j & 1u) a.sel.kept_idx[at++] = o.iadd + r.base + j;
-    if (a.sel.keep) {
-        uint8_t* f = a.sel.keep + o.off + r.base;
-        if (r.lo == 0 && r.hi == K && ((uintptr_t)f & 3) == 0) {
-#pragma unroll
-            for (int q = 0; q < K / 4; ++q)  // four bits to four bytes
-                reinterpret_cast<uint32_t*>(f)[q] = ((kp >> (4 * q) & 0xFu) * 0x00204081u) & 0x01010101u;
-        } else {
-#pragma unroll
-            for (int j = 0; j < K; ++j)
-                if (j >= r.lo && j < r.hi) f[j] = (uint8_t)(kp >> j & 1u);
         }
     }
 }
@@ -2077,20 +2134,20 @@ __device__ __forceinline__ bool select_edges(const PostArgs& a, const SelUnit& s
     return true;
 }
 
-// A selection of at most NT * K tokens in one block, its keys in registers.
-template <int NT, int K>
-__device__ __forceinline__ void select_in_regs(const PostArgs& a, const SelUnit& su, PostShared<NT>& sh)
+// A selection of at most NT * K tokens, its keys in registers: one block, or
+// one per round of quads, each of which finds the largest kept key from all of
+// the keys and writes its round.
+template <int NT, int K, typename KT>
+__device__ __forceinline__ void select_in_regs(const PostArgs& a, const SelUnit& su, int k, const SelDest& o, PostShared<NT>& sh)
 {
-    RegKeys<NT, K> r;
-    load_keys<NT, K>(r, token_keys(a, su), 0, su.N);
+    RegKeys<NT, K, KT> r;
+    load_keys<NT, K, KT>(r, token_keys(a, su), 0, su.N);
     clear_hist(sh);  // while the keys are in flight
-    const int k = keep_of(a, su, sh);
-    SelDest o;
-    if (select_edges<NT>(a, su, k, 0, su.N, o)) return;
     __syncthreads();
     uint32_t below;
-    const uint64_t vstar = radix_rank<NT>(sh, r, su.N, (uint32_t)k - 1, key_bits(su), 0ull, true, &below);
-    place_regs<NT, K>(a, sh, r, vstar, (uint32_t)k - below, 0u, 0u, o);
+    const KT vstar = radix_rank<NT>(sh, r, su.N, (uint32_t)k - 1, key_bits(su), (KT)0, true, &below);
+    place_regs<NT, K, KT>(a, sh, r, 0, su.N, vstar, (uint32_t)k - below, 0u, 0u, o,
+                            su.nparts > 1 ? su.part : -1);
 }
 
 // A selection of more tokens whose tables leave no room for the two passes of
@@ -2108,7 +2165,7 @@ __device__ __forceinline__ void select_from_memory(const PostArgs& a, const SelU
     if (select_edges<NT>(a, su, k, s0, s1, o)) return;
     const TokenKeys tk = token_keys(a, su);
     uint32_t below;
-    const uint64_t vstar = radix_rank<NT>(sh, MemKeys<NT>{tk, nullptr, N}, N, (uint32_t)k - 1, key_bits(su), 0ull, false, &below);
+    const uint64_t vstar = radix_rank<NT>(sh, MemKeys<NT>{tk, nullptr, N}, N, (uint32_t)k - 1, key_bits(su), (uint64_t)0, false, &below);
     const uint32_t ties = (uint32_t)k - below;
     // counts of keys below and equal to vstar before this block's slice (the
     // prefix [0, s0) split evenly over the wavefronts), and in each
@@ -2211,8 +2268,8 @@ __global__ __launch_bounds__(kBigBlock) void k_big_hist(PostArgs a)
     __shared__ PostShared<kBigBlock> sh;
     const SelUnit su = a.t.sel_unit[blockIdx.x];
     const int t0 = su.part * kBigChunk, n = min(kBigChunk, su.N - t0);
-    RegKeys<kBigBlock, kBigK> r;
-    load_keys<kBigBlock, kBigK>(r, token_keys(a, su), t0, n);
+    RegKeys<kBigBlock, kBigK, uint64_t> r;
+    load_keys<kBigBlock, kBigK, uint64_t>(r, token_keys(a, su), t0, n);
     clear_hist(sh);
     __syncthreads();
     const int shift = first_shift(key_bits(su));
@@ -2232,8 +2289,8 @@ __global__ __launch_bounds__(kBigBlock) void k_big_cand(PostArgs a)
     const BigRefs b = big_refs(a, su);
     const int tid = threadIdx.x, own = su.part;
     const int t0 = own * kBigChunk, n = min(kBigChunk, su.N - t0);
-    RegKeys<kBigBlock, kBigK> r;
-    load_keys<kBigBlock, kBigK>(r, token_keys(a, su), t0, n);
+    RegKeys<kBigBlock, kBigK, uint64_t> r;
+    load_keys<kBigBlock, kBigK, uint64_t>(r, token_keys(a, su), t0, n);
     // bins 2 tid and 2 tid + 1 over all chunks, and over those before this one
     uint32_t tot0 = 0, tot1 = 0, bef0 = 0, bef1 = 0;
     constexpr int U = 8;
@@ -2278,12 +2335,12 @@ __global__ __launch_bounds__(kBigBlock) void k_big_cand(PostArgs a)
     uint32_t m = 0;
 #pragma unroll
     for (int j = 0; j < kBigK; ++j)
-        if (j >= r.lo && j < r.hi && (uint32_t)(r.key[j] >> shift) == digit) m |= 1u << j;
+        if ((r.in >> j & 1u) && (uint32_t)(r.key[j] >> shift) == digit) m |= 1u << j;
     uint32_t at = inb + block_exscan<kBigBlock>((uint32_t)__builtin_popcount(m), sh, &total);
     if (shift > 0) {  // otherwise the digit is the key
 #pragma unroll
         for (int j = 0; j < kBigK; ++j)
-            if (m >> j & 1u) b.cand[at++] = r.base + j;
+            if (m >> j & 1u) b.cand[at++] = t0 + quad_first<kBigBlock>(0, n) + j;
     }
     if (tid == 0) {
         b.pre[own] = BigPre{(uint32_t)sh.red, inb};
@@ -2300,8 +2357,8 @@ __device__ __forceinline__ void select_big(const PostArgs& a, const SelUnit& su,
     const BigPre pre = b.pre[su.part];
     const TokenKeys tk = token_keys(a, su);
     const int t0 = su.part * kBigChunk, n = min(kBigChunk, su.N - t0);
-    RegKeys<NT, K> r;
-    load_keys<NT, K>(r, tk, t0, n);
+    RegKeys<NT, K, uint64_t> r;
+    load_keys<NT, K, uint64_t>(r, tk, t0, n);
     SelDest o;
     if (select_edges<NT>(a, su, head.k, t0, t0 + n, o)) return;
     const int shift = first_shift(key_bits(su));
@@ -2314,22 +2371,21 @@ __device__ __forceinline__ void select_big(const PostArgs& a, const SelUnit& su,
         uint64_t nlt = 0, neq = 0;
         if (m <= NT * 4) {
             // four candidates a thread, in registers
-            RegKeys<NT, 4> c;
-            c.base = (int)threadIdx.x * 4;
-            c.lo = 0;
-            c.hi = max(0, min(4, m - c.base));
+            RegKeys<NT, 4, uint64_t> c;
+            const int c0 = (int)threadIdx.x * 4;
+            c.in = (1u << max(0, min(4, m - c0))) - 1u;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) c.key[j] = tk.at(b.cand[min(c.base + j, m - 1)]);
-            vstar = radix_rank<NT>(sh, c, m, rank, shift, head.digit, false, &cb);
+            for (int j = 0; j < 4; ++j) c.key[j] = tk.at(b.cand[min(c0 + j, m - 1)]);
+            vstar = radix_rank<NT>(sh, c, m, rank, shift, (uint64_t)head.digit, false, &cb);
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                const bool in = j < c.hi && c.base + j < (int)pre.in_bin;
+                const bool in = (c.in >> j & 1u) && c0 + j < (int)pre.in_bin;
                 nlt += in && c.key[j] < vstar ? 1u : 0u;
                 neq += in && c.key[j] == vstar ? 1u : 0u;
             }
         } else {
             const MemKeys<NT> src{tk, b.cand, m};
-            vstar = radix_rank<NT>(sh, src, m, rank, shift, head.digit, false, &cb);
+            vstar = radix_rank<NT>(sh, src, m, rank, shift, (uint64_t)head.digit, false, &cb);
             const MemKeys<NT> first{tk, b.cand, (int)pre.in_bin};
             first.each([&](uint64_t x, bool in) {
                 nlt += in && x < vstar ? 1u : 0u;
@@ -2341,7 +2397,7 @@ __device__ __forceinline__ void select_big(const PostArgs& a, const SelUnit& su,
         lt0 += (uint32_t)s;
         eq0 = (uint32_t)(s >> 32);
     }
-    place_regs<NT, K>(a, sh, r, vstar, (uint32_t)head.k - below, lt0, eq0, o);
+    place_regs<NT, K, uint64_t>(a, sh, r, t0, n, vstar, (uint32_t)head.k - below, lt0, eq0, o, -1);
 }
 
 // Top-k of one selection: the k smallest (key, index) pairs of a segment, or
@@ -2352,31 +2408,48 @@ __device__ __forceinline__ void select_big(const PostArgs& a, const SelUnit& su,
 // per frame writes its kept indices at positions f k_f.. of the segment's
 // range and its share, P - k_f entries, of the -1 tail after the T k_f kept
 // ones. The number of keys a thread holds follows the selection's size.
-template <int NT>
-__device__ __forceinline__ void role_select(const PostArgs& a, int unit, PostShared<NT>& sh)
+template <int NT, int K>
+__device__ __forceinline__ void select_by_width(const PostArgs& a, const SelUnit& su, int k, const SelDest& o, PostShared<NT>& sh)
 {
-    const SelUnit su = a.t.sel_unit[unit];
+    if (su.kind == kKeyFull) select_in_regs<NT, K, uint64_t>(a, su, k, o, sh);
+    else select_in_regs<NT, K, uint32_t>(a, su, k, o, sh);
+}
+
+template <int NT>
+__device__ __forceinline__ void role_select(const PostArgs& a, int b, PostShared<NT>& sh)
+{
+    // blocks of listed parts, then a.sel_parts for each of the other selections
+    const bool listed = b < a.n_sel_listed;
+    const int unit = listed ? b : a.n_sel_listed + (b - a.n_sel_listed) / a.sel_parts;
+    SelUnit su = a.t.sel_unit[unit];
     if constexpr (NT == kPostBigBlock) {
         // (selections of more than kSelSmallTokens tokens always take these blocks)
         if (su.big) {
             select_big<NT>(a, su, sh);
             return;
         }
-        if (su.nparts > 1) {
+        if (listed) {
             select_from_memory<NT>(a, su, sh);
             return;
         }
+        static_assert(kSelRegTokens <= 16 * NT, "16 keys a thread hold the largest selection in registers");
     } else {
-        static_assert(kSelSmallTokens <= 32 * NT, "32 keys a thread hold the largest selection of the small blocks");
-        if (su.N > 16 * NT) {
-            select_in_regs<NT, 32>(a, su, sh);
-            return;
-        }
+        static_assert(kSelSmallTokens <= 16 * NT, "16 keys a thread hold the largest selection of the small blocks");
     }
-    static_assert(kSelRegTokens <= 16 * kPostBigBlock, "16 keys a thread hold the largest selection in registers");
-    if (su.N <= 4 * NT) select_in_regs<NT, 4>(a, su, sh);
-    else if (su.N <= 8 * NT) select_in_regs<NT, 8>(a, su, sh);
-    else select_in_regs<NT, 16>(a, su, sh);
+    int s0 = 0, s1 = su.N;
+    if (a.sel_parts > 1) {
+        su.part = (b - a.n_sel_listed) % a.sel_parts;
+        su.nparts = max(1, (su.N + 4 * NT - 1) / (4 * NT));
+        if (su.part >= su.nparts) return;
+        s0 = su.part * 4 * NT;
+        s1 = min(su.N, s0 + 4 * NT);
+    }
+    const int k = keep_of(a, su, sh);
+    SelDest o;
+    if (select_edges<NT>(a, su, k, s0, s1, o)) return;
+    if (su.N <= 4 * NT) select_by_width<NT, 4>(a, su, k, o, sh);
+    else if (su.N <= 8 * NT) select_by_width<NT, 8>(a, su, k, o, sh);
+    else select_by_width<NT, 16>(a, su, k, o, sh);
 }
 
 // LR: a learned call (request role with head counts, descriptors and the
@@ -2655,12 +2728,15 @@ int launch_post(const PostArgs& a, void* stream, void* ev0, void* ev1)
 {
     const int blocks = a.n_req_blocks + a.n_frame_blocks + a.n_sel_blocks;
     if (blocks <= 0) return kNoLaunch;
+    if (a.n_sel_blocks > 0 && (a.sel_parts < 1 || a.n_sel_listed < 0 || a.n_sel_listed > a.n_sel_blocks ||
+                               (a.n_sel_listed > 0 && !a.big_block)))
+        return (int)hipErrorInvalidValue;
     if (a.learned && (!a.t.partial_x || !a.t.head_count || (a.use_mlp && !a.mlp_u))) return (int)hipErrorInvalidValue;
     if (a.learned)
         return launch(k_post<kPostBlock, true>, dim3((unsigned)(a.n_req_blocks + a.n_frame_blocks)), dim3(kPostBlock), 0,
                       stream, a, ev0, ev1);
     if (a.n_big_blocks > 0) {
-        if (!a.big || a.n_big_blocks > a.n_sel_blocks) return (int)hipErrorInvalidValue;
+        if (!a.big || a.n_big_blocks > a.n_sel_listed) return (int)hipErrorInvalidValue;
         const dim3 grid((unsigned)a.n_big_blocks), block(kBigBlock);
         int rc = launch(k_big_hist, grid, block, 0, stream, a, ev0, nullptr);
         if (rc == 0) rc = launch(k_big_cand, grid, block, 0, stream, a, nullptr, nullptr);

@@ -1,5 +1,7 @@
 """Selection over its sizes: the keys of up to 16,384 tokens sit in the
-registers of one block (4, 8, 16 or 32 a thread), larger selections take the
+registers of a block (4, 8 or 16 a thread), and while there are fewer than 256
+selections each round of four a thread is written by a block of its own; larger
+selections take the
 two passes over chunks of 4,096, or, in the smallest workspace that is
 accepted, blocks that re-read all keys. Every size at the edges of those
 ranges, every kind of key (activity, temporal, both; tied in long runs, one
@@ -135,3 +137,16 @@ def test_smallest_workspace(n, how, dev):
     print(f"[selection] smallest workspace {n} {how}", flush=True)
     check([(IMAGE, 1, 3, 512, 0.5), (IMAGE, 1, n, 512, 0.4)], how, dev, smallest=True, seed=n)
     check([(VIDEO, 5, n // 5, 512, -1.0)], how, dev, smallest=True, seed=n + 1)
+
+
+@pytest.mark.parametrize("largest", [4095, 4096, 16384])
+@pytest.mark.parametrize("count", [255, 256, 257])
+def test_one_block_or_one_per_round(count, largest, dev):
+    """On both sides of the 256 selections up to which a selection is written
+    by a block per round (1,024 tokens, or 4,096 beside one of 4,096 and more)."""
+    print(f"[selection] {count} selections up to {largest}", flush=True)
+    n = [1 + (37 * i) % 1100 for i in range(count - 5)] + [1024, 1025, 2049, 3000, largest]
+    segs = [(VIDEO, 3, -(-x // 3), 40, -1.0) if i % 7 == 2 else (IMAGE, 1, x, 40, 0.0 if i % 11 == 3 else 0.37)
+            for i, x in enumerate(n)]
+    check(segs, "crowded", dev, seed=count)
+    check(segs[-3:-1], "tied", dev, seed=count + 1)
