@@ -235,6 +235,33 @@ size_t workspace_bytes_for(int n, int R, int64_t ntok, int64_t nframes)
            align_up(sizeof(float) * (size_t)kNumMod * (size_t)std::max(R, 1), kWsAlign);
 }
 
+// Whether the chain pass scores a clip of rows for k_pair<true> faster. That
+// instance has one wavefront per SIMD, so as long as a call's pairs of positions
+// are no more than the SIMDs it is 5-60 % faster than the chain pass; above that
+// it takes whole rounds of ranges of F frames, of which a SIMD reads frames_read.
+// Calls, chain pass : k_pair (1,024 SIMDs):
+//  - fp32, whose chain pass reads few frames twice. 4,096 pairs of 1,024 channels
+//    1 : 1.36 at 2 frames, 1.11 at 6, 0.96 at 16, 0.92 at 32; 1,280 pairs (rounds of
+//    75-90 % use) 1.2 at 2 to 24 frames; 1,792 pairs of 16 to 24 frames, one range each
+//    (87 %), 0.96; 1,536 pairs of 32 frames in two ranges (94 %) 0.97, in ranges of 8
+//    frames and less 1.1. So k_pair takes clips of 16 frames and more in nearly
+//    full rounds of whole clips or of long ranges.
+//  - bf16. 2 frames 1 : 1.1 to 1.3; 3 frames 0.91 to 1.01 with 1,152 channels (1.05 to
+//    1.09 from 8,192 pairs) and 1.0 to 1.15 with 1,536 and 2,048; 6 frames 0.8; second
+//    rounds of at most a third, of 9 to 15 frames 1.0 to 1.1, of 4 to 8 with rows over
+//    3 KiB 1.0 to 1.13; 4 frames of such rows in rounds of 70-83 % use 1.1, of 96 % 0.9.
+bool chain_is_faster(const msao_segment& s, int64_t row_bytes, int64_t pairs_total, int F, int64_t frames_read)
+{
+    if (pairs_total <= kPairTargetWaves) return false;
+    const int T = s.n_frames;
+    const double use = (double)pairs_total * T / ((double)kPairTargetWaves * (double)frames_read);
+    if (s.dtype == MSAO_BF16)
+        return T < 3 || (T == 3 && (row_bytes >= 3072 || pairs_total >= 8 * kPairTargetWaves)) ||
+               (T == 4 && row_bytes > 3072 && use < 0.86) ||
+               (T < 16 && pairs_total * 8 < kPairTargetWaves * 11 && (T > 8 || row_bytes > 3072));
+    return T < 16 || use < (F == T ? 0.86 : F >= 12 && pairs_total < 2 * kPairTargetWaves ? 0.85 : 0.96);
+}
+
 // fuse_copy: a full run with compaction, where segments that keep every row
 // are copied by the scoring pass (they get no gather items).
 void build_plan(const msao_ctx* ctx, const msao_segment* segs, int n, int R, const msao_params* p,
@@ -424,9 +451,9 @@ void build_plan(const msao_ctx* ctx, const msao_segment* segs, int n, int R, con
             // beyond one per SIMD queue behind the first, and a range after a
             // clip's first re-reads one frame; ties keep the longer range
             int F = std::min(s.n_frames, kPairMaxFrames);
+            int64_t best_cost = INT64_MAX;
             {
                 int best = F;
-                int64_t best_cost = INT64_MAX;
                 for (int f = F;; f = (f + 1) / 2) {
                     const int64_t tb = (s.n_frames + f - 1) / f;
                     const int64_t rounds = (pairs_total * tb + kPairTargetWaves - 1) / kPairTargetWaves;
@@ -442,9 +469,10 @@ void build_plan(const msao_ctx* ctx, const msao_segment* segs, int n, int R, con
             const int tblk = (s.n_frames + F - 1) / F;
             const int64_t pitems =
                 ((int64_t)((s.tokens_per_frame + 1) / 2) * tblk + kPairWaves - 1) / kPairWaves * kPairWaves;
-            if (pitems <= N) {
+            const bool wide = s.dtype != MSAO_BF16 || row_bytes > kPairNarrowRowBytes;
+            if (pitems <= N && !(wide && chain_is_faster(s, row_bytes, pairs_total, F, best_cost))) {
                 d.pair = 1;
-                if (s.dtype != MSAO_BF16 || row_bytes > kPairNarrowRowBytes) pl.pair_wide = true;
+                if (wide) pl.pair_wide = true;
                 d.tblk = tblk;
                 d.per_item = F;
                 items = (int)pitems;

@@ -112,3 +112,13 @@ def test_workspace_with_room_for_the_chain_pass_only(entry, dtype, C, dev, monke
         assert np.array_equal(a, b), k
     for c in ctxs:
         c.close()
+
+
+@pytest.mark.parametrize("dtype,C,T,P", [("f32", 8, 2, 2046), ("f32", 8, 2, 2050), ("f32", 8, 15, 4096), ("f32", 8, 16, 4096),
+                                         ("f32", 8, 33, 2100), ("bf16", 1032, 2, 2050), ("bf16", 1032, 4, 2050),
+                                         ("bf16", 1544, 4, 2050), ("bf16", 1032, 9, 2050)])
+def test_clips_of_more_positions_than_simds_take_pairs_of(dtype, C, T, P, dev):
+    """Both sides of the rule that leaves wide rows to the chain pass when there
+    are more than 1,024 pairs of positions; beside them, a clip of narrow rows."""
+    log(f"[pair wide] {T} x {P} x {C} {dtype}")
+    run_and_compare(clips(T + P, [(T, P, C)], dtype) + clips(1, [(5, 9, 256)], "bf16"), 2, default_params(), dev)
