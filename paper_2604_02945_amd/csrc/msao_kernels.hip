@@ -1707,6 +1707,7 @@ __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t x)
 template <int NT>
 struct MemKeys {
     using Key = uint64_t;
+    static constexpr bool kInRegs = false;
     TokenKeys t;
     const int32_t* idx;  // the tokens (NULL: tokens 0 .. N - 1)
     int N;
@@ -1748,6 +1749,7 @@ struct MemKeys {
 template <int NT, int K, typename KT>
 struct RegKeys {
     using Key = KT;
+    static constexpr bool kInRegs = true;
     KT key[K];
     uint32_t in;  // bit j: key j is a token of this thread
     template <typename F>
@@ -1953,10 +1955,13 @@ __device__ __forceinline__ X radix_rank(PostShared<NT>& sh, const Src& src, int 
                 if (base + lane < ncand && (x >> bits) == prefix) atomicAdd(&sh.hist[(uint32_t)(x >> shift) & mask], 1u);
             }
         } else {
+            // (keys in memory are read once for both)
             src.each([&](X x, bool in) {
-                if (in && (all || (X)(x >> bits) == prefix)) atomicAdd(&sh.hist[(uint32_t)(x >> shift) & mask], 1u);
+                const bool match = in && (all || (X)(x >> bits) == prefix);
+                if (match) atomicAdd(&sh.hist[(uint32_t)(x >> shift) & mask], 1u);
+                if (!Src::kInRegs && collect) push_cand(sh.cand, &sh.ncand, x, match);
             });
-            if (collect) src.copy(sh.cand, &sh.ncand, [&](X x) { return (X)(x >> bits) == prefix; });
+            if (Src::kInRegs && collect) src.copy(sh.cand, &sh.ncand, [&](X x) { return (X)(x >> bits) == prefix; });
         }
         __syncthreads();
         if (collect) ncand = (int)sh.ncand;
