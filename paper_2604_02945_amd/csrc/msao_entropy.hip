@@ -16,7 +16,10 @@
 // With a few rows (a decode step) one workgroup per row is bound by one CU's
 // latency, so a row is cut into up to 64 parts of at least one batch (16 KiB):
 // each workgroup leaves its state in a slot of device memory and the last to
-// arrive at a row merges them. Nothing waits on the device.
+// arrive at a row merges them. Nothing waits on the device. A call that gets no
+// slot takes one workgroup of 1,024 threads per row, whose four groups take the
+// same parts in turn and whose states merge in the same order: the results of a
+// call do not depend, in any bit, on what else is in flight.
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -72,21 +75,59 @@ __device__ __forceinline__ Acc acc_merge(Acc a, Acc b)
     if (b.s != 0.0f) {
         const float dm = (b.m - a.m) * kLog2e;
         const float sc = __builtin_amdgcn_exp2f(dm);
-        a.u += (b.u + dm * b.s) * sc;
-        a.s += b.s * sc;
+        a.u = fmaf(fmaf(dm, b.s, b.u), sc, a.u);
+        a.s = fmaf(b.s, sc, a.s);
     }
     return a;
 }
 
-__device__ __forceinline__ Acc acc_shfl_xor(const Acc& a, int o)
+// The lane's value with DPP control CTRL in the rows of ROWS, `old` where there is none.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int dpp_i(int old, int v)
+{
+    return __builtin_amdgcn_update_dpp(old, v, CTRL, ROWS, 0xF, false);
+}
+
+// op over the wavefront, in every lane: four shifts within each row of 16 lanes, then
+// lane 15 of a row to the next row and lane 31 to the upper half. id: op(x, id) = x.
+template <typename Op>
+__device__ __forceinline__ int wave_reduce(int v, int id, Op op)
+{
+    v = op(v, dpp_i<0x111, 0xF>(id, v));
+    v = op(v, dpp_i<0x112, 0xF>(id, v));
+    v = op(v, dpp_i<0x114, 0xF>(id, v));
+    v = op(v, dpp_i<0x118, 0xF>(id, v));
+    v = op(v, dpp_i<0x142, 0xA>(id, v));
+    v = op(v, dpp_i<0x143, 0xC>(id, v));
+    return __builtin_amdgcn_readlane(v, kEntWave - 1);
+}
+
+__device__ __forceinline__ float wave_sum(float v)
+{
+    return __int_as_float(wave_reduce(__float_as_int(v), 0, [](int a, int b) {
+        return __float_as_int(__int_as_float(a) + __int_as_float(b));
+    }));
+}
+
+// The lanes' states merged, in every lane: their maximum first, so that each
+// lane rescales its sums once.
+__device__ __forceinline__ Acc wave_merge(const Acc& a)
 {
     Acc r;
-    r.m = __shfl_xor(a.m, o);
-    r.s = __shfl_xor(a.s, o);
-    r.u = __shfl_xor(a.u, o);
-    r.idx = __shfl_xor(a.idx, o);
+    r.m = __int_as_float(wave_reduce(__float_as_int(a.m), (int)0xFF800000u, [](int x, int y) {
+        return __float_as_int(fmaxf(__int_as_float(x), __int_as_float(y)));
+    }));
+    r.idx = wave_reduce(a.m == r.m ? a.idx : 0x7FFFFFFF, 0x7FFFFFFF, [](int x, int y) { return x < y ? x : y; });
+    // the lower bound (2^-1000 is 0) keeps a lane without a finite value at 0
+    const float dm = fmaxf((a.m - r.m) * kLog2e, -1000.0f);
+    const float sc = __builtin_amdgcn_exp2f(dm);
+    r.s = wave_sum(a.s * sc);
+    r.u = wave_sum(fmaf(dm, a.s, a.u) * sc);
     return r;
 }
+
+// The state of no logits: never the lower index.
+constexpr Acc kEmpty{-__builtin_huge_valf(), 0.0f, 0.0f, 0x7FFFFFFF};
 
 template <int DT> struct EntLane;
 template <> struct EntLane<kBF16> {
@@ -135,7 +176,7 @@ __device__ __forceinline__ void acc_add(Acc& a, const float (&x)[N], IndexOf ind
         if (a.s > 0.0f) {
             const float dm = (a.m - cm) * kLog2e;
             const float sc = __builtin_amdgcn_exp2f(dm);
-            a.u = (a.u + dm * a.s) * sc;
+            a.u = fmaf(dm, a.s, a.u) * sc;
             a.s *= sc;
         }
         a.m = cm;
@@ -187,15 +228,14 @@ __device__ __forceinline__ bool meet(const EntArgs& a, int row, int part, Acc& a
         before = __hip_atomic_fetch_add(&a.slot->row_count[row], 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
     }
     if ((int)__shfl(before, 0) != a.parts - 1) return false;
-    acc = Acc{-INFINITY, 0.0f, 0.0f, 0x7FFFFFFF};  // empty: never the lower index
+    acc = kEmpty;
     if (lane < a.parts) {
         uint32_t w[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) w[i] = __hip_atomic_load(&parts[lane].w[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         acc = Acc{__uint_as_float(w[0]), __uint_as_float(w[1]), __uint_as_float(w[2]), (int)w[3]};
     }
-#pragma unroll
-    for (int o = 1; o < kEntWave; o <<= 1) acc = acc_merge(acc, acc_shfl_xor(acc, o));
+    acc = wave_merge(acc);
     return true;
 }
 
@@ -210,20 +250,23 @@ __device__ __forceinline__ void leave(const EntArgs& a, int row)
     __hip_atomic_store(a.done, a.ticket, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-template <int DT, int U, bool SPLIT>
-__global__ __launch_bounds__(kEntBlock) void k_entropy(EntArgs a)
+// How a row is spread: one workgroup; one workgroup per part; one workgroup
+// whose kEntGroups groups of kEntBlock threads take the parts in turn.
+enum EntMode { kWhole, kSplit, kGrouped };
+constexpr int kEntWaves = kEntBlock / kEntWave;
+
+// This thread's state over chunks [c_lo, c_lo + nfull) of the row at `row`,
+// and over the elements past the row's last whole chunk if they follow.
+template <int DT, int U>
+__device__ __forceinline__ Acc part_state(const EntArgs& a, const uint8_t* row, int c_lo, int per, int tid)
 {
     using L = EntLane<DT>;
     constexpr int EPC = L::EPC;
     constexpr int STEP = U * kEntBlock;  // chunks per batch of the block
-    const int row = SPLIT ? (int)blockIdx.x / a.parts : (int)blockIdx.x;
-    const int part = SPLIT ? (int)blockIdx.x - row * a.parts : 0;
-    const int tid = threadIdx.x, lane = tid & (kEntWave - 1), wid = tid >> 6;
-    const int c_lo = SPLIT ? part * a.per : 0;           // the part's first chunk
-    const int e_lo = c_lo * EPC;                         // and element
-    const uint8_t* base = a.logits + (int64_t)row * a.row_bytes + (int64_t)c_lo * 16;
+    const int e_lo = c_lo * EPC;                         // the part's first element
+    const uint8_t* base = row + (int64_t)c_lo * 16;
     const int row_chunks = a.vocab / EPC;                // whole 16-byte chunks of the row
-    const int nfull = SPLIT ? min(a.per, row_chunks - c_lo) : row_chunks;  // and of the part
+    const int nfull = min(per, row_chunks - c_lo);       // and of the part
     const int npair = nfull / (2 * STEP) * (2 * STEP);  // chunks of whole pairs of batches
     const ent_rsrc_t rs = ent_rsrc(base, nfull * 16);
     Acc acc{-INFINITY, 0.0f, 0.0f, 0};
@@ -284,19 +327,98 @@ __global__ __launch_bounds__(kEntBlock) void k_entropy(EntArgs a)
         float x1[1] = {L::element(base, i)};
         acc_add<1>(acc, x1, [&](int) { return e_lo + i; });
     }
+    return acc;
+}
+
+// The states of the row's parts (whole batches each), wavefront by wavefront as
+// part_state and wave_merge give them, by a workgroup of kEntGroups groups. The
+// batches of a group follow one another over its parts; each is loaded while the
+// one before it is reduced, and the groups share the CU's SIMDs.
+template <int DT, int U>
+__device__ __forceinline__ void grouped_states(const EntArgs& a, const uint8_t* row, Acc (*part_acc)[kEntWaves])
+{
+    using L = EntLane<DT>;
+    constexpr int EPC = L::EPC;
+    constexpr int STEP = U * kEntBlock;
+    const int group = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kEntBlock);
+    const int tid = threadIdx.x & (kEntBlock - 1), lane = tid & (kEntWave - 1), wid = tid >> 6;
+    const int row_chunks = a.vocab / EPC;
+    const ent_rsrc_t rs = ent_rsrc(row, row_chunks * 16);
+    float x[U * EPC];
+    ent_vec4 b[U];
+    auto load = [&](int c0) {  // (past the row: zeros; the offsets stay below 2^31, as there)
 #pragma unroll
-    for (int o = 1; o < kEntWave; o <<= 1) acc = acc_merge(acc, acc_shfl_xor(acc, o));
-    __shared__ Acc wave_acc[kEntBlock / kEntWave];
-    if (lane == 0) wave_acc[wid] = acc;
-    __syncthreads();
-    if (tid >= (SPLIT ? kEntWave : 1)) return;
-    Acc r = wave_acc[0];
+        for (int u = 0; u < U; ++u) b[u] = ent_load(rs, (c0 + u * kEntBlock + tid) * 16);
+    };
+    Acc acc{-INFINITY, 0.0f, 0.0f, 0};
+    int p = group, c = 0;
+    if (p < a.parts) load(p * a.per);
+    while (p < a.parts) {
+        const int c0 = p * a.per + c, end = min((p + 1) * a.per, row_chunks);  // every part has a chunk
 #pragma unroll
-    for (int w = 1; w < kEntBlock / kEntWave; ++w) r = acc_merge(r, wave_acc[w]);
-    if (SPLIT) {
-        if (!meet(a, row, part, r)) return;
-        if (tid != 0) return;
-        leave(a, row);
+        for (int u = 0; u < U; ++u) {
+            L::widen(b[u], &x[u * EPC]);
+            if (c0 + STEP > row_chunks && c0 + u * kEntBlock + tid >= row_chunks) {
+#pragma unroll
+                for (int j = 0; j < EPC; ++j) x[u * EPC + j] = -INFINITY;
+            }
+        }
+        const bool last = c0 + STEP >= end;  // of the part
+        const int np = last ? p + kEntGroups : p, nc = last ? 0 : c + STEP;
+        if (np < a.parts) load(np * a.per + nc);
+        acc_add<U * EPC>(acc, x, [&](int j) { return (c0 + (j / EPC) * kEntBlock + tid) * EPC + j % EPC; });
+        if (last) {
+            // the elements past the last whole chunk, one per thread
+            const int i = row_chunks * EPC + tid;
+            if (p == a.parts - 1 && i < a.vocab) {
+                float x1[1] = {L::element(row, i)};
+                acc_add<1>(acc, x1, [&](int) { return i; });
+            }
+            acc = wave_merge(acc);
+            if (lane == 0) part_acc[p][wid] = acc;
+            acc = Acc{-INFINITY, 0.0f, 0.0f, 0};
+        }
+        p = np;
+        c = nc;
+    }
+}
+
+__device__ __forceinline__ Acc merge_waves(const Acc (&w)[kEntWaves])
+{
+    Acc r = w[0];
+#pragma unroll
+    for (int i = 1; i < kEntWaves; ++i) r = acc_merge(r, w[i]);
+    return r;
+}
+
+template <int DT, int U, EntMode MODE>
+__global__ __launch_bounds__(MODE == kGrouped ? kEntGroups * kEntBlock : kEntBlock) void k_entropy(EntArgs a)
+{
+    const int row = MODE == kSplit ? (int)blockIdx.x / a.parts : (int)blockIdx.x;
+    const int part = MODE == kSplit ? (int)blockIdx.x - row * a.parts : 0;
+    const int lane = threadIdx.x & (kEntWave - 1);
+    const uint8_t* base = a.logits + (int64_t)row * a.row_bytes;
+    Acc r;
+    if constexpr (MODE == kGrouped) {
+        __shared__ Acc part_acc[kEntSplitBlocks][kEntWaves];
+        grouped_states<DT, U>(a, base, part_acc);
+        __syncthreads();
+        if (threadIdx.x >= kEntWave) return;
+        r = wave_merge(lane < a.parts ? merge_waves(part_acc[lane]) : kEmpty);
+        if (lane != 0) return;
+    } else {
+        __shared__ Acc wave_acc[kEntWaves];
+        const int tid = threadIdx.x;
+        const Acc acc = wave_merge(part_state<DT, U>(a, base, part * a.per, a.per, tid));
+        if (lane == 0) wave_acc[tid >> 6] = acc;
+        __syncthreads();
+        if (tid >= (MODE == kSplit ? kEntWave : 1)) return;
+        r = merge_waves(wave_acc);
+        if constexpr (MODE == kSplit) {
+            if (!meet(a, row, part, r)) return;
+            if (tid != 0) return;
+            leave(a, row);
+        }
     }
     // Eq. 9: H = -sum p ln p = ln s - t / s with p = exp(x - m) / s and t = u / L
     const float H = __logf(r.s) - (r.u * 0.6931471805599453f) / r.s;
@@ -307,14 +429,23 @@ __global__ __launch_bounds__(kEntBlock) void k_entropy(EntArgs a)
     if (a.speculate) a.speculate[row] = Hn <= a.theta ? 1 : 0;  // Eq. 10
 }
 
-template <int DT, bool SPLIT>
+template <int DT, EntMode MODE>
 void enqueue(const EntArgs& a, hipStream_t st, void* ev0, void* ev1)
 {
-    const dim3 grid((unsigned)a.rows * (unsigned)a.parts), block(kEntBlock);
+    const dim3 grid((unsigned)a.rows * (unsigned)(MODE == kSplit ? a.parts : 1)),
+        block(MODE == kGrouped ? kEntGroups * kEntBlock : kEntBlock);
     if (ev0 && ev1)
-        hipExtLaunchKernelGGL((k_entropy<DT, kEntUnits, SPLIT>), grid, block, 0, st, (hipEvent_t)ev0, (hipEvent_t)ev1, 0, a);
+        hipExtLaunchKernelGGL((k_entropy<DT, kEntUnits, MODE>), grid, block, 0, st, (hipEvent_t)ev0, (hipEvent_t)ev1, 0, a);
     else
-        hipLaunchKernelGGL((k_entropy<DT, kEntUnits, SPLIT>), grid, block, 0, st, a);
+        hipLaunchKernelGGL((k_entropy<DT, kEntUnits, MODE>), grid, block, 0, st, a);
+}
+
+template <int DT>
+void enqueue_any(const EntArgs& a, hipStream_t st, void* ev0, void* ev1)
+{
+    if (a.parts == 1) enqueue<DT, kWhole>(a, st, ev0, ev1);
+    else if (a.slot) enqueue<DT, kSplit>(a, st, ev0, ev1);
+    else enqueue<DT, kGrouped>(a, st, ev0, ev1);
 }
 
 std::mutex g_slot_mu;
@@ -356,14 +487,16 @@ void ent_slots_give(int device, int n, EntSlot* const* given)
         if (given[i]) g_slot_taken[device] &= ~(1ull << (given[i] - (EntSlot*)p));
 }
 
-// Workgroups per row that a call of these sizes is worth. A workgroup takes 0.4
-// us a batch (fp32; 0.8 bf16) and 3 us besides; a split adds 4 us and about 0.05
-// us for every workgroup, whose release writes back an L2. So the shares are 64
-// workgroups in all, and rows that take a workgroup less than 9 us or so (16
-// batches of fp32, 12 of bf16) are not split: 65,536 fp32 logits 9.5 -> 7.4 us,
-// but 32,000 6.6 -> 7.6. Of 151,936 logits, one row of fp32 18.1 -> 7.7 us and of
-// bf16 17.6 -> 8.0, 16 rows 19.7 -> 11.4 and 19.2 -> 11.3; with up to 1,024
-// workgroups 16 rows took 16.7 and 64 rows 22.6 against 19.8.
+// Parts per row that a call of these sizes is worth. A workgroup takes 0.4 us a
+// batch (fp32; 0.8 bf16) and 3 us besides; the meeting of a row's workgroups adds
+// 2 us and about 0.05 us for every one, whose release writes back an L2. So the
+// parts are 64 in all, and rows that take a workgroup less than 9 us or so (16
+// batches of fp32, 12 of bf16) are not cut: 65,536 fp32 logits 10.4 -> 5.7 us, but
+// 32,000 5.5 -> 6.1. Of 151,936 logits, one row of fp32 18.7 -> 5.6 us and of bf16
+// 18.4 -> 6.1, 16 rows 19.3 -> 10.3 and 19.4 -> 9.8; with up to 1,024 workgroups 16
+// rows took 16.7 and 64 rows 22.6 against 19.8. Without a slot (a call recorded into a
+// graph, launch to launch) 19.1 -> 18.1 and 18.3 -> 14.4, 16 rows 19.9 -> 14.2 and
+// 19.9 -> 13.3.
 void ent_split(int64_t rows, int64_t vocab, int dtype, int* parts, int* per)
 {
     const int64_t chunks = vocab / (dtype == kBF16 ? 8 : 4), batch = (int64_t)kEntUnits * kEntBlock;
@@ -373,7 +506,7 @@ void ent_split(int64_t rows, int64_t vocab, int dtype, int* parts, int* per)
     *parts = 1;
     *per = (int)chunks;
     if (p < 2) return;
-    const int64_t c = ((chunks + p - 1) / p + kEntWave - 1) / kEntWave * kEntWave;
+    const int64_t c = ((chunks + p - 1) / p + batch - 1) / batch * batch;  // whole batches: a part of one takes a batch's time
     *per = (int)c;
     *parts = (int)((chunks + c - 1) / c);  // every part has a chunk
 }
@@ -382,13 +515,11 @@ int launch_entropy(const EntArgs& a, void* stream, void* ev0, void* ev1)
 {
     if (a.rows <= 0) return kNoLaunch;
     const hipStream_t st = (hipStream_t)stream;
-    if (a.parts < 1 || (a.parts > 1 && (!a.slot || !a.done || a.rows > kEntSplitRows ||
-                                        (int64_t)a.rows * a.parts > kEntSplitBlocks)))
+    if (a.parts < 1 || (a.parts > 1 && (a.rows > kEntSplitRows || (int64_t)a.rows * a.parts > kEntSplitBlocks)) ||
+        (a.slot && !a.done))
         return (int)hipErrorInvalidValue;
-    if (a.dtype == kBF16)
-        a.parts > 1 ? enqueue<kBF16, true>(a, st, ev0, ev1) : enqueue<kBF16, false>(a, st, ev0, ev1);
-    else
-        a.parts > 1 ? enqueue<kF32, true>(a, st, ev0, ev1) : enqueue<kF32, false>(a, st, ev0, ev1);
+    if (a.dtype == kBF16) enqueue_any<kBF16>(a, st, ev0, ev1);
+    else enqueue_any<kF32>(a, st, ev0, ev1);
     return (int)hipGetLastError();
 }
 

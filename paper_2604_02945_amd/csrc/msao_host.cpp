@@ -1483,7 +1483,8 @@ msao_status msao_draft_entropy(msao_ctx* ctx, const void* logits, int64_t rows, 
     a.draft_token = out->draft_token;
     a.speculate = out->speculate;
     // few rows are split over workgroups that meet in a slot that no call uses;
-    // a graph, whose replays come whenever they like, holds none
+    // a graph, whose replays come whenever they like, holds none. Without a slot
+    // one workgroup takes the parts of a row: the same bits
     ent_split(rows, vocab, dtype, &a.parts, &a.per);
     int slot = -1;
     if (a.parts > 1) {
@@ -1496,7 +1497,6 @@ msao_status msao_draft_entropy(msao_ctx* ctx, const void* logits, int64_t rows, 
             const int i = (ctx->next_ent + q) % ctx->n_ent;
             if (__atomic_load_n(&ctx->ent_done[i], __ATOMIC_ACQUIRE) == ctx->ent_ticket[i] && ctx->ent_slot[i]) slot = i;
         }
-        if (slot < 0) a.parts = 1;
     }
     if (slot < 0) return launched(ctx, MSAO_KERNEL_ENTROPY, (hipStream_t)stream, run_entropy, &a);
     a.slot = ctx->ent_slot[slot];

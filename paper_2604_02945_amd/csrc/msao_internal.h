@@ -368,6 +368,7 @@ int launch_score_inline(const ScoreInline& u, void* stream, void* ev0, void* ev1
 // or, for few rows, one row over the `parts` workgroups that meet in a slot.
 constexpr int kEntSplitRows = 16;                     // most rows of a split call
 constexpr int kEntSplitBlocks = 64;                   // most workgroups of one (one wavefront merges those of a row)
+constexpr int kEntGroups = 4;                         // groups of a workgroup that takes a row's parts without a slot
 constexpr int kEntSplitBatchesF32 = 16;               // fewest batches of loads of its rows
 constexpr int kEntSplitBatchesBF16 = 12;
 constexpr int kEntSlots = 4;                          // slots a context holds
@@ -386,10 +387,11 @@ struct EntSlot {
 int ent_slots_take(int device, int want, EntSlot** out);
 void ent_slots_give(int device, int n, EntSlot* const* slots);
 struct EntArgs {
-    EntSlot* slot;           // split call: its slot, and the pinned word set to ticket when it is free again
+    EntSlot* slot;           // split call: its slot (NULL: one workgroup per row), and the pinned word set to ticket when
+                             // it is free again
     uint32_t* done;
     uint32_t ticket;
-    int32_t parts, per;      // workgroups per row (1: no slot); whole 16-byte chunks of each
+    int32_t parts, per;      // parts of a row; whole 16-byte chunks of each
     const uint8_t* logits;   // row r starts at logits + r * row_bytes
     int64_t row_bytes;
     int32_t rows, vocab, dtype;

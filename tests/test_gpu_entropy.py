@@ -163,6 +163,12 @@ def test_entropy_feeds_algorithm_1(dev):
     assert np.array_equal(dec, odec) and np.array_equal(th, oth)
 
 
+def same_bits(got, want):
+    for k in ("entropy", "entropy_norm", "draft_token", "speculate"):
+        a, b = got[k].cpu().numpy(), want[k].cpu().numpy()
+        assert np.array_equal(a.view(np.uint8), b.view(np.uint8)), (k, a, b)
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("rows,batches,extra", [
     (1, 1, 1), (1, 12, -1), (2, 12, 0), (1, 16, -1), (1, 16, 0), (1, 16, 1), (2, 31, -3), (1, 64, 5), (3, 64, 64), (1, 130, 7), (15, 17, 3),
@@ -205,7 +211,8 @@ def test_split_rows_special_values(dev):
 
 def test_split_rows_in_flight_and_in_a_graph(dev):
     """More split calls in flight than a context has slots, on two streams; then
-    one recorded into a graph; every result is the same call's made alone."""
+    one recorded into a graph; every result is the same call's made alone, bit
+    for bit."""
     log("[entropy split] in flight")
     ctx = B.Context(0)
     xs = [torch.from_numpy(draft_logits(1 + i % 3, 151936, seed=i, dtype="f32")).to(dev) for i in range(12)]
@@ -229,11 +236,8 @@ def test_split_rows_in_flight_and_in_a_graph(dev):
         msao.msao_draft_entropy(x, 0.3, ctx=ctx, stream=streams[i % 2], outputs=got[i])
     torch.cuda.synchronize()
 
-    def same(g, w):
-        assert np.array_equal(g["draft_token"].cpu().numpy(), w["draft_token"].cpu().numpy())
-        np.testing.assert_allclose(g["entropy"].cpu().numpy(), w["entropy"].cpu().numpy(), rtol=0, atol=H_TOL)
     for g, w in zip(got, want):
-        same(g, w)
+        same_bits(g, w)
     graph = torch.cuda.CUDAGraph()
     with torch.cuda.graph(graph):
         msao.msao_draft_entropy(xs[0], 0.3, ctx=ctx, outputs=got[0])
@@ -242,6 +246,37 @@ def test_split_rows_in_flight_and_in_a_graph(dev):
         graph.replay()
         msao.msao_draft_entropy(xs[1], 0.3, ctx=ctx, outputs=got[1])
         torch.cuda.synchronize()
-        same(got[0], want[0])
-        same(got[1], want[1])
+        same_bits(got[0], want[0])
+        same_bits(got[1], want[1])
+    ctx.close()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("rows,batches,extra", [(1, 16, 0), (1, 16, 1), (1, 64, 5), (2, 31, -3), (3, 40, 64), (7, 17, 3), (16, 16, 7),
+                                                (16, 38, -1), (17, 16, 1), (1, 11, 0)])
+def test_results_do_not_depend_on_slots(rows, batches, extra, dtype, dev):
+    """The same rows split over workgroups and, recorded into a graph, by one
+    workgroup each: every output has the same bits, NaN and infinities included."""
+    vocab = batches * (4096 if dtype == "f32" else 8192) + extra
+    log(f"[entropy slots] {rows} x {vocab} {dtype}")
+    ctx = B.Context(0)
+    x = draft_logits(rows, -(-vocab // 8) * 8, seed=rows + batches, dtype=dtype)
+    t = to_dev(x, dtype, dev)
+    if rows >= 3:
+        t[1, vocab // 3:] = -float("inf")
+        t[2, vocab - 2] = float("nan")
+    theta = float(msao.msao_draft_entropy(t, 0.3, vocab=vocab, ctx=ctx)["entropy_norm"][0])
+    want = msao.msao_draft_entropy(t, theta, vocab=vocab, ctx=ctx)
+    got = {k: torch.zeros_like(v) for k, v in want.items()}
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        msao.msao_draft_entropy(t, theta, vocab=vocab, ctx=ctx, outputs=got)
+    for _ in range(3):
+        for v in got.values():
+            v.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        same_bits(got, want)
+    assert int(want["speculate"][0]) == 1  # theta is row 0's own value
     ctx.close()
