@@ -38,6 +38,12 @@ constexpr float kLog2e = 1.4426950408889634f;
 // that multiplies exp(x - m) in t only matters for x = -inf, whose term is
 // then 0 * -200 = 0 instead of 0 * -inf = NaN. A NaN logit still makes s NaN.
 constexpr float kMinDiff = -200.0f;
+// A maximum whose product with log2(e) is no finite float (a row, or what has
+// been seen of it, masked with the type's lowest value).
+constexpr float kFarMax = 2.3e38f;
+// Difference of two maxima in log2 units, at least what makes 2^dm 0: a difference
+// that overflows would turn the product with the sums into 0 * inf.
+__device__ __forceinline__ float max_diff(float lower, float upper) { return fmaxf((lower - upper) * kLog2e, -1000.0f); }
 
 typedef unsigned int ent_vec4 __attribute__((ext_vector_type(4)));
 typedef __amdgpu_buffer_rsrc_t ent_rsrc_t;
@@ -73,7 +79,7 @@ __device__ __forceinline__ Acc acc_merge(Acc a, Acc b)
         b = c;
     }
     if (b.s != 0.0f) {
-        const float dm = (b.m - a.m) * kLog2e;
+        const float dm = max_diff(b.m, a.m);
         const float sc = __builtin_amdgcn_exp2f(dm);
         a.u = fmaf(fmaf(dm, b.s, b.u), sc, a.u);
         a.s = fmaf(b.s, sc, a.s);
@@ -118,8 +124,7 @@ __device__ __forceinline__ Acc wave_merge(const Acc& a)
         return __float_as_int(fmaxf(__int_as_float(x), __int_as_float(y)));
     }));
     r.idx = wave_reduce(a.m == r.m ? a.idx : 0x7FFFFFFF, 0x7FFFFFFF, [](int x, int y) { return x < y ? x : y; });
-    // the lower bound (2^-1000 is 0) keeps a lane without a finite value at 0
-    const float dm = fmaxf((a.m - r.m) * kLog2e, -1000.0f);
+    const float dm = max_diff(a.m, r.m);  // (a lane without a finite value stays at 0)
     const float sc = __builtin_amdgcn_exp2f(dm);
     r.s = wave_sum(a.s * sc);
     r.u = wave_sum(fmaf(dm, a.s, a.u) * sc);
@@ -174,7 +179,7 @@ __device__ __forceinline__ void acc_add(Acc& a, const float (&x)[N], IndexOf ind
             if (x[j] == cm) js = j;
         const int at = index(js);
         if (a.s > 0.0f) {
-            const float dm = (a.m - cm) * kLog2e;
+            const float dm = max_diff(a.m, cm);
             const float sc = __builtin_amdgcn_exp2f(dm);
             a.u = fmaf(dm, a.s, a.u) * sc;
             a.s *= sc;
@@ -189,8 +194,10 @@ __device__ __forceinline__ void acc_add(Acc& a, const float (&x)[N], IndexOf ind
     // A -inf logit gives e = 0 and d = -inf, whose product must be 0, not
     // NaN. The sums are taken without a clamp on d; a -inf then shows as a
     // NaN u beside a finite s (a NaN logit makes s NaN too), and only then is
-    // u summed again with d clamped, from the values still in registers. Both
-    // ways give the same bits wherever no -inf occurs.
+    // u summed again with d clamped, from the values still in registers (the
+    // same for the lowest value beside ordinary ones). Where the maximum itself is
+    // so far from 0 that L m overflows, both sums are taken again from L (x - m).
+    // Both ways give the same bits wherever none of that occurs.
     float s = a.s, u = a.u;
 #pragma unroll
     for (int j = 0; j < N; ++j) {
@@ -199,12 +206,15 @@ __device__ __forceinline__ void acc_add(Acc& a, const float (&x)[N], IndexOf ind
         s += e;
         u = fmaf(e, d, u);
     }
-    if (__ballot(__builtin_isnan(u) && !__builtin_isnan(s)) != 0) {
+    const bool far = fabsf(a.m) > kFarMax && a.m != -INFINITY;
+    if (__ballot((__builtin_isnan(u) && !__builtin_isnan(s)) || far) != 0) {
+        s = a.s;
         u = a.u;
 #pragma unroll
         for (int j = 0; j < N; ++j) {
-            const float d = fmaf(x[j], kLog2e, nml);
+            const float d = far ? (x[j] - a.m) * kLog2e : fmaf(x[j], kLog2e, nml);
             const float e = __builtin_amdgcn_exp2f(d);
+            s += e;
             u = fmaf(e, fmaxf(d, kMinDiff * kLog2e), u);
         }
     }

@@ -280,3 +280,24 @@ def test_results_do_not_depend_on_slots(rows, batches, extra, dtype, dev):
         same_bits(got, want)
     assert int(want["speculate"][0]) == 1  # theta is row 0's own value
     ctx.close()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("rows,vocab", [(6, 151936), (40, 151936), (6, 5003)])
+def test_rows_masked_with_the_lowest_value(rows, vocab, dtype, dev):
+    """Tokens that a decoder rules out carry the type's lowest value: the tail of
+    the vocabulary, its head, and all but a few tokens, one of them the last."""
+    log(f"[entropy masks] {rows} x {vocab} {dtype}")
+    stride = -(-vocab // 8) * 8
+    x = draft_logits(rows, stride, seed=rows, dtype="f32")
+    low = float(torch.finfo(torch.float32 if dtype == "f32" else torch.bfloat16).min)
+    x[0, 2 * vocab // 3:] = low
+    x[1, :2 * vocab // 3] = low
+    for r, kept in ((2, [vocab // 2]), (3, [7, vocab // 5, vocab - 1]), (4, range(vocab // 3, vocab // 3 + 300))):
+        v = x[r, list(kept)].copy()
+        x[r] = low
+        x[r, list(kept)] = v
+    x[5] = low
+    x = x if dtype == "f32" else (torch.from_numpy(x).to(torch.bfloat16).view(torch.int16).numpy())
+    H = check(x, dtype, vocab, dev, rows_to_check=np.arange(6))[0]
+    assert np.all(np.isfinite(H))
