@@ -171,7 +171,9 @@ typedef struct {
  * MSAO_POST_BIG_SEGMENT (a launch with a selection of at least this many
  * tokens takes 1,024-thread blocks, 4096; one of more than 4,096 always does). */
 msao_status msao_create(msao_ctx** ctx, int device);
-/* Destroy a context (NULL is ignored). Waits for the context's pending uploads. */
+/* Destroy a context (NULL is ignored). Waits for the context's pending uploads
+ * and split rows of logits; if the device fails meanwhile, what these use is
+ * left allocated. */
 void msao_destroy(msao_ctx* ctx);
 /* Message of the last failed call on this context ("" if none). */
 const char* msao_last_error(const msao_ctx* ctx);

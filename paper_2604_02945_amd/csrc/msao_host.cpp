@@ -6,18 +6,17 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <atomic>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
 #include <numeric>
 #include <string>
-#include <thread>
 #include <vector>
 
 #include "../../include/msao.h"
 #include "msao_internal.h"
+#include "msao_wait.h"
 
 using namespace msao;
 
@@ -37,12 +36,14 @@ struct msao_ctx {
     uint32_t* stage_done = nullptr;   // pinned
     uint32_t stage_ticket[kStageSlots] = {};
     int stage_blocks[kStageSlots] = {};
+    hipStream_t stage_stream[kStageSlots] = {};
     int next_slot = 0;
     // slots in which the workgroups of a split row of logits meet. A call takes
     // one whose last user has set ent_done[slot] to ent_ticket[slot]
     EntSlot* ent_slot[kEntSlots] = {};
     uint32_t* ent_done = nullptr;     // pinned, behind stage_done
     uint32_t ent_ticket[kEntSlots] = {};
+    hipStream_t ent_stream[kEntSlots] = {};
     int n_ent = 0, next_ent = 0;
     // profiling: an event pair around every launch, averaged per kernel on query
     bool profiling = false;
@@ -643,21 +644,42 @@ msao_status reserve_stage(msao_ctx* ctx, int slot, size_t bytes)
     ctx->stage[slot] = nullptr;
     ctx->stage_cap[slot] = 0;
     const size_t cap = align_up(std::max<size_t>(bytes, 65536), 65536);
-    const hipError_t e = hipHostMalloc(&ctx->stage[slot], cap, hipHostMallocDefault);
+    const hipError_t e = hipHostMalloc(&ctx->stage[slot], cap, hipHostMallocCoherent);
     if (e != hipSuccess) return hip_fail(ctx, e, "hipHostMalloc");
     ctx->stage_cap[slot] = cap;
     return MSAO_OK;
 }
 
-// Until the last upload from a slot has read it. That upload was launched
-// without an error on a stream that was not being captured, so it runs.
-void wait_stage(msao_ctx* ctx, int slot)
+StreamState stream_state(hipStream_t stream)
 {
-    uint32_t* done = ctx->stage_done + slot * kUploadMaxBlocks;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    hipError_t e = hipStreamIsCapturing(stream, &cap);
+    if (e == hipSuccess && cap != hipStreamCaptureStatusNone) return StreamState::busy;  // a query would end the capture
+    if (e == hipSuccess) e = hipStreamQuery(stream);
+    if (e == hipSuccess) return StreamState::drained;
+    (void)hipGetLastError();
+    switch (e) {
+    case hipErrorNotReady:
+    case hipErrorStreamCaptureUnsupported:
+    case hipErrorStreamCaptureImplicit: return StreamState::busy;
+    case hipErrorInvalidHandle:
+    case hipErrorContextIsDestroyed: return StreamState::drained;
+    default: return StreamState::failed;
+    }
+}
+
+// Until the last upload from a slot has read it. That upload was launched
+// without an error on a stream that was not being captured, so it runs unless
+// the device fails.
+bool wait_stage(msao_ctx* ctx, int slot)
+{
+    const uint32_t* done = ctx->stage_done + slot * kUploadMaxBlocks;
     for (int b = 0; b < ctx->stage_blocks[slot]; ++b)
-        for (int spin = 0; __atomic_load_n(&done[b], __ATOMIC_ACQUIRE) != ctx->stage_ticket[slot]; ++spin)
-            if (spin >= 4096) std::this_thread::yield();
+        if (!wait_until([&] { return __atomic_load_n(&done[b], __ATOMIC_ACQUIRE) == ctx->stage_ticket[slot]; },
+                        [&] { return stream_state(ctx->stage_stream[slot]); }, wait_now_ms))
+            return false;
     ctx->stage_blocks[slot] = 0;
+    return true;
 }
 
 // Put the tables into a pinned slot and enqueue the kernel that brings them
@@ -692,8 +714,8 @@ msao_status upload(msao_ctx* ctx, const Plan& pl, int n, void* ws, hipStream_t s
     if (slotted) {
         if (!grow && ctx->stage_cap[slot] < pl.copy_bytes)
             return fail(&ctx->err, MSAO_ERR_UNSUPPORTED, "per-call tables larger than the context's reserved staging");
+        if (!wait_stage(ctx, slot)) return fail(&ctx->err, MSAO_ERR_HIP, "an earlier call's table upload has not run");
         ctx->next_slot = (slot + 1) % kStageSlots;
-        wait_stage(ctx, slot);
         if (ctx->stage_cap[slot] < pl.copy_bytes) MSAO_TRY(reserve_stage(ctx, slot, pl.copy_bytes));
         h = (uint8_t*)ctx->stage[slot];
     }
@@ -738,7 +760,10 @@ msao_status upload(msao_ctx* ctx, const Plan& pl, int n, void* ws, hipStream_t s
     const int blocks = (int)std::min<int64_t>(units, kUploadMaxBlocks);
     const int rc = captured ? launch_upload_pieces(a, blocks, stream) : launch_upload(a, blocks, stream);
     if (rc != 0) return hip_fail(ctx, (hipError_t)rc, "table upload");
-    if (slotted) ctx->stage_blocks[slot] = blocks;
+    if (slotted) {
+        ctx->stage_blocks[slot] = blocks;
+        ctx->stage_stream[slot] = stream;
+    }
     return MSAO_OK;
 }
 
@@ -1057,7 +1082,7 @@ msao_status msao_create(msao_ctx** out, int device)
     c->device = device;
     DeviceGuard guard(device);
     if ((e = hipHostMalloc((void**)&c->stage_done, sizeof(uint32_t) * (kStageSlots * kUploadMaxBlocks + kEntSlots),
-                           hipHostMallocDefault)) != hipSuccess) {
+                           hipHostMallocCoherent)) != hipSuccess) {
         g_err = std::string("hipHostMalloc: ") + hipGetErrorString(e);
         msao_destroy(c);
         return MSAO_ERR_HIP;
@@ -1094,15 +1119,21 @@ void msao_destroy(msao_ctx* ctx)
 {
     if (!ctx) return;
     DeviceGuard guard(ctx->device);
+    // what a kernel that has not run may still read or write is left behind
+    bool all = true;
     for (int i = 0; i < kStageSlots; ++i) {
-        wait_stage(ctx, i);
-        if (ctx->stage[i]) (void)hipHostFree(ctx->stage[i]);
+        if (!wait_stage(ctx, i)) all = false;
+        else if (ctx->stage[i]) (void)hipHostFree(ctx->stage[i]);
     }
     for (int i = 0; i < ctx->n_ent; ++i)
-        for (int spin = 0; ctx->ent_slot[i] && __atomic_load_n(&ctx->ent_done[i], __ATOMIC_ACQUIRE) != ctx->ent_ticket[i]; ++spin)
-            if (spin >= 4096) std::this_thread::yield();
+        if (ctx->ent_slot[i] &&
+            !wait_until([&] { return __atomic_load_n(&ctx->ent_done[i], __ATOMIC_ACQUIRE) == ctx->ent_ticket[i]; },
+                        [&] { return stream_state(ctx->ent_stream[i]); }, wait_now_ms)) {
+            ctx->ent_slot[i] = nullptr;
+            all = false;
+        }
     ent_slots_give(ctx->device, ctx->n_ent, ctx->ent_slot);
-    if (ctx->stage_done) (void)hipHostFree(ctx->stage_done);
+    if (all && ctx->stage_done) (void)hipHostFree(ctx->stage_done);
     for (int k = 0; k < MSAO_NUM_KERNELS; ++k)
         for (auto& pr : ctx->rec[k]) {
             (void)hipEventSynchronize(pr.second);
@@ -1504,8 +1535,10 @@ msao_status msao_draft_entropy(msao_ctx* ctx, const void* logits, int64_t rows, 
     a.ticket = ctx->ent_ticket[slot] + 1;
     ctx->next_ent = (slot + 1) % ctx->n_ent;
     const msao_status rc = launched(ctx, MSAO_KERNEL_ENTROPY, (hipStream_t)stream, run_entropy, &a);
-    if (rc == MSAO_OK) ctx->ent_ticket[slot] = a.ticket;
-    else ctx->ent_slot[slot] = nullptr;  // not known to be free: never used again
+    if (rc == MSAO_OK) {
+        ctx->ent_ticket[slot] = a.ticket;
+        ctx->ent_stream[slot] = (hipStream_t)stream;
+    } else ctx->ent_slot[slot] = nullptr;  // not known to be free: never used again
     return rc;
 }
 
