@@ -6,6 +6,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include "msao_keys.h"
+
 namespace msao {
 
 enum : int { kText = 0, kImage = 1, kVideo = 2, kAudio = 3, kNumMod = 4 };
@@ -64,11 +66,6 @@ struct DevSeg {
     int32_t pair, tblk;
 };
 
-// Key kinds of a selection: Ms z + Mt (E - d) in general, z or E - d alone
-// when the other weight is 0 (the same order, a narrower range); or, in a
-// learned run, a segment with a head ranked by its Eq. 3 importance.
-enum : int { kKeyZero = 0, kKeyZ = 1, kKeyE = 2, kKeyFull = 3, kKeyImp = 4 };
-constexpr uint32_t kImpKeyMax = 0x3F800000u;  // the bits of 1.0f
 
 // One selection block: a whole segment (frame -1) or one frame of a clip
 // (per-frame scope), or one of the nparts blocks of a large selection, which

@@ -1201,10 +1201,6 @@ void k_pair_inline(ScoreInline u)
 
 // ---------------------------------------------------------------- k_post
 
-
-constexpr int kRadixBits = 11;
-constexpr int kRadixBins = 1 << kRadixBits;
-
 constexpr int kMaxCand = 2048;   // radix candidates copied out of the keys
 constexpr int kSmallCand = 256;  // candidates ranked directly instead of by further digit passes
 
@@ -1622,39 +1618,6 @@ __device__ __forceinline__ void role_frame(const PostArgs& a, int f, PostShared<
     }
 }
 
-// A learned importance as a key: larger importance first. It is a sigmoid, at
-// most 1, and the bits of a positive float grow with its value, so their
-// distance below those of 1 orders it downwards; NaN and values not above 0
-// take the largest key (importance 0). (30 bits instead of the complement's
-// 32: the first digit then tells 16 values per octave apart instead of 4, and
-// few enough keys share one to be ranked directly.)
-__device__ __forceinline__ uint32_t imp_key(float m) { return m > 0.0f ? kImpKeyMax - __float_as_uint(m) : kImpKeyMax; }
-
-// The keys of a selection's tokens, key(i) = Ms z + Mt (E - d) of token i,
-// order-equivalent to L_s z / C + L_t (E - d) / E (E = C for bit sampling,
-// where Ms = L_s and Mt = L_t); when one weight is 0 the other term alone
-// orders the tokens, so it is used unscaled; or the learned importance.
-// `first`: the z values or importances; d: NULL where not used.
-struct TokenKeys {
-    const uint32_t* first;
-    const uint32_t* d;
-    int kind;
-    uint64_t Ms, Mt;
-    uint32_t E;
-    __device__ __forceinline__ uint64_t of(uint32_t z, uint32_t dd) const
-    {
-        if (kind == kKeyImp) return (uint64_t)imp_key(__uint_as_float(z));
-        return Ms * (uint64_t)z + (d ? Mt * (uint64_t)(E - dd) : 0ull);
-    }
-    __device__ __forceinline__ uint64_t at(int i) const { return of(first ? first[i] : 0u, d ? d[i] : 0u); }
-    // the same for every kind but kKeyFull, whose keys alone need more than 32 bits
-    __device__ __forceinline__ uint32_t of32(uint32_t z, uint32_t dd) const
-    {
-        if (kind == kKeyImp) return imp_key(__uint_as_float(z));
-        return z + (d ? E - dd : 0u);
-    }
-};
-
 // Appends the lanes' keys with `match` to the candidates.
 __device__ __forceinline__ void push_cand(uint64_t* cand, uint32_t* count, uint64_t x, bool match)
 {
@@ -1677,6 +1640,7 @@ __device__ __forceinline__ TokenKeys token_keys(const PostArgs& a, const SelUnit
     t.Ms = full ? su.Ms : 1ull;
     t.Mt = full ? su.Mt : 1ull;
     t.E = su.E;
+    t.mask = (1ull << key_bits(su.kmax)) - 1ull;  // (kmax is below 2^63)
     return t;
 }
 
@@ -2110,11 +2074,6 @@ __device__ __forceinline__ int keep_of(const PostArgs& a, const SelUnit& su, Pos
     return guided_keep_count(mas, su.N);
 }
 
-__device__ __forceinline__ int key_bits(const SelUnit& su)
-{
-    return su.kmax > 0 ? 64 - __clzll((long long)su.kmax) : 0;
-}
-
 // What every block of a selection does besides: kept_count, its share of the
 // -1 tail after the kept indices, and a selection that keeps none or all of
 // its tokens [s0, s1) (then the block is done: true).
@@ -2150,7 +2109,7 @@ __device__ __forceinline__ void select_in_regs(const PostArgs& a, const SelUnit&
     clear_hist(sh);  // while the keys are in flight
     __syncthreads();
     uint32_t below;
-    const KT vstar = radix_rank<NT>(sh, r, su.N, (uint32_t)k - 1, key_bits(su), (KT)0, true, &below);
+    const KT vstar = radix_rank<NT>(sh, r, su.N, (uint32_t)k - 1, key_bits(su.kmax), (KT)0, true, &below);
     place_regs<NT, K, KT>(a, sh, r, 0, su.N, vstar, (uint32_t)k - below, 0u, 0u, o,
                             su.nparts > 1 ? su.part : -1);
 }
@@ -2170,7 +2129,7 @@ __device__ __forceinline__ void select_from_memory(const PostArgs& a, const SelU
     if (select_edges<NT>(a, su, k, s0, s1, o)) return;
     const TokenKeys tk = token_keys(a, su);
     uint32_t below;
-    const uint64_t vstar = radix_rank<NT>(sh, MemKeys<NT>{tk, nullptr, N}, N, (uint32_t)k - 1, key_bits(su), (uint64_t)0, false, &below);
+    const uint64_t vstar = radix_rank<NT>(sh, MemKeys<NT>{tk, nullptr, N}, N, (uint32_t)k - 1, key_bits(su.kmax), (uint64_t)0, false, &below);
     const uint32_t ties = (uint32_t)k - below;
     // counts of keys below and equal to vstar before this block's slice (the
     // prefix [0, s0) split evenly over the wavefronts), and in each
@@ -2263,8 +2222,6 @@ __device__ __forceinline__ BigRefs big_refs(const PostArgs& a, const SelUnit& su
     return r;
 }
 
-__device__ __forceinline__ int first_shift(int bits) { return bits > kRadixBits ? bits - kRadixBits : 0; }
-
 constexpr int kBigBlock = kPostBigBlock;
 constexpr int kBigK = kBigChunk / kBigBlock;
 
@@ -2277,9 +2234,9 @@ __global__ __launch_bounds__(kBigBlock) void k_big_hist(PostArgs a)
     load_keys<kBigBlock, kBigK, uint64_t>(r, token_keys(a, su), t0, n);
     clear_hist(sh);
     __syncthreads();
-    const int shift = first_shift(key_bits(su));
+    const int shift = first_shift(key_bits(su.kmax));
     r.each([&](uint64_t x, bool in) {
-        if (in) atomicAdd(&sh.hist[(uint32_t)(x >> shift) & (kRadixBins - 1)], 1u);
+        if (in) atomicAdd(&sh.hist[first_digit(x, shift)], 1u);
     });
     __syncthreads();
     uint32_t* out = big_refs(a, su).hist + (int64_t)su.part * (kRadixBins / 2);
@@ -2336,11 +2293,11 @@ __global__ __launch_bounds__(kBigBlock) void k_big_cand(PostArgs a)
     const uint64_t ltw = wave_sum_u64(lt);
     if ((tid & (kWave - 1)) == 0 && ltw) atomicAdd(&sh.red, (unsigned long long)ltw);
     const uint32_t inb = sh.ncand;
-    const int shift = first_shift(key_bits(su));
+    const int shift = first_shift(key_bits(su.kmax));
     uint32_t m = 0;
 #pragma unroll
     for (int j = 0; j < kBigK; ++j)
-        if ((r.in >> j & 1u) && (uint32_t)(r.key[j] >> shift) == digit) m |= 1u << j;
+        if ((r.in >> j & 1u) && first_digit(r.key[j], shift) == digit) m |= 1u << j;
     uint32_t at = inb + block_exscan<kBigBlock>((uint32_t)__builtin_popcount(m), sh, &total);
     if (shift > 0) {  // otherwise the digit is the key
 #pragma unroll
@@ -2366,7 +2323,7 @@ __device__ __forceinline__ void select_big(const PostArgs& a, const SelUnit& su,
     load_keys<NT, K, uint64_t>(r, tk, t0, n);
     SelDest o;
     if (select_edges<NT>(a, su, head.k, t0, t0 + n, o)) return;
-    const int shift = first_shift(key_bits(su));
+    const int shift = first_shift(key_bits(su.kmax));
     uint64_t vstar = head.digit;
     uint32_t below = head.below, lt0 = pre.below, eq0 = pre.in_bin;
     if (shift > 0) {
