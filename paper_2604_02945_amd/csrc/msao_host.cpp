@@ -322,7 +322,8 @@ void build_plan(const msao_ctx* ctx, const msao_segment* segs, int n, int R, con
     }
     pl.big_block = max_n >= (ctx ? ctx->post_big_segment : kPostBigSegment) || max_n > kSelSmallTokens;
     const int round = 4 * (pl.big_block ? kPostBigBlock : kPostBlock);
-    pl.sel_parts = n_sels < kSelSplitMax ? std::max(1, (max_reg_n + round - 1) / round) : 1;
+    pl.sel_parts = std::max(1, (max_reg_n + round - 1) / round);
+    if (pl.big_block ? n_sels * pl.sel_parts > kSelSplitBigBlocks : n_sels >= kSelSplitMax) pl.sel_parts = 1;
     std::vector<SelUnit> big_units, mem_units;  // parts of large selections, ahead of the others
     size_t big_bytes = 0;
     for (int i = 0; i < n; ++i) {

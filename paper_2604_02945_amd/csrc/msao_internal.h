@@ -85,7 +85,9 @@ struct SelUnit {
     uint32_t big;           // a selection of k_big_hist and k_big_cand: 1 + the offset of its area, in 16 bytes (else 0)
 };
 // A selection of at most kSelRegTokens tokens is held in the registers of a
-// block's threads. While a launch has fewer than kSelSplitMax selections it
+// block's threads. While a launch has fewer than kSelSplitMax selections (of
+// kPostBlock threads; at most kSelSplitBigBlocks blocks of kPostBigBlock threads: 8
+// selections of 12,000 tokens 11.4 -> 10.8 us, but 96 of 6,000 7.5 -> 8.6) it
 // has a block for each round of quads of its longest one; every block of a
 // selection finds the largest kept key from all of the keys, and writes its
 // own round. A larger selection is listed in parts: one per chunk of kBigChunk
@@ -96,6 +98,7 @@ struct SelUnit {
 constexpr int kSelRegTokens = 16384;
 constexpr int kSelSmallTokens = 4096; // most tokens of a selection in a block of kPostBlock threads
 constexpr int kSelSplitMax = 256;
+constexpr int kSelSplitBigBlocks = 128;
 constexpr int kSelPartTokens = 2048;
 constexpr int kBigChunk = 4096;
 constexpr int kBigBins = 2048;        // first radix digit

@@ -140,10 +140,11 @@ def test_smallest_workspace(n, how, dev):
 
 
 @pytest.mark.parametrize("largest", [4095, 4096, 16384])
-@pytest.mark.parametrize("count", [255, 256, 257])
+@pytest.mark.parametrize("count", [31, 43, 64, 255, 256, 257])
 def test_one_block_or_one_per_round(count, largest, dev):
     """On both sides of the 256 selections up to which a selection is written
-    by a block per round (1,024 tokens, or 4,096 beside one of 4,096 and more)."""
+    by a block per round (1,024 tokens), and of the 128 blocks (rounds of 4,096,
+    beside a selection of 4,096 and more)."""
     print(f"[selection] {count} selections up to {largest}", flush=True)
     n = [1 + (37 * i) % 1100 for i in range(count - 5)] + [1024, 1025, 2049, 3000, largest]
     segs = [(VIDEO, 3, -(-x // 3), 40, -1.0) if i % 7 == 2 else (IMAGE, 1, x, 40, 0.0 if i % 11 == 3 else 0.37)
