@@ -734,7 +734,8 @@ msao_status upload(msao_ctx* ctx, const Plan& pl, int n, void* ws, hipStream_t s
     std::memset(&a, 0, sizeof a);
     a.src = h;
     a.dst = b;
-    a.copy_bytes = (uint32_t)pl.copy_bytes;
+    a.copy_bytes = pl.copy_bytes;
+    static_assert(sizeof a.copy_bytes == sizeof pl.copy_bytes, "tables of any size");
     a.n = n;
     a.copy_units = (int32_t)((pl.copy_bytes + kUploadCopyBytes - 1) / kUploadCopyBytes);
     // units per segment: one for each stripe of the longest run, while they are not many

@@ -320,7 +320,7 @@ struct UploadArgs {
     const uint8_t* src;      // the staged tables (the segment records first): a pinned slot, or any
                              // host memory for copy_bytes <= kUploadInline and for pieces
     uint8_t* dst;            // workspace
-    uint32_t copy_bytes;     // a multiple of 16
+    uint64_t copy_bytes;     // a multiple of 16; over 4 GiB from some ten million segments on
     int32_t n;               // segments
     int32_t copy_units, fill_parts;
     int32_t any_hash;        // the call has hash tiles

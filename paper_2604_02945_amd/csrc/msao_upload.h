@@ -31,14 +31,14 @@ __device__ __forceinline__ void fill_run(int32_t* dst, int begin, int count, int
 // The tables of `a`, staged at src.
 __device__ __forceinline__ void upload_tables(const UploadArgs& a, const uint8_t* staged)
 {
-    const int units = a.copy_units + a.n * a.fill_parts;
-    for (int u = blockIdx.x; u < units; u += gridDim.x) {
+    const int64_t units = a.copy_units + (int64_t)a.n * a.fill_parts;
+    for (int64_t u = blockIdx.x; u < units; u += gridDim.x) {
         if (u < a.copy_units) {
             // 16-byte pieces (the staged bytes and both addresses are multiples of 16)
             constexpr int V = kUploadCopyBytes / (16 * kUploadBlock);
             const uvec4* src = (const uvec4*)staged;
             uvec4* dst = (uvec4*)a.dst;
-            const uint32_t pieces = a.copy_bytes / 16u;
+            const uint32_t pieces = (uint32_t)(a.copy_bytes / 16u);
             const uint32_t p0 = (uint32_t)u * (kUploadCopyBytes / 16) + threadIdx.x;
             uvec4 v[V];
 #pragma unroll
@@ -49,7 +49,8 @@ __device__ __forceinline__ void upload_tables(const UploadArgs& a, const uint8_t
                 if (p0 + q * kUploadBlock < pieces) dst[p0 + q * kUploadBlock] = v[q];
             continue;
         }
-        const int f = u - a.copy_units, s = f / a.fill_parts, part = f - s * a.fill_parts;
+        const int64_t f = u - a.copy_units;
+        const int s = a.fill_parts == 1 ? (int)f : (int)(f / a.fill_parts), part = (int)(f - (int64_t)s * a.fill_parts);
         const DevSeg& sg = ((const DevSeg*)staged)[s];  // the segment records lead the staged tables
         fill_run(a.wi_seg, sg.wi_begin, sg.n_items, s, part, a.fill_parts);
         fill_run(a.gi_seg, sg.g_begin, sg.n_gather, s, part, a.fill_parts);

@@ -77,10 +77,10 @@ int launch_upload(const UploadArgs& a, int blocks, void* stream)
 int launch_upload_pieces(const UploadArgs& a, int blocks, void* stream)
 {
     if (blocks < 1 || blocks > kUploadMaxBlocks || a.copy_bytes % 16 != 0 || !a.src || !a.dst) return (int)hipErrorInvalidValue;
-    for (uint32_t at = 0; at < a.copy_bytes; at += kUploadPiece) {
+    for (uint64_t at = 0; at < a.copy_bytes; at += kUploadPiece) {
         UploadPiece u;
         u.dst = a.dst + at;
-        u.bytes = a.copy_bytes - at < kUploadPiece ? a.copy_bytes - at : kUploadPiece;
+        u.bytes = a.copy_bytes - at < kUploadPiece ? (uint32_t)(a.copy_bytes - at) : kUploadPiece;
         memcpy(u.tables, a.src + at, u.bytes);
         hipLaunchKernelGGL(k_upload_piece, dim3(1), dim3(kUploadBlock), 0, (hipStream_t)stream, u);
         const hipError_t e = hipGetLastError();
