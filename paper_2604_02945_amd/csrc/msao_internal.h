@@ -431,12 +431,15 @@ constexpr int kScoreBlock = 256;   // 4 wavefronts, one work item each
 // k_pair block: wavefronts on consecutive pairs of positions over the same
 // frames (four: a clip batch of 1,024 wavefronts puts one on every SIMD)
 constexpr int kPairWaves = MSAO_PAIR_WAVES;
-// k_pair's register budget: a ring of four frames of four units needs about
-// 146 VGPRs, of eight units about 250
+// k_pair's register budget: a ring of four frames of four units takes about 150
+// VGPRs (three wavefronts per SIMD would fit, and the budget gives two); the instance
+// with rings of up to eight units takes 256 and 24-29 AGPRs, one wavefront per SIMD
 constexpr int kPairWavesPerEU = 2;
 // work items of other segments that run in k_pair's launch: a launch of their
 // own for the text of one request costs 4-6 us; more than about one per SIMD
-// would be slower at k_pair's occupancy than in k_score
+// would be slower at k_pair's occupancy than in k_score. Items of any size: beside
+// a clip, 64 rows of 256 KiB take a call of 64.4 us in this launch and 66.9 in one
+// of their own, 250 rows 80.2 and 83.8
 constexpr int kPairRestItems = 1024;
 constexpr int kPairRing = 4;                  // frames in registers per k_pair wavefront (even)
 constexpr int kPairMaxRowBytes = 4096;        // rows k_pair takes: eight 512-byte units per half-wavefront

@@ -806,7 +806,10 @@ __global__ __launch_bounds__(kScoreBlock) __attribute__((amdgpu_waves_per_eu(5, 
 
 // k_score<false> with the call's tables in its arguments, so that a small call
 // is one launch shorter: an image request 17.6 -> 13.3 us in all (the upload's
-// 2.9 us on the GPU and its launch on the host), this kernel 4.5 -> 5.2. The
+// 2.9 us on the GPU and its launch on the host), this kernel 4.5 -> 5.2. Large
+// segments lose nothing by the search: four of 16,384 x 4,096 bf16 76.6 us in k_score
+// and 75.7 here, one of 65,536 x 4,096 76.1 and 76.7, nine of 200,000 x 256 187.8 and
+// 185.9, and the calls are 12-50 % shorter than with a copy command. The
 // tables for the following launches are written last: before the work item
 // they would keep scalar registers busy through it.
 __global__ __launch_bounds__(kScoreBlock) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_score_inline(ScoreInline u)

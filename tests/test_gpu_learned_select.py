@@ -180,6 +180,20 @@ def test_video_clip_with_a_head(per_frame, dev):
     run_and_check(w.segments, 2, heads, None, dev, p)
 
 
+@pytest.mark.parametrize("keep", [0.3, -1.0])
+@pytest.mark.parametrize("P", [16384, 18000])
+def test_large_selections(P, keep, dev):
+    """Selections of 16,384 tokens (one block's registers) and more (three
+    launches): an image with a head, whose frame holds at most 16,384, a clip with
+    a head of two frames of half of that, and an image without one."""
+    rng = np.random.default_rng(P)
+    seg = lambda r, m, T, n, C, k: Segment(r, m, T, n, C, "f32", k, rng.standard_normal((T * n, C)).astype(np.float32))  # noqa: E731
+    segs = [seg(0, VIDEO, 2, P // 2, 16, keep), seg(1, IMAGE, 1, 16384, 16, keep), seg(1, TEXT, 1, 5, 16, 1.0),
+            seg(0, IMAGE, 1, P, 16, 0.4)]
+    heads = [make_head(segs[0], rng, 0, 3, -0.3)[1], make_head(segs[1], rng, 128, 5, 0.1)[1], None, None]
+    run_and_check(segs, 2, heads, None, dev)
+
+
 def test_nan_rows_and_fp32_segment(dev):
     rng = np.random.default_rng(29)
     x = rng.standard_normal((24 * 24, 520)).astype(np.float32)
