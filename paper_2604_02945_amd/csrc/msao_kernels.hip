@@ -819,7 +819,7 @@ __global__ __launch_bounds__(kScoreBlock) __attribute__((amdgpu_waves_per_eu(4, 
     const int lane = threadIdx.x & (kWave - 1);
     const int w = uniform(score_block(u.a) * (kScoreBlock / kWave) + (threadIdx.x >> 6));
     if (w < u.a.t.n_wi_score) score_item<false>(u.a, ArgSegs{tables, u.up.n}.of(w), w, lane);
-    upload_tables(u.up, (const uint8_t*)tables);
+    upload_tables<int>(u.up, (const uint8_t*)tables);
 }
 
 // ---------------------------------------------------------------- k_pair
@@ -1198,7 +1198,7 @@ __global__ __launch_bounds__(kPairWaves * 64) __attribute__((amdgpu_waves_per_eu
 void k_pair_inline(ScoreInline u)
 {
     const args_ptr tables = kernel_args() + offsetof(ScoreInline, tables);
-    upload_tables(u.up, (const uint8_t*)tables);
+    upload_tables<int>(u.up, (const uint8_t*)tables);
     pair_block<WIDE, true>(u.a, ArgSegs{tables, u.up.n});
 }
 

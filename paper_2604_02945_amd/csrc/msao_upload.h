@@ -28,11 +28,13 @@ __device__ __forceinline__ void fill_run(int32_t* dst, int begin, int count, int
     }
 }
 
-// The tables of `a`, staged at src.
+// The tables of `a`, staged at src. Unit: of the units' indices (int for tables of
+// at most kUploadInline bytes, a dozen segments).
+template <typename Unit>
 __device__ __forceinline__ void upload_tables(const UploadArgs& a, const uint8_t* staged)
 {
-    const int64_t units = a.copy_units + (int64_t)a.n * a.fill_parts;
-    for (int64_t u = blockIdx.x; u < units; u += gridDim.x) {
+    const Unit units = a.copy_units + (Unit)a.n * a.fill_parts;
+    for (Unit u = blockIdx.x; u < units; u += gridDim.x) {
         if (u < a.copy_units) {
             // 16-byte pieces (the staged bytes and both addresses are multiples of 16)
             constexpr int V = kUploadCopyBytes / (16 * kUploadBlock);
@@ -49,8 +51,8 @@ __device__ __forceinline__ void upload_tables(const UploadArgs& a, const uint8_t
                 if (p0 + q * kUploadBlock < pieces) dst[p0 + q * kUploadBlock] = v[q];
             continue;
         }
-        const int64_t f = u - a.copy_units;
-        const int s = a.fill_parts == 1 ? (int)f : (int)(f / a.fill_parts), part = (int)(f - (int64_t)s * a.fill_parts);
+        const Unit f = u - a.copy_units;
+        const int s = a.fill_parts == 1 ? (int)f : (int)(f / a.fill_parts), part = (int)(f - (Unit)s * a.fill_parts);
         const DevSeg& sg = ((const DevSeg*)staged)[s];  // the segment records lead the staged tables
         fill_run(a.wi_seg, sg.wi_begin, sg.n_items, s, part, a.fill_parts);
         fill_run(a.gi_seg, sg.g_begin, sg.n_gather, s, part, a.fill_parts);

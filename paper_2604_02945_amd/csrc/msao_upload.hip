@@ -30,7 +30,7 @@ namespace {
 
 __global__ __launch_bounds__(kUploadBlock) void k_upload(UploadArgs a)
 {
-    upload_tables(a, a.src);
+    upload_tables<int64_t>(a, a.src);
     if (a.done) {
         // every thread's reads of the slot have returned (its stores took their
         // values), and nothing that it wrote need be visible to the host
@@ -47,7 +47,7 @@ __global__ __launch_bounds__(kUploadBlock) void k_upload(UploadArgs a)
 // other arguments in the 4 KiB that a launch takes.
 __global__ __launch_bounds__(kUploadBlock) void k_upload_inline(UploadInline u)
 {
-    upload_tables(u.a, (const uint8_t*)(kernel_args() + offsetof(UploadInline, tables)));
+    upload_tables<int>(u.a, (const uint8_t*)(kernel_args() + offsetof(UploadInline, tables)));
 }
 
 // One block per piece: 3,840 bytes are 240 threads' 16 bytes.
