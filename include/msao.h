@@ -38,9 +38,10 @@
  *  - Every data pointer is HIP device memory owned by the caller unless it is
  *    marked "host". The library allocates no device memory: scratch comes
  *    from the caller's workspace (size from msao_workspace_size), except for
- *    msao_run_noalloc, which uses the library's own static array. The context
- *    owns host state only (pinned staging for the small per-call tables, HIP
- *    events, the last error message).
+ *    msao_run_noalloc and for a few long rows of msao_draft_entropy, which use
+ *    static arrays of the library's own. The context owns host state only
+ *    (pinned staging for the small per-call tables, HIP events, the last error
+ *    message).
  *  - Calls are asynchronous: they enqueue on `stream` (a hipStream_t; NULL is
  *    the null stream) and return; outputs are valid once the caller has
  *    synchronised with that stream. Pointers are not retained after return.
