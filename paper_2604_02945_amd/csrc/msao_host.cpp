@@ -263,6 +263,45 @@ bool chain_is_faster(const msao_segment& s, int64_t row_bytes, int64_t pairs_tot
     return T < 16 || use < (F == T ? 0.86 : F >= 12 && pairs_total < 2 * kPairTargetWaves ? 0.85 : 0.96);
 }
 
+// Rows of a scoring work item: the fewest that reach the target bytes, unless
+// they pass it by more than a quarter (then one less, at least one).
+int64_t rows_per_item(const msao_ctx* ctx, int64_t row_bytes)
+{
+    const int64_t target = ctx ? ctx->row_item_bytes : 8192;
+    const int64_t rb = (target + row_bytes - 1) / row_bytes;
+    return rb > 1 && rb * row_bytes * 4 > target * 5 ? rb - 1 : rb;
+}
+
+bool pair_is_wide(const msao_segment& s) { return s.dtype != MSAO_BF16 || (int64_t)s.hidden * elt_size(s.dtype) > kPairNarrowRowBytes; }
+
+// Whether small wide clips are better in the k_score launch that a call's other
+// work items take anyway, where those are too many for k_pair's launch: a launch
+// of their own costs 4 us and does not overlap. Calls, chain pass : k_pair beside
+// 10, 41 and 164 MB of rows:
+//  - fp32 clips of 0.3 to 4 MB 1 : 1.03 to 1.27 beside any; of 6 to 17 MB 1.05 to 1.23,
+//    0.98 to 1.0, 0.95 to 1.03; of 19 to 50 MB 1.02 to 1.09, 0.84 to 0.97, 0.77 to 0.95;
+//  - bf16 clips of 0.7 to 5 MB 0.62 to 0.67, 0.77 to 0.81, 1.03 to 1.11; larger 0.4 to 0.8.
+// A call with narrow clips has k_pair's launch either way.
+bool clips_stay_with_rows(const msao_ctx* ctx, const msao_segment* segs, int n, int dtype)
+{
+    int64_t items = 0, rest_bytes = 0, clip_bytes = 0;
+    for (int i = 0; i < n; ++i) {
+        const msao_segment& s = segs[i];
+        const int64_t N = (int64_t)s.n_frames * s.tokens_per_frame, row = (int64_t)s.hidden * elt_size(s.dtype);
+        if (is_temporal(s)) {
+            if (!pair_is_wide(s)) return false;
+            clip_bytes += N * row;
+        } else {
+            const int64_t rb = rows_per_item(ctx, row);
+            items += (N + rb - 1) / rb;
+            rest_bytes += N * row;
+        }
+    }
+    if (items <= kPairRestItems) return false;
+    if (dtype == MSAO_BF16) return clip_bytes < 6000000 && rest_bytes > 100000000;
+    return clip_bytes < 16000000 || (clip_bytes < 56000000 && rest_bytes < 20000000);
+}
+
 // fuse_copy: a full run with compaction, where segments that keep every row
 // are copied by the scoring pass (they get no gather items).
 void build_plan(const msao_ctx* ctx, const msao_segment* segs, int n, int R, const msao_params* p,
@@ -305,6 +344,7 @@ void build_plan(const msao_ctx* ctx, const msao_segment* segs, int n, int R, con
     int64_t tok = 0, frame = 0;
     int wi = 0, gi = 0;
     int64_t chains_total = 0, pairs_total = 0;
+    const bool stay_f32 = clips_stay_with_rows(ctx, segs, n, MSAO_F32), stay_bf16 = clips_stay_with_rows(ctx, segs, n, MSAO_BF16);
     for (int i = 0; i < n; ++i)
         if (is_temporal(segs[i])) {
             chains_total += segs[i].tokens_per_frame;
@@ -471,8 +511,9 @@ void build_plan(const msao_ctx* ctx, const msao_segment* segs, int n, int R, con
             const int tblk = (s.n_frames + F - 1) / F;
             const int64_t pitems =
                 ((int64_t)((s.tokens_per_frame + 1) / 2) * tblk + kPairWaves - 1) / kPairWaves * kPairWaves;
-            const bool wide = s.dtype != MSAO_BF16 || row_bytes > kPairNarrowRowBytes;
-            if (pitems <= N && !(wide && chain_is_faster(s, row_bytes, pairs_total, F, best_cost))) {
+            const bool wide = pair_is_wide(s);
+            if (pitems <= N && !(wide && ((s.dtype == MSAO_BF16 ? stay_bf16 : stay_f32) ||
+                                          chain_is_faster(s, row_bytes, pairs_total, F, best_cost)))) {
                 d.pair = 1;
                 if (wide) pl.pair_wide = true;
                 d.tblk = tblk;
@@ -503,11 +544,7 @@ void build_plan(const msao_ctx* ctx, const msao_segment* segs, int n, int R, con
             pl.tseg.push_back(i);
             pl.any_temporal = true;
         } else if (N > 0) {
-            // the fewest rows that reach the target bytes, unless they pass it
-            // by more than a quarter (then one row less, at least one)
-            const int64_t target = ctx ? ctx->row_item_bytes : 8192, row = (int64_t)s.hidden * es;
-            int64_t rb = (target + row - 1) / row;
-            if (rb > 1 && rb * row * 4 > target * 5) --rb;
+            const int64_t rb = rows_per_item(ctx, row_bytes);
             d.per_item = (int32_t)rb;
             items = (int)((N + rb - 1) / rb);
         } else {

@@ -122,3 +122,18 @@ def test_clips_of_more_positions_than_simds_take_pairs_of(dtype, C, T, P, dev):
     are more than 1,024 pairs of positions; beside them, a clip of narrow rows."""
     log(f"[pair wide] {T} x {P} x {C} {dtype}")
     run_and_compare(clips(T + P, [(T, P, C)], dtype) + clips(1, [(5, 9, 256)], "bf16"), 2, default_params(), dev)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("rows", [4096, 4100, 52000])
+@pytest.mark.parametrize("narrow", [False, True])
+def test_small_clips_beside_many_rows(narrow, rows, dtype, dev):
+    """Small wide clips beside 1,024, 1,025 and 13,000 work items of rows (107 MB),
+    alone and with a clip of narrow rows: in k_pair's launch or left to k_score's."""
+    rng = np.random.default_rng(rows)
+    C = 1160 if dtype == "bf16" else 72
+    segs = clips(rows, [(6, 5, C), (9, 4, C)], dtype) + [_rand_seg(rng, 0, AUDIO, 1, rows, 1024, "bf16", 0.25, "relu_bg")]
+    if narrow:
+        segs += clips(2, [(5, 9, 256)], "bf16")
+    log(f"[pair wide] {dtype} beside {rows} rows, narrow {narrow}")
+    run_and_compare(segs, 2, default_params(), dev)
