@@ -150,7 +150,7 @@ struct Plan {
     std::vector<float> alpha;
     int64_t ntok = 0, nframes = 0;
     int n_wi = 0, n_gwi = 0;
-    std::vector<SelUnit> sel_unit; // selections: a segment, or a frame (per-frame scope); those over kSelRegTokens in parts
+    std::vector<SelUnit> sel_unit; // selections: a segment, or a frame (per-frame scope); those over sel_reg_tokens in parts
     int n_listed = 0, n_big_blk = 0; // the first of them: parts of those; and of these the first: chunks of large selections
     int sel_parts = 1;             // blocks for each of the others
     bool big_block = false;        // the selections take 1,024-thread blocks
@@ -350,6 +350,14 @@ void build_plan(const msao_ctx* ctx, const msao_segment* segs, int n, int R, con
             chains_total += segs[i].tokens_per_frame;
             pairs_total += (segs[i].tokens_per_frame + 1) / 2;
         }
+    // key kind of a segment's selections: a learned run ranks a segment with a head
+    // by its Eq. 3 importance
+    auto key_kind = [&](int i) {
+        const msao_segment& s = segs[i];
+        if (select_imp && learned && heads && heads[i].weight && s.tokens_per_frame > 0) return (int)kKeyImp;
+        const bool ls = q24(p->lambda_s[s.modality]) > 0, lt = q24(p->lambda_t[s.modality]) > 0 && is_temporal(s);
+        return (int)(lt ? (ls ? kKeyFull : kKeyE) : (ls ? kKeyZ : kKeyZero));
+    };
     // the sizes of the selections, for the blocks that they take
     int64_t n_sels = 0;
     int max_n = 0, max_reg_n = 0;
@@ -358,7 +366,7 @@ void build_plan(const msao_ctx* ctx, const msao_segment* segs, int n, int R, con
         const int n_u = framed ? segs[i].tokens_per_frame : segs[i].n_frames * segs[i].tokens_per_frame;
         n_sels += framed ? segs[i].n_frames : 1;
         max_n = std::max(max_n, n_u);
-        if (n_u <= kSelRegTokens) max_reg_n = std::max(max_reg_n, n_u);
+        if (n_u <= sel_reg_tokens(key_kind(i))) max_reg_n = std::max(max_reg_n, n_u);
     }
     pl.big_block = max_n >= (ctx ? ctx->post_big_segment : kPostBigSegment) || max_n > kSelSmallTokens;
     const int round = 4 * (pl.big_block ? kPostBigBlock : kPostBlock);
@@ -403,10 +411,7 @@ void build_plan(const msao_ctx* ctx, const msao_segment* segs, int n, int R, con
         // selections: the segment, or each of its frames (per-frame scope);
         // a large one is written by several blocks, each of a slice
         const bool framed = per_frame && s.n_frames >= 2 && s.tokens_per_frame > 0;
-        // a learned run ranks a segment with a head by its Eq. 3 importance
-        const bool by_imp = select_imp && learned && heads && heads[i].weight && N > 0;
-        const int kind = by_imp ? kKeyImp
-                         : d.temporal && L_t > 0 ? (L_s > 0 ? kKeyFull : kKeyE) : (L_s > 0 ? kKeyZ : kKeyZero);
+        const int kind = key_kind(i);
         auto push_selection = [&](int frame, int n_u, int kfix) {
             if (pl.no_select) return;
             SelUnit u;
@@ -429,13 +434,13 @@ void build_plan(const msao_ctx* ctx, const msao_segment* segs, int n, int R, con
             u.seg_off = d.tok_off;
             u.request = s.request;
             u.modality = s.modality;
-            const bool big = n_u > kSelRegTokens && !pl.lean;
-            if (n_u > kSelRegTokens) u.nparts = (n_u + (big ? kBigChunk : kSelPartTokens) - 1) / (big ? kBigChunk : kSelPartTokens);
+            const bool listed = n_u > sel_reg_tokens(kind), big = listed && !pl.lean;
+            if (listed) u.nparts = (n_u + (big ? kBigChunk : kSelPartTokens) - 1) / (big ? kBigChunk : kSelPartTokens);
             if (big) {
                 u.big = (uint32_t)(1 + big_bytes / 16);
                 big_bytes += big_area_bytes(n_u);
             }
-            std::vector<SelUnit>& to = big ? big_units : n_u > kSelRegTokens ? mem_units : pl.sel_unit;
+            std::vector<SelUnit>& to = big ? big_units : listed ? mem_units : pl.sel_unit;
             for (int q = 0; q < u.nparts; ++q) {
                 u.part = q;
                 to.push_back(u);

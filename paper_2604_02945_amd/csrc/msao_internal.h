@@ -84,8 +84,10 @@ struct SelUnit {
     int32_t request, modality;
     uint32_t big;           // a selection of k_big_hist and k_big_cand: 1 + the offset of its area, in 16 bytes (else 0)
 };
-// A selection of at most kSelRegTokens tokens is held in the registers of a
-// block's threads. While a launch has fewer than kSelSplitMax selections (of
+// A selection of at most kSelRegTokens tokens, or kSelRegTokens32 where its keys
+// have 32 bits (24 a thread take 120 VGPRs, 32 would spill), is held in the
+// registers of a block's threads: calls on 20,000 tokens 24.4 us in the three launches
+// of larger ones and 22.4 here, 8 of them 35.8 and 33.2. While a launch has fewer than kSelSplitMax selections (of
 // kPostBlock threads; at most kSelSplitBigBlocks blocks of kPostBigBlock threads: 8
 // selections of 12,000 tokens 11.4 -> 10.8 us, but 96 of 6,000 7.5 -> 8.6) it
 // has a block for each round of quads of its longest one; every block of a
@@ -94,8 +96,10 @@ struct SelUnit {
 // tokens after two passes of their own (k_big_hist, k_big_cand), with an area
 // of the workspace for what these hand on; or, where a caller's workspace has no
 // room for that, blocks of kSelPartTokens tokens that each search all of the
-// keys (a call on 17,000 tokens 27.8 us against 24.4, on 32,768 35.1 against 24.9).
+// keys (a call on 32,768 tokens 35.1 us against 24.9).
 constexpr int kSelRegTokens = 16384;
+constexpr int kSelRegTokens32 = 24576;
+inline int sel_reg_tokens(int kind) { return kind == kKeyFull ? kSelRegTokens : kSelRegTokens32; }
 constexpr int kSelSmallTokens = 4096; // most tokens of a selection in a block of kPostBlock threads
 constexpr int kSelSplitMax = 256;
 constexpr int kSelSplitBigBlocks = 128;
@@ -214,7 +218,7 @@ struct PostArgs {
     int32_t n_req_blocks; // then one per request
     int32_t n_frame_blocks;// then one per temporal frame
     int32_t temporal_only;// request role writes only the temporal term
-    int32_t n_sel_listed; // of the selection blocks, the first: one per record (parts of selections over kSelRegTokens)
+    int32_t n_sel_listed; // of the selection blocks, the first: one per record (parts of selections over sel_reg_tokens)
     int32_t n_big_blocks; // and of these the first: chunks of large selections
     int32_t sel_parts;    // blocks for each of the other records
     uint8_t* big;         // workspace area of the large selections

@@ -1217,7 +1217,7 @@ struct PostShared {
     static_assert(kRadixBins % NT == 0, "every thread owns the same number of radix bins");
     alignas(16) uint32_t hist[kRadixBins];  // read 16 bytes at a time by the digit scan
     uint32_t scan[kWaves];
-    uint32_t tot[kWave];      // selection: counts of each round of quads and wavefront
+    uint32_t tot[2 * kWave];  // selection: counts of each round of quads and wavefront
     uint32_t wcnt[kWaves][4];
     unsigned long long lo, hi, red;
     uint64_t vsel;            // selection: key of the wanted rank among few candidates
@@ -1754,45 +1754,45 @@ __device__ __forceinline__ int quad_first(int q, int n) { return min(4 * (q * NT
 template <int NT, int K, typename KT>
 __device__ __forceinline__ void load_keys(RegKeys<NT, K, KT>& r, const TokenKeys& t, int t0, int n)
 {
-    uint32_t zz[K], dd[K];
-#pragma unroll
-    for (int j = 0; j < K; ++j) zz[j] = dd[j] = 0u;
     r.in = 0u;
     if (n >= 4) {
-        // every load is in bounds and issued before any is used
-        if (t.first) {
-#pragma unroll
-            for (int q = 0; q < K / 4; ++q) {
-                const sel_u32x4 v = *reinterpret_cast<const sel_u32x4*>(t.first + t0 + quad_first<NT>(q, n));
-                zz[4 * q] = v.x; zz[4 * q + 1] = v.y; zz[4 * q + 2] = v.z; zz[4 * q + 3] = v.w;
-            }
-        }
-        if (t.d) {
-#pragma unroll
-            for (int q = 0; q < K / 4; ++q) {
-                const sel_u32x4 v = *reinterpret_cast<const sel_u32x4*>(t.d + t0 + quad_first<NT>(q, n));
-                dd[4 * q] = v.x; dd[4 * q + 1] = v.y; dd[4 * q + 2] = v.z; dd[4 * q + 3] = v.w;
-            }
-        }
 #pragma unroll
         for (int q = 0; q < K / 4; ++q) {
             const int skip = 4 * (q * NT + (int)threadIdx.x) - quad_first<NT>(q, n);  // tokens of other threads
             r.in |= (skip < 4 ? 0xFu << skip & 0xFu : 0u) << (4 * q);
         }
-    } else {
-        if (threadIdx.x == 0) r.in = (1u << n) - 1u;
-#pragma unroll
-        for (int j = 0; j < 3; ++j) {
-            if (r.in >> j & 1u) {
-                if (t.first) zz[j] = t.first[t0 + j];
-                if (t.d) dd[j] = t.d[t0 + j];
-            }
-        }
+    } else if (threadIdx.x == 0) {
+        r.in = (1u << n) - 1u;
     }
+    // one array's values of this thread's tokens: every load is in bounds and
+    // issued before any is used
+    auto values = [&](const uint32_t* p, uint32_t (&v)[K]) {
 #pragma unroll
-    for (int j = 0; j < K; ++j) {
-        if constexpr (sizeof(KT) == 4) r.key[j] = t.of32(zz[j], dd[j]);
-        else r.key[j] = t.of(zz[j], dd[j]);
+        for (int j = 0; j < K; ++j) v[j] = 0u;
+        if (!p) return;
+        if (n >= 4) {
+#pragma unroll
+            for (int q = 0; q < K / 4; ++q) {
+                const sel_u32x4 x = *reinterpret_cast<const sel_u32x4*>(p + t0 + quad_first<NT>(q, n));
+                v[4 * q] = x.x; v[4 * q + 1] = x.y; v[4 * q + 2] = x.z; v[4 * q + 3] = x.w;
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < 3; ++j)
+                if (r.in >> j & 1u) v[j] = p[t0 + j];
+        }
+    };
+    uint32_t zz[K];
+    if constexpr (sizeof(KT) == 4) {
+        values(t.one(), zz);
+#pragma unroll
+        for (int j = 0; j < K; ++j) r.key[j] = t.of_one(zz[j]);
+    } else {
+        uint32_t dd[K];
+        values(t.first, zz);
+        values(t.d, dd);
+#pragma unroll
+        for (int j = 0; j < K; ++j) r.key[j] = t.of(zz[j], dd[j]);
     }
 }
 
@@ -1992,7 +1992,7 @@ __device__ __forceinline__ void place_regs(const PostArgs& a, PostShared<NT>& sh
                                            KT vstar, uint32_t ties, uint32_t lt0, uint32_t eq0, const SelDest& o, int only)
 {
     constexpr int Q = K / 4, kW = NT / kWave;
-    static_assert(Q * kW <= kWave && NT * K <= 32768, "a total per lane, two 16-bit counts per word");
+    static_assert(Q * kW <= 2 * kWave && NT * K <= 32768, "two totals per lane, two 16-bit counts per word");
     const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x >> 6;
     uint32_t ltm = 0, eqm = 0;  // this thread's tokens below and equal to vstar
 #pragma unroll
@@ -2013,13 +2013,22 @@ __device__ __forceinline__ void place_regs(const PostArgs& a, PostShared<NT>& sh
         before[q] = inc - c;
     }
     __syncthreads();
-    const uint32_t tot = lane < Q * kW ? sh.tot[lane] : 0u;
-    const uint32_t ex = wave_incl_scan(tot) - tot;
+    // the totals before total e = q kW + wavefront: lane e of ex, or, of more than
+    // 64 totals, lane e / 2 of ex and, for odd e, of ex1
+    constexpr bool kTwo = Q * kW > kWave;
+    const int e0 = kTwo ? 2 * lane : lane;
+    const uint32_t tot = e0 < Q * kW ? sh.tot[e0] : 0u;
+    const uint32_t tot1 = kTwo && e0 + 1 < Q * kW ? sh.tot[e0 + 1] : 0u;
+    const uint32_t ex = wave_incl_scan(tot + tot1) - tot - tot1, ex1 = ex + tot;
     const int w = uniform(wid);
+    auto before_total = [&](int e) {
+        if constexpr (kTwo) return (uint32_t)__builtin_amdgcn_readlane((int)(e & 1 ? ex1 : ex), e >> 1);
+        return (uint32_t)__builtin_amdgcn_readlane((int)ex, e);
+    };
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
         if (only >= 0 && q != only) continue;
-        const uint32_t b = before[q] + (uint32_t)__builtin_amdgcn_readlane((int)ex, q * kW + w);
+        const uint32_t b = before[q] + before_total(q * kW + w);
         const uint32_t lt = lt0 + (b & 0xFFFFu), eq = eq0 + (b >> 16);
         uint32_t eqk = eqm >> (4 * q) & 0xFu;
         // of the equal ones, those whose number among all equal ones is below ties
@@ -2193,7 +2202,7 @@ __device__ __forceinline__ void select_from_memory(const PostArgs& a, const SelU
     }
 }
 
-// ---- selections of more than kSelRegTokens tokens
+// ---- selections of more tokens than registers hold
 //
 // Three launches, one block per chunk of kBigChunk tokens in each, so that
 // every pass over the keys is spread over the chip and each key is read three
@@ -2397,7 +2406,7 @@ __device__ __forceinline__ void role_select(const PostArgs& a, int b, PostShared
             select_from_memory<NT>(a, su, sh);
             return;
         }
-        static_assert(kSelRegTokens <= 16 * NT, "16 keys a thread hold the largest selection in registers");
+        static_assert(kSelRegTokens <= 16 * NT && kSelRegTokens32 <= 24 * NT, "the largest selections in registers");
     } else {
         static_assert(kSelSmallTokens <= 16 * NT, "16 keys a thread hold the largest selection of the small blocks");
     }
@@ -2414,7 +2423,8 @@ __device__ __forceinline__ void role_select(const PostArgs& a, int b, PostShared
     if (select_edges<NT>(a, su, k, s0, s1, o)) return;
     if (su.N <= 4 * NT) select_by_width<NT, 4>(a, su, k, o, sh);
     else if (su.N <= 8 * NT) select_by_width<NT, 8>(a, su, k, o, sh);
-    else select_by_width<NT, 16>(a, su, k, o, sh);
+    else if (NT != kPostBigBlock || su.N <= 16 * NT) select_by_width<NT, 16>(a, su, k, o, sh);
+    else if constexpr (NT == kPostBigBlock) select_in_regs<NT, 24, uint32_t>(a, su, k, o, sh);
 }
 
 // LR: a learned call (request role with head counts, descriptors and the
@@ -2687,7 +2697,7 @@ int launch_score_inline(const ScoreInline& u, void* stream, void* ev0, void* ev1
 // 1024-thread blocks (a selection is a chain of passes over its keys in one
 // block); otherwise kPostBlock threads, which leave room for the scoring of
 // other batches in flight. The blocks of selections of more than
-// kSelRegTokens tokens lead the list, and their two passes go first; ev0 is
+// more tokens than registers hold lead the list, and their two passes go first; ev0 is
 // recorded at the first launch's start, ev1 at the last one's end.
 int launch_post(const PostArgs& a, void* stream, void* ev0, void* ev1)
 {

@@ -55,11 +55,12 @@ struct TokenKeys {
         return (Ms * (uint64_t)z + (d ? Mt * (uint64_t)(E - dd) : 0ull)) & mask;
     }
     MSAO_KEYS_FN uint64_t at(int i) const { return of(first ? first[i] : 0u, d ? d[i] : 0u); }
-    // the same for every kind but kKeyFull, whose keys alone need more than 32 bits
-    MSAO_KEYS_FN uint32_t of32(uint32_t z, uint32_t dd) const
+    // The same for every kind but kKeyFull, whose keys alone need more than 32 bits
+    // and two values: v is the token's entry of `one`.
+    MSAO_KEYS_FN const uint32_t* one() const { return first ? first : d; }
+    MSAO_KEYS_FN uint32_t of_one(uint32_t v) const
     {
-        if (kind == kKeyImp) return imp_key(z) & (uint32_t)mask;
-        return (z + (d ? E - dd : 0u)) & (uint32_t)mask;
+        return (kind == kKeyImp ? imp_key(v) : kind == kKeyE ? E - v : v) & (uint32_t)mask;
     }
 };
 

@@ -41,7 +41,7 @@ static void selection(std::mt19937_64& rng, int kind, uint32_t C, uint32_t E, ui
     for (int i = 0; i < N; ++i) {
         const uint64_t k = t.at(i);
         CHECK(k <= t.mask);
-        if (kind != kKeyFull) CHECK(t.of32(t.first ? z[i] : 0u, t.d ? d[i] : 0u) == k);
+        if (kind != kKeyFull) CHECK(t.of_one(t.one() ? t.one()[i] : 0u) == k);
         if (in_range) {
             if (kind == kKeyZ) CHECK(k == z[i]);
             if (kind == kKeyE) CHECK(k == E - d[i]);

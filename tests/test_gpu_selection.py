@@ -1,5 +1,5 @@
-"""Selection over its sizes: the keys of up to 16,384 tokens sit in the
-registers of a block (4, 8 or 16 a thread), and while there are fewer than 256
+"""Selection over its sizes: the keys of up to 16,384 tokens (24,576 of one
+term) sit in the registers of a block (4, 8, 16 or 24 a thread), and while there are fewer than 256
 selections each round of four a thread is written by a block of its own; larger
 selections take the
 two passes over chunks of 4,096, or, in the smallest workspace that is
@@ -21,7 +21,7 @@ pytestmark = pytest.mark.gpu
 
 IMAGE, VIDEO = B.IMAGE, B.VIDEO
 SIZES = [1, 2, 3, 4, 5, 7, 63, 255, 256, 257, 1023, 1024, 1025, 2047, 2048, 2049, 4095, 4096, 4097, 8191, 8192, 8193,
-         16383, 16384, 16385, 20481, 40000, 65537]
+         16383, 16384, 16385, 20480, 20481, 24575, 24576, 24577, 40000, 65537]
 
 
 @pytest.fixture(scope="module")
@@ -131,7 +131,7 @@ def test_wide_keys_of_large_selections(how, dev):
     check([(IMAGE, 1, 5, 4096, 0.5), (VIDEO, 9, 2003, 4096, 0.7)], how, dev, seed=2)
 
 
-@pytest.mark.parametrize("n", [16385, 40000])
+@pytest.mark.parametrize("n", [16385, 24577, 40000])
 @pytest.mark.parametrize("how", ["spread", "tied"])
 def test_smallest_workspace(n, how, dev):
     print(f"[selection] smallest workspace {n} {how}", flush=True)
