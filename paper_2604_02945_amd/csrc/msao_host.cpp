@@ -282,14 +282,15 @@ bool pair_is_wide(const msao_segment& s) { return s.dtype != MSAO_BF16 || (int64
 //    0.98 to 1.0, 0.95 to 1.03; of 19 to 50 MB 1.02 to 1.09, 0.84 to 0.97, 0.77 to 0.95;
 //  - bf16 clips of 0.7 to 5 MB 0.62 to 0.67, 0.77 to 0.81, 1.03 to 1.11; larger 0.4 to 0.8.
 // A call with narrow clips has k_pair's launch either way.
-bool clips_stay_with_rows(const msao_ctx* ctx, const msao_segment* segs, int n, int dtype)
+// The fp32 ones, and the bf16 ones.
+std::pair<bool, bool> clips_stay_with_rows(const msao_ctx* ctx, const msao_segment* segs, int n)
 {
     int64_t items = 0, rest_bytes = 0, clip_bytes = 0;
     for (int i = 0; i < n; ++i) {
         const msao_segment& s = segs[i];
         const int64_t N = (int64_t)s.n_frames * s.tokens_per_frame, row = (int64_t)s.hidden * elt_size(s.dtype);
         if (is_temporal(s)) {
-            if (!pair_is_wide(s)) return false;
+            if (!pair_is_wide(s)) return {false, false};
             clip_bytes += N * row;
         } else {
             const int64_t rb = rows_per_item(ctx, row);
@@ -297,9 +298,9 @@ bool clips_stay_with_rows(const msao_ctx* ctx, const msao_segment* segs, int n, 
             rest_bytes += N * row;
         }
     }
-    if (items <= kPairRestItems) return false;
-    if (dtype == MSAO_BF16) return clip_bytes < 6000000 && rest_bytes > 100000000;
-    return clip_bytes < 16000000 || (clip_bytes < 56000000 && rest_bytes < 20000000);
+    if (items <= kPairRestItems) return {false, false};
+    return {clip_bytes < 16000000 || (clip_bytes < 56000000 && rest_bytes < 20000000),
+            clip_bytes < 6000000 && rest_bytes > 100000000};
 }
 
 // fuse_copy: a full run with compaction, where segments that keep every row
@@ -344,7 +345,8 @@ void build_plan(const msao_ctx* ctx, const msao_segment* segs, int n, int R, con
     int64_t tok = 0, frame = 0;
     int wi = 0, gi = 0;
     int64_t chains_total = 0, pairs_total = 0;
-    const bool stay_f32 = clips_stay_with_rows(ctx, segs, n, MSAO_F32), stay_bf16 = clips_stay_with_rows(ctx, segs, n, MSAO_BF16);
+    std::pair<bool, bool> stay{false, false};  // asked for at the first wide clip
+    bool stay_known = false;
     for (int i = 0; i < n; ++i)
         if (is_temporal(segs[i])) {
             chains_total += segs[i].tokens_per_frame;
@@ -352,21 +354,22 @@ void build_plan(const msao_ctx* ctx, const msao_segment* segs, int n, int R, con
         }
     // key kind of a segment's selections: a learned run ranks a segment with a head
     // by its Eq. 3 importance
-    auto key_kind = [&](int i) {
+    auto key_kind = [&](int i, uint32_t L_s, uint32_t L_t) {
         const msao_segment& s = segs[i];
         if (select_imp && learned && heads && heads[i].weight && s.tokens_per_frame > 0) return (int)kKeyImp;
-        const bool ls = q24(p->lambda_s[s.modality]) > 0, lt = q24(p->lambda_t[s.modality]) > 0 && is_temporal(s);
-        return (int)(lt ? (ls ? kKeyFull : kKeyE) : (ls ? kKeyZ : kKeyZero));
+        return (int)(L_t > 0 && is_temporal(s) ? (L_s > 0 ? kKeyFull : kKeyE) : (L_s > 0 ? kKeyZ : kKeyZero));
     };
     // the sizes of the selections, for the blocks that they take
     int64_t n_sels = 0;
     int max_n = 0, max_reg_n = 0;
-    for (int i = 0; i < n; ++i) {
+    for (int i = 0; i < n && !pl.no_select; ++i) {
         const bool framed = per_frame && segs[i].n_frames >= 2 && segs[i].tokens_per_frame > 0;
         const int n_u = framed ? segs[i].tokens_per_frame : segs[i].n_frames * segs[i].tokens_per_frame;
         n_sels += framed ? segs[i].n_frames : 1;
         max_n = std::max(max_n, n_u);
-        if (n_u <= sel_reg_tokens(key_kind(i))) max_reg_n = std::max(max_reg_n, n_u);
+        const int m = segs[i].modality;
+        if (n_u <= kSelRegTokens || (n_u <= kSelRegTokens32 && n_u <= sel_reg_tokens(key_kind(i, q24(p->lambda_s[m]), q24(p->lambda_t[m])))))
+            max_reg_n = std::max(max_reg_n, n_u);
     }
     pl.big_block = max_n >= (ctx ? ctx->post_big_segment : kPostBigSegment) || max_n > kSelSmallTokens;
     const int round = 4 * (pl.big_block ? kPostBigBlock : kPostBlock);
@@ -411,7 +414,7 @@ void build_plan(const msao_ctx* ctx, const msao_segment* segs, int n, int R, con
         // selections: the segment, or each of its frames (per-frame scope);
         // a large one is written by several blocks, each of a slice
         const bool framed = per_frame && s.n_frames >= 2 && s.tokens_per_frame > 0;
-        const int kind = key_kind(i);
+        const int kind = key_kind(i, L_s, L_t);
         auto push_selection = [&](int frame, int n_u, int kfix) {
             if (pl.no_select) return;
             SelUnit u;
@@ -517,7 +520,11 @@ void build_plan(const msao_ctx* ctx, const msao_segment* segs, int n, int R, con
             const int64_t pitems =
                 ((int64_t)((s.tokens_per_frame + 1) / 2) * tblk + kPairWaves - 1) / kPairWaves * kPairWaves;
             const bool wide = pair_is_wide(s);
-            if (pitems <= N && !(wide && ((s.dtype == MSAO_BF16 ? stay_bf16 : stay_f32) ||
+            if (wide && !stay_known) {
+                stay = clips_stay_with_rows(ctx, segs, n);
+                stay_known = true;
+            }
+            if (pitems <= N && !(wide && ((s.dtype == MSAO_BF16 ? stay.second : stay.first) ||
                                           chain_is_faster(s, row_bytes, pairs_total, F, best_cost)))) {
                 d.pair = 1;
                 if (wide) pl.pair_wide = true;
